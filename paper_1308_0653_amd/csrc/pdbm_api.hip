@@ -582,43 +582,62 @@ int pdbm_diag_history(pdbm_solver *h, pdbm_diag *out, int32_t cap, int32_t *n)
     int64_t k0 = (s.rec_from + de - 1) / de;     // first record since the reset
     if (k1 - k0 > HIST_CAP) k0 = k1 - HIST_CAP;
     if (k1 - k0 > cap) k0 = k1 - cap;
-    for (int64_t k = k0; k < k1; ++k)
-        HIPCHK(hipMemcpy(out + (k - k0), s.hd.hist + (k % HIST_CAP), sizeof(pdbm_diag), hipMemcpyDeviceToHost));
+    for (int64_t k = k0; k < k1;) {  // at most two runs of the ring
+        const int64_t n = std::min(k1 - k, HIST_CAP - k % HIST_CAP);
+        HIPCHK(hipMemcpyAsync(out + (k - k0), s.hd.hist + (k % HIST_CAP), n * sizeof(pdbm_diag),
+                              hipMemcpyDeviceToHost, h->st));
+        k += n;
+    }
+    HIPCHK(hipStreamSynchronize(h->st));
     *n = (int32_t)(k1 - k0);
     return PDBM_OK;
 }
 
 }  // extern "C"
 
-// f on the device: r rows of 33 * pitch elements in the paired layout of
-// elem_of; host arrays are [NQ][nr][ntheta].  Whole buffers are copied and
-// rearranged on the host.
-static hipError_t f_to_host(const Solve &s, void *host)
+// The current state to host f [NQ][nr][ntheta] (in the solve's precision, or
+// with `wide` in float64) and lam [nr][ntheta], and such arrays into buffer
+// `buf`; either pointer may be NULL.  The rearrangement runs on the device
+// through the other pair of buffers: f there holds every plane in the solve's
+// precision and, of a float32 solve, a third of them in float64.  Synchronous.
+static int planes_per_copy(const Solve &s, bool wide) { return s.fp32 && wide ? NQ / 3 : NQ; }
+
+static int state_to_host(const Solve &s, void *f, double *lam, bool wide, hipStream_t st)
 {
-    const int nr = s.p.nr, nt = s.p.ntheta;
-    const size_t esz = s.L.esz, pitch = s.L.pitch, rstride = (size_t)NQ * pitch;
-    std::vector<char> raw((size_t)nr * rstride * esz);
-    hipError_t e = hipMemcpy(raw.data(), s.hd.f[s.cur()], raw.size(), hipMemcpyDeviceToHost);
-    if (e != hipSuccess) return e;
-    for (int q = 0; q < NQ; ++q)
-        for (int ir = 0; ir < nr; ++ir)
-            for (int jt = 0; jt < nt; ++jt)
-                std::memcpy((char *)host + (((size_t)q * nr + ir) * nt + jt) * esz,
-                            raw.data() + (ir * rstride + elem_of(q, jt, pitch)) * esz, esz);
-    return hipSuccess;
+    const int cur = s.cur(), most = planes_per_copy(s, wide);
+    const size_t ncell = (size_t)s.p.nr * s.p.ntheta, plane = ncell * (wide ? sizeof(double) : s.L.esz);
+    void *stage = s.hd.f[cur ^ 1];
+    double *lstage = s.hd.lam[cur ^ 1];
+    if (lam) {
+        HIPCHK(launch_planes_out(s.hd, cur, s.fp32, 0, 0, wide, stage, lstage, st));
+        HIPCHK(hipMemcpyAsync(lam, lstage, ncell * sizeof(double), hipMemcpyDeviceToHost, st));
+    }
+    for (int q = 0; f && q < NQ; q += most) {
+        const int n = std::min(most, NQ - q);
+        HIPCHK(launch_planes_out(s.hd, cur, s.fp32, q, q + n, wide, stage, nullptr, st));
+        HIPCHK(hipMemcpyAsync((char *)f + q * plane, stage, n * plane, hipMemcpyDeviceToHost, st));
+    }
+    HIPCHK(hipStreamSynchronize(st));
+    return PDBM_OK;
 }
 
-static hipError_t f_to_device(const Solve &s, int buf, const void *host)
+static int state_to_device(const Solve &s, int buf, const void *f, const double *lam, bool wide, hipStream_t st)
 {
-    const int nr = s.p.nr, nt = s.p.ntheta;
-    const size_t esz = s.L.esz, pitch = s.L.pitch, rstride = (size_t)NQ * pitch;
-    std::vector<char> raw((size_t)nr * rstride * esz, 0);
-    for (int q = 0; q < NQ; ++q)
-        for (int ir = 0; ir < nr; ++ir)
-            for (int jt = 0; jt < nt; ++jt)
-                std::memcpy(raw.data() + (ir * rstride + elem_of(q, jt, pitch)) * esz,
-                            (const char *)host + (((size_t)q * nr + ir) * nt + jt) * esz, esz);
-    return hipMemcpy(s.hd.f[buf], raw.data(), raw.size(), hipMemcpyHostToDevice);
+    const int most = planes_per_copy(s, wide);
+    const size_t ncell = (size_t)s.p.nr * s.p.ntheta, plane = ncell * (wide ? sizeof(double) : s.L.esz);
+    void *stage = s.hd.f[buf ^ 1];
+    double *lstage = s.hd.lam[buf ^ 1];
+    if (lam) {
+        HIPCHK(hipMemcpyAsync(lstage, lam, ncell * sizeof(double), hipMemcpyHostToDevice, st));
+        HIPCHK(launch_planes_in(s.hd, buf, s.fp32, 0, 0, wide, stage, lstage, st));
+    }
+    for (int q = 0; f && q < NQ; q += most) {
+        const int n = std::min(most, NQ - q);
+        HIPCHK(hipMemcpyAsync(stage, (const char *)f + q * plane, n * plane, hipMemcpyHostToDevice, st));
+        HIPCHK(launch_planes_in(s.hd, buf, s.fp32, q, q + n, wide, stage, nullptr, st));
+    }
+    HIPCHK(hipStreamSynchronize(st));
+    return PDBM_OK;
 }
 
 extern "C" {
@@ -626,51 +645,20 @@ extern "C" {
 int pdbm_read_f(pdbm_solver *h, double *f, double *lam)
 {
     if (!h) return fail(PDBM_EINVAL, "NULL solver");
-    const Solve &s = h->s;
-    const int nr = s.p.nr, nt = s.p.ntheta, pitch = s.L.pitch;
-    const size_t ncell = (size_t)nr * nt;
-    HIPCHK(hipStreamSynchronize(h->st));
-    if (f) {
-        if (s.fp32) {
-            std::vector<float> tmp((size_t)NQ * ncell);
-            HIPCHK(f_to_host(s, tmp.data()));
-            for (size_t i = 0; i < tmp.size(); ++i) f[i] = tmp[i];
-        } else {
-            HIPCHK(f_to_host(s, f));
-        }
-    }
-    if (lam)
-        HIPCHK(hipMemcpy2D(lam, nt * sizeof(double), s.hd.lam[s.cur()], pitch * sizeof(double), nt * sizeof(double),
-                           nr, hipMemcpyDeviceToHost));
-    return PDBM_OK;
+    return state_to_host(h->s, f, lam, true, h->st);
 }
 
 int pdbm_write_f(pdbm_solver *h, const double *f, const double *lam, int64_t step)
 {
     if (!h || step < 0) return fail(PDBM_EINVAL, "bad argument");
     Solve &s = h->s;
-    const int nr = s.p.nr, nt = s.p.ntheta, pitch = s.L.pitch;
-    const size_t ncell = (size_t)nr * nt;
-    HIPCHK(hipStreamSynchronize(h->st));
+    // the state must end up in the buffer of the new step's parity
     const int cur = s.cur(), buf = (int)(step & 1);
-    if (cur != buf) {  // the state must end up in the buffer of the new step's parity
-        if (!f || !lam) {
-            HIPCHK(hipMemcpy(s.hd.f[buf], s.hd.f[cur], s.L.f, hipMemcpyDeviceToDevice));
-            HIPCHK(hipMemcpy(s.hd.lam[buf], s.hd.lam[cur], s.L.lam, hipMemcpyDeviceToDevice));
-        }
-    }
-    if (f) {
-        if (s.fp32) {
-            std::vector<float> tmp((size_t)NQ * ncell);
-            for (size_t i = 0; i < tmp.size(); ++i) tmp[i] = (float)f[i];
-            HIPCHK(f_to_device(s, buf, tmp.data()));
-        } else {
-            HIPCHK(f_to_device(s, buf, f));
-        }
-    }
-    if (lam)
-        HIPCHK(hipMemcpy2D(s.hd.lam[buf], pitch * sizeof(double), lam, nt * sizeof(double), nt * sizeof(double), nr,
-                           hipMemcpyHostToDevice));
+    if (cur != buf && !f) HIPCHK(hipMemcpyAsync(s.hd.f[buf], s.hd.f[cur], s.L.f, hipMemcpyDeviceToDevice, h->st));
+    if (cur != buf && !lam)
+        HIPCHK(hipMemcpyAsync(s.hd.lam[buf], s.hd.lam[cur], s.L.lam, hipMemcpyDeviceToDevice, h->st));
+    int rc = state_to_device(s, buf, f, lam, true, h->st);
+    if (rc) return rc;
     return s.set_step(step, h->st);
 }
 
@@ -687,7 +675,7 @@ int pdbm_get_state(pdbm_solver *h, void *buf, size_t *bytes)
 {
     if (!h || !bytes) return fail(PDBM_EINVAL, "NULL argument");
     const Solve &s = h->s;
-    const int nr = s.p.nr, nt = s.p.ntheta, pitch = s.L.pitch;
+    const int nr = s.p.nr, nt = s.p.ntheta;
     const size_t fb = (size_t)NQ * nr * nt * s.L.esz, lb = (size_t)nr * nt * sizeof(double);
     const size_t need = sizeof(BlobHeader) + fb + lb;
     if (!buf) {
@@ -698,10 +686,8 @@ int pdbm_get_state(pdbm_solver *h, void *buf, size_t *bytes)
     BlobHeader hh{BLOB_MAGIC, 1, nr, nt, s.p.precision, s.step};
     std::memcpy(buf, &hh, sizeof hh);
     char *fdst = (char *)buf + sizeof hh;
-    HIPCHK(hipStreamSynchronize(h->st));
-    HIPCHK(f_to_host(s, fdst));
-    HIPCHK(hipMemcpy2D(fdst + fb, nt * sizeof(double), s.hd.lam[s.cur()], pitch * sizeof(double), nt * sizeof(double),
-                       nr, hipMemcpyDeviceToHost));
+    int rc = state_to_host(s, fdst, (double *)(fdst + fb), false, h->st);
+    if (rc) return rc;
     *bytes = need;
     return PDBM_OK;
 }
@@ -712,17 +698,14 @@ int pdbm_set_state(pdbm_solver *h, const void *buf, size_t bytes)
     Solve &s = h->s;
     BlobHeader hh;
     std::memcpy(&hh, buf, sizeof hh);
-    const int nr = s.p.nr, nt = s.p.ntheta, pitch = s.L.pitch;
+    const int nr = s.p.nr, nt = s.p.ntheta;
     const size_t fb = (size_t)NQ * nr * nt * s.L.esz, lb = (size_t)nr * nt * sizeof(double);
     if (hh.magic != BLOB_MAGIC || hh.version != 1 || hh.nr != nr || hh.ntheta != nt || hh.precision != s.p.precision ||
         hh.step < 0 || bytes < sizeof hh + fb + lb)
         return fail(PDBM_EINVAL, "checkpoint does not match this solve");
     const char *src = (const char *)buf + sizeof hh;
-    const int b = (int)(hh.step & 1);
-    HIPCHK(hipStreamSynchronize(h->st));
-    HIPCHK(f_to_device(s, b, src));
-    HIPCHK(hipMemcpy2D(s.hd.lam[b], pitch * sizeof(double), src + fb, nt * sizeof(double), nt * sizeof(double), nr,
-                       hipMemcpyHostToDevice));
+    int rc = state_to_device(s, (int)(hh.step & 1), src, (const double *)(src + fb), false, h->st);
+    if (rc) return rc;
     return s.set_step(hh.step, h->st);
 }
 

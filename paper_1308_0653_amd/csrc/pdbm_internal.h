@@ -128,6 +128,13 @@ hipError_t launch_init_ic(const SolveDesc &d, int cur, bool fp32, const pdbm_ic 
 hipError_t launch_init_fields(const SolveDesc &d, int cur, bool fp32, const double *fields, hipStream_t st);
 hipError_t launch_moments(const SolveDesc &d, int cur, bool fp32, double *out, const DiagCtl &dc, hipStream_t st);
 int cell_blocks(int nr, int nt);
+// Planes [q0, q1) of f in buffer `cur` to or from dense device memory
+// [q1 - q0][nr][nt] in the solve's precision, or with `wide` in float64, and
+// (lam not NULL) lambda to or from dense [nr][nt].
+hipError_t launch_planes_out(const SolveDesc &d, int cur, bool fp32, int q0, int q1, bool wide, void *out,
+                             double *lam, hipStream_t st);
+hipError_t launch_planes_in(const SolveDesc &d, int cur, bool fp32, int q0, int q1, bool wide, const void *in,
+                            const double *lam, hipStream_t st);
 // Wavefront tiles of a solve marched `rows` rows at a time.
 int solve_waves(int nr, int nt, int rows);
 // Rows per wavefront of the step kernel for a solve that has the GPU to itself.

@@ -71,6 +71,10 @@ class PdbmError(RuntimeError):
 
 _lib = None
 
+# PyBytes_FromStringAndSize(NULL, n): a bytes object of n bytes still to be filled
+_new_bytes = C.pythonapi.PyBytes_FromStringAndSize
+_new_bytes.restype, _new_bytes.argtypes = C.py_object, [C.c_char_p, C.c_ssize_t]
+
 
 def lib():
     """Loads libpdbm.so (building it first only if it does not exist)."""
@@ -349,15 +353,16 @@ class Solver:
     def pdbm_get_state(self) -> bytes:
         n = C.c_size_t(0)
         _check(self.L.pdbm_get_state(self.h, None, C.byref(n)))
-        buf = C.create_string_buffer(n.value)
-        _check(self.L.pdbm_get_state(self.h, buf, C.byref(n)))
-        return buf.raw[: n.value]
+        # the blob is written straight into a fresh bytes object (no zeroing, no copy of it afterwards)
+        blob = _new_bytes(None, n.value)
+        _check(self.L.pdbm_get_state(self.h, C.c_char_p(blob), C.byref(n)))
+        return blob
 
     get_state = pdbm_get_state
 
     def pdbm_set_state(self, blob: bytes):
-        buf = C.create_string_buffer(blob, len(blob))
-        _check(self.L.pdbm_set_state(self.h, buf, len(blob)))
+        blob = bytes(blob)  # the same object if it is one
+        _check(self.L.pdbm_set_state(self.h, C.c_char_p(blob), len(blob)))
 
     set_state = pdbm_set_state
 

@@ -49,7 +49,7 @@ Layout pdbm::layout_of(const pdbm_params &p, int rows)
     L.esz = p.precision == PDBM_FP32 ? sizeof(float) : sizeof(double);
     L.pitch = pitch_of(p.ntheta);
     L.rows = rows;
-    L.nwaves = solve_waves(p.nr, p.ntheta, rows);
+    L.nwaves = rows == PATCHES ? patch_geom(p.nr, p.ntheta, p.sector).ntiles : solve_waves(p.nr, p.ntheta, rows);
     L.cblocks = cell_blocks(p.nr, p.ntheta);
     const size_t cells_p = (size_t)p.nr * L.pitch;
     L.f = align256((size_t)NQ * cells_p * L.esz);
@@ -76,6 +76,7 @@ Layout pdbm::layout_of(const pdbm_params &p, int rows)
 int pdbm::rows_per_wave(const pdbm_params &p)
 {
     const int nr = p.nr, nt = p.ntheta;
+    if (patch_geom(nr, nt, p.sector).threads > 0) return PATCHES;
     static const int env = [] {
         const char *e = std::getenv("PDBM_ROWS_PER_WAVE");
         return e ? std::atoi(e) : 0;
@@ -284,6 +285,7 @@ int Solve::init(const pdbm_params &pp, const pdbm_ic *ic, void *workspace, size_
     hd.disc = p.r_min == 0.0;
     hd.reacts = (p.w1 > 0.0 || p.w2 > 0.0) ? 1 : 0;
     hd.rows = rows;
+    if (rows == PATCHES) hd.patch = patch_geom(p.nr, p.ntheta, p.sector);
     hd.nwaves = L.nwaves;
     hd.nstrip = (p.ntheta + STRIP - 1) / STRIP;
     hd.diag_every = p.diag_every;
@@ -295,6 +297,7 @@ int Solve::init(const pdbm_params &pp, const pdbm_ic *ic, void *workspace, size_
     hd.r_min = p.r_min;
     hd.dt_dr = p.dt / hd.dr;
     hd.dt_dth = p.dt / hd.dth;
+    hd.inv2 = 0.5 / p.ntheta;
     hd.omega = std::exp(-p.dt / p.tau);
     hd.w1 = p.w1;
     hd.w2 = p.w2;
@@ -308,12 +311,15 @@ int Solve::init(const pdbm_params &pp, const pdbm_ic *ic, void *workspace, size_
     // counters, then the initial state.  Host sources of the asynchronous
     // copies (hd, zero_state) must outlive them: the caller synchronises st
     // before returning to its own caller.
-    const double dth = hd.dth;
     double2 piece[256];
     for (int j0 = 0; j0 < p.ntheta; j0 += 256) {
         const int n = std::min(256, p.ntheta - j0);
-        for (int j = 0; j < n; ++j)
-            piece[j] = make_double2(std::cos((j0 + j + 0.5) * dth), std::sin((j0 + j + 0.5) * dth));
+        for (int j = 0; j < n; ++j) {
+            // theta_j above its octant: ((2j + 1) sector mod 2 ntheta) / (2 ntheta) pi/4
+            const int64_t num = (2 * int64_t(j0 + j) + 1) * p.sector % (2 * int64_t(p.ntheta));
+            const double th = (double)num / (2.0 * p.ntheta) * (M_PI / 4.0);
+            piece[j] = make_double2(std::cos(th), std::sin(th));
+        }
         HIPCHK(hipMemcpyAsync((void *)(hd.cs + j0), piece, n * sizeof(double2), hipMemcpyHostToDevice, st));
         HIPCHK(hipStreamSynchronize(st));
     }
@@ -367,9 +373,11 @@ static bool fuse_off()
     return off;
 }
 
-bool Solve::fusable() const { return !fuse_off() && p.ntheta > 1 && L.rows <= FUSE_ROWS; }
+bool Solve::fusable() const { return !fuse_off() && !patched() && p.ntheta > 1 && L.rows <= FUSE_ROWS; }
 
-bool Solve::columnar() const { return !fuse_off() && p.ntheta == 1; }
+bool Solve::columnar() const { return !fuse_off() && !patched() && p.ntheta == 1; }
+
+int Solve::patch_steps() const { return fuse_off() ? 1 : hd.patch.k; }
 
 int Solve::reduce_records(hipStream_t st)
 {
@@ -487,9 +495,17 @@ int pdbm_step(pdbm_solver *h, int64_t nsteps)
     Solve &s = h->s;
     const bool pairs = s.fusable();
     const bool column = s.columnar();
-    const int most = column ? COL_K : 2;  // steps of one launch, at most
+    const int most = s.patched() ? s.patch_steps() : column ? COL_K : 2;  // steps of one launch, at most
     for (int64_t i = 0; i < nsteps;) {
-        if (column) {
+        if (s.patched()) {
+            // as a column's launches
+            const int nk = (int)std::min<int64_t>(most, nsteps - i);
+            HIPCHK(launch_patch(s.dd, nullptr, s.waves(), s.hd.patch.threads, nullptr, s.step, nullptr, s.flip, nk,
+                                s.fp32, s.tauf(), h->st));
+            s.step += nk;
+            s.flip ^= (nk + 1) & 1;
+            i += nk;
+        } else if (column) {
             // a single column: up to COL_K steps per launch; the state moves
             // to the other buffer, which toggles the parity unless nk is odd
             const int nk = (int)std::min<int64_t>(COL_K, nsteps - i);
@@ -500,12 +516,12 @@ int pdbm_step(pdbm_solver *h, int64_t nsteps)
             i += nk;
         } else if (pairs && nsteps - i >= 2) {
             HIPCHK(launch_step2(s.dd, nullptr, s.waves(), nullptr, s.step, nullptr, s.flip, false, s.fp32, s.tauf(),
-                                s.rot(), h->st));
+                                s.mixed(), h->st));
             s.step += 2;
             s.flip ^= 1;
             i += 2;
         } else {
-            HIPCHK(launch_step(s.dd, nullptr, s.waves(), nullptr, s.step, nullptr, s.flip, s.fp32, s.rot(), s.tauf(),
+            HIPCHK(launch_step(s.dd, nullptr, s.waves(), nullptr, s.step, nullptr, s.flip, s.fp32, s.mixed(), s.tauf(),
                                h->st));
             s.step += 1;
             i += 1;

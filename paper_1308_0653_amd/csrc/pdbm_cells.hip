@@ -12,7 +12,6 @@ namespace {
 template <typename real>
 __global__ __launch_bounds__(BLOCK) void k_moments(SolveDesc d, int cur, double *out, DiagCtl dc)
 {
-    const int nb = gridDim.x;
     const int c = blockIdx.x * BLOCK + threadIdx.x;
     const int ncell = d.nr * d.nt;
     double red[5] = {0, 0, 0, 0, 0};
@@ -41,7 +40,7 @@ __global__ __launch_bounds__(BLOCK) void k_moments(SolveDesc d, int cur, double 
             out[5 * (size_t)ncell + c] = lam;
         }
         const double ri = d.r_min + ((double)ir + 0.5) * d.dr;
-        diag_cell(red, rd, ux, uy, T, (double)e, lam, ri * d.dr * d.dth, d.Q);
+        diag_cell(red, true, rd, ux, uy, T, (double)e, lam, ri * d.dr * d.dth, d.Q);
     }
     diag_partial(dc, red, blockIdx.x);
 }
@@ -211,7 +210,8 @@ __global__ __launch_bounds__(BLOCK) void k_omega(SolveDesc d, const double *tau,
 // Planes [q0, q1) of f from the paired layout of elem_of to dense
 // [q1 - q0][nr][nt] (k_planes_out, in the solve's precision or widened to
 // float64) and back (k_planes_in), and with `lam` lambda between its padded
-// rows and dense [nr][nt].  Rearranging on the device leaves the host
+// rows and dense [nr][nt].  The caller's directions are Cartesian ones, those
+// on the device relative to the column's octant.  Rearranging on the device leaves the host
 // one plain copy: done there element by element, saving and resuming a
 // 512 x 384 float64 state took 85 ms; it takes 15 ms this way, nearly all
 // of it the copies over PCIe and the caller's fresh pages.
@@ -224,7 +224,9 @@ __global__ __launch_bounds__(BLOCK) void k_planes_out(SolveDesc d, int cur, int 
     const int ir = c / d.nt;
     const int jt = c - ir * d.nt;
     const real *f = (const real *)d.f[cur] + (int64_t)ir * d.rstride;
-    for (int q = q0; q < q1; ++q) out[(size_t)(q - q0) * ncell + c] = (T)f[elem_of(q, jt, d.pitch)];
+    const int turn = -octant_of(jt, d.nt, d.sector);
+    for (int q = q0; q < q1; ++q)
+        out[(size_t)(q - q0) * ncell + c] = (T)f[elem_of(plane_of(q, turn), jt, d.pitch)];
     if (lam) lam[c] = d.lam[cur][(int64_t)ir * d.pitch + jt];
 }
 
@@ -238,7 +240,9 @@ __global__ __launch_bounds__(BLOCK) void k_planes_in(SolveDesc d, int cur, int q
     const int ir = c / d.nt;
     const int jt = c - ir * d.nt;
     real *f = (real *)d.f[cur] + (int64_t)ir * d.rstride;
-    for (int q = q0; q < q1; ++q) f[elem_of(q, jt, d.pitch)] = (real)in[(size_t)(q - q0) * ncell + c];
+    const int turn = -octant_of(jt, d.nt, d.sector);
+    for (int q = q0; q < q1; ++q)
+        f[elem_of(plane_of(q, turn), jt, d.pitch)] = (real)in[(size_t)(q - q0) * ncell + c];
     if (lam) d.lam[cur][(int64_t)ir * d.pitch + jt] = lam[c];
 }
 

@@ -8,11 +8,25 @@
 // the 16 pairs of opposite directions interleaved per column (elem_of), so
 // that a wavefront of 64 consecutive theta cells reads one contiguous block
 // per plane or pair, one 8- or 16-byte access per lane for a pair.
-// The collision is evaluated in the Cartesian frame: f^eq depends on v.u and
-// |u|^2 only, which are the same in polar and Cartesian components, so the
-// 33 velocities are compile-time constants (speeds 0, 1.5, 3.5, 7.5, 12.5 of
-// Sec. II.B, directions i*pi/4 fixed in the Cartesian frame).  Polar
-// components are needed only for the Courant numbers and for u_r, u_theta.
+// The collision is evaluated in the Cartesian frame of the cell's octant
+// (pdbm_offsets.h): f^eq depends on v.u and |u|^2 only, which are the same in
+// polar and Cartesian components, so the 33 velocities are compile-time
+// constants (speeds 0, 1.5, 3.5, 7.5, 12.5 of Sec. II.B, directions i*pi/4
+// in that frame).  Polar components are needed only for the Courant numbers
+// and for u_r, u_theta.
+//
+// The step kernels branch on wave-uniform conditions only and select lane by
+// lane, never switching lanes off in code with many live registers: apart
+// from the DPP moves that need every lane, the compiler has placed register
+// copies between a divergent branch's end and the restore of the lane mask,
+// which left stale values in the lanes that had not taken the branch.
+//
+// Every kernel rounds a cell's update the same way: multiply-adds are written
+// out (fma), none are formed by the compiler, and sums over the speeds are
+// taken as (((rest + 1) + 2) + (3 + 4)), the order in which two or four lanes
+// that share a cell add up their parts.  A cell's new state then does not
+// depend on the kernel, the strip, the row block or the patch it is computed
+// in, so how a launch divides a grid is free to follow the load.
 
 #pragma once
 
@@ -20,6 +34,8 @@
 
 #include "pdbm_internal.h"
 #include "pdbm_offsets.h"
+
+#pragma clang fp contract(off)
 
 namespace pdbm {
 namespace {
@@ -58,40 +74,42 @@ template <typename real>
 __device__ __forceinline__ void weights(const double *A, double T, real F[5])
 {
     const double T2 = T * T, T3 = T2 * T, T4 = T2 * T2;
-    double s = 0.0;
+    double w[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         double v = A[4 * k] * T;
         v = fma(A[4 * k + 1], T2, v);
         v = fma(A[4 * k + 2], T3, v);
-        v = fma(A[4 * k + 3], T4, v);
-        F[k + 1] = (real)v;
-        s += v;
+        w[k] = fma(A[4 * k + 3], T4, v);
+        F[k + 1] = (real)w[k];
     }
-    F[0] = (real)(1.0 - 8.0 * s);
+    F[0] = (real)fma(-8.0, (w[0] + w[1]) + (w[2] + w[3]), 1.0);
 }
 
+// One ring's (speed v) share of the moments: its sum, and the momentum and
+// energy it adds.  g[0..3] and h[0..3] are directions 0..3 and 4..7.
+template <typename real>
+__device__ __forceinline__ void ring_moments(const real g[4], const real h[4], real v, real &sum, real &mx, real &my,
+                                             real &en)
+{
+    sum = ((g[0] + h[0]) + (g[2] + h[2])) + ((g[1] + h[1]) + (g[3] + h[3]));
+    const real a15 = g[1] - h[1], a37 = g[3] - h[3];
+    mx = v * fma((real)SQH, a15 - a37, g[0] - h[0]);
+    my = v * fma((real)SQH, a15 + a37, g[2] - h[2]);
+    en = (real)0.5 * v * v * sum;
+}
 // rho, rho*u (Cartesian), and e = sum f |v|^2 / 2 of one cell.
 template <typename real>
 __device__ __forceinline__ void raw_moments(const real f[NQ], real &rho, real &jx, real &jy, real &e)
 {
-    rho = f[0];
-    jx = 0;
-    jy = 0;
-    e = 0;
+    real r[4], x[4], y[4], en[4];
 #pragma unroll
-    for (int k = 1; k <= 4; ++k) {
-        const real *g = f + 1 + 8 * (k - 1);
-        const real v = (real)speed(k);
-        const real ring = ((g[0] + g[4]) + (g[2] + g[6])) + ((g[1] + g[5]) + (g[3] + g[7]));
-        const real a15 = g[1] - g[5], a37 = g[3] - g[7];
-        const real X = (g[0] - g[4]) + (real)SQH * (a15 - a37);
-        const real Y = (g[2] - g[6]) + (real)SQH * (a15 + a37);
-        rho += ring;
-        jx += v * X;
-        jy += v * Y;
-        e += (real)(0.5 * speed(k) * speed(k)) * ring;
-    }
+    for (int k = 0; k < 4; ++k)
+        ring_moments(f + 1 + 8 * k, f + 5 + 8 * k, (real)speed(k + 1), r[k], x[k], y[k], en[k]);
+    rho = ((f[0] + r[0]) + r[1]) + (r[2] + r[3]);
+    jx = (x[0] + x[1]) + (x[2] + x[3]);
+    jy = (y[0] + y[1]) + (y[2] + y[3]);
+    e = (en[0] + en[1]) + (en[2] + en[3]);
 }
 
 // 1/x: in float32 the hardware reciprocal (within 1 ulp) and one Newton step
@@ -114,8 +132,8 @@ struct EqPoly {
     {
         const real iT = inv(T);
         const real a = (real)0.5 * u2 * iT;
-        c0 = (real)1 - a + (real)0.5 * a * a;
         c1 = (real)1 - a;
+        c0 = fma((real)0.5 * a, a, c1);
         c2 = (real)0.5 * c1;
         wx = ux * iT;
         wy = uy * iT;
@@ -129,8 +147,8 @@ struct EqPoly {
     __device__ __forceinline__ void parts(real z, real &ev, real &od) const
     {
         const real z2 = z * z;
-        ev = c0 + z2 * (c2 + z2 * (real)(1.0 / 24.0));
-        od = z * (c1 + z2 * (real)(1.0 / 6.0));
+        ev = fma(z2, fma(z2, (real)(1.0 / 24.0), c2), c0);
+        od = z * fma(z2, (real)(1.0 / 6.0), c1);
     }
     // P(z) and P(-z)
     __device__ __forceinline__ void eval(real z, real &pp, real &pm) const
@@ -159,8 +177,8 @@ __device__ __forceinline__ void pair_coll(const EqPoly<real> &EP, real z, real r
     real ev, od;
     EP.parts(z, ev, od);
     const real rb = rB * z;
-    E = ev * rA + od * rb;
-    O = od * rA + ev * rb;
+    E = fma(ev, rA, od * rb);
+    O = fma(od, rA, ev * rb);
 }
 // f^new of one direction from its collision part c = E +- O.  (acr, act and
 // v enter as they are, not as the products v acr, v act: acr is the same in
@@ -169,7 +187,7 @@ __device__ __forceinline__ void pair_coll(const EqPoly<real> &EP, real z, real r
 template <typename real>
 __device__ __forceinline__ real dir_new(real c, real s, real x, real v, real acr, real act, real nbr, real nbt)
 {
-    return c + s * x + v * (acr * nbr + act * nbt);
+    return fma(v, fma(acr, nbr, act * nbt), fma(s, x, c));
 }
 
 template <typename real>
@@ -177,7 +195,7 @@ __device__ __forceinline__ void equilibrium(const double *A, real rho, real ux, 
 {
     real F[5];
     weights(A, (double)T, F);
-    const real u2 = ux * ux + uy * uy;
+    const real u2 = fma(ux, ux, uy * uy);
     const EqPoly<real> P(ux, uy, u2, T);
     f[0] = rho * F[0] * P.c0;
 #pragma unroll
@@ -220,6 +238,30 @@ __device__ __forceinline__ double wave_sum(double x)
                             __builtin_amdgcn_readlane(__double2loint(x), 63));
 }
 
+// The value lane l ^ x holds, x = 1 or 2 (a permutation within each group of
+// four lanes).
+template <int X>
+__device__ __forceinline__ float lane_xor(float v)
+{
+    constexpr int ctl = X == 1 ? 0xB1 : 0x4E;  // quad_perm [1,0,3,2] or [2,3,0,1]
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), ctl, 0xf, 0xf, false));
+}
+template <int X>
+__device__ __forceinline__ double lane_xor(double v)
+{
+    constexpr int ctl = X == 1 ? 0xB1 : 0x4E;
+    return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), ctl, 0xf, 0xf, false),
+                            __builtin_amdgcn_mov_dpp(__double2loint(v), ctl, 0xf, 0xf, false));
+}
+// The sum of v over the LPC lanes of a cell (1, 2 or 4 adjacent lanes).
+template <int LPC, typename T>
+__device__ __forceinline__ T cell_sum(T v)
+{
+    if constexpr (LPC >= 2) v += lane_xor<1>(v);
+    if constexpr (LPC == 4) v += lane_xor<2>(v);
+    return v;
+}
+
 // Sums v[0..4] over the workgroup; the result is valid in thread 0.
 __device__ __forceinline__ void block_sum5(double v[5])
 {
@@ -257,19 +299,17 @@ __device__ __forceinline__ void diag_partial(const DiagCtl &dc, double v[5], int
     }
 }
 
-// Contribution of one cell to the drift report.
-__device__ __forceinline__ void diag_cell(double v[5], double rho, double ux, double uy, double T, double e, double lam,
-                                          double w, double Q)
+// Contribution of one cell (where `valid`) to the drift report.
+__device__ __forceinline__ void diag_cell(double v[5], bool valid, double rho, double ux, double uy, double T, double e,
+                                          double lam, double w, double Q)
 {
     const bool finite = isfinite(rho) && isfinite(T) && isfinite(ux) && isfinite(uy) && isfinite(lam);
-    if (!finite) {
-        v[3] += 1.0;
-        return;
-    }
-    if (rho <= 0.0 || T <= 0.0) v[4] += 1.0;
-    v[0] += rho * w;
-    v[1] += e * w;
-    v[2] += rho * Q * (1.0 - lam) * w;
+    const bool ok = valid && finite, bad = valid && !finite, nonphys = ok && (rho <= 0.0 || T <= 0.0);
+    v[3] += bad ? 1.0 : 0.0;
+    v[4] += nonphys ? 1.0 : 0.0;
+    v[0] += ok ? rho * w : 0.0;
+    v[1] += ok ? e * w : 0.0;
+    v[2] += ok ? rho * Q * (1.0 - lam) * w : 0.0;
 }
 
 // ------------------------------------------------- wavefront strips --
@@ -438,19 +478,21 @@ __device__ __forceinline__ void settle(T &v)
 // store of a plane or pair covers whole cache lines; lanes past the last
 // column own a padding column.  The second row ahead is requested a whole row
 // of compute before it is first needed.
-template <typename real, bool ROT>
+// MIXED: the strips of the grid may hold columns of more than one octant,
+// whose directions are turned against one another at the lanes turn_left and
+// turn_right.
+template <typename real, bool MIXED>
 struct Strip {
     DescPtr dp;
     __amdgpu_buffer_rsrc_t fin, fout, lin, lout;
     uint32_t vo, vo2, vol;   // byte offsets of this lane's column: rest plane, pair, lambda
     uint32_t vos, vos2, vols;  // ... of the lane's own column (the padding for periodic images)
-    uint32_t vh1, vh2, vhl;  // byte offsets of this lane's halo gathers (plane and column)
+    uint32_t vh1, vh2, vhl, vhs;  // byte offsets of this lane's halo gathers (plane and column)
     uint32_t row_bytes, lrow_bytes, rest_bytes, pair_bytes;
-    uint32_t poff[4];     // rotated sectors: byte offset of the pair holding this lane's directions dd, dd + 4
-    bool pswap[4];        // ... and whether its members come in the other order
-    int lane, pc, rot;    // physical column, direction shift of this lane's data
+    StripTurns turns;
+    int lane, pc;         // physical column
     bool useful;
-    bool turned;          // rotated sectors: some lane of the wavefront holds turned data (wave-uniform)
+    bool turn_left, turn_right;  // MIXED: the neighbour on that side lies in the octant before or after
 
     __device__ __forceinline__ Strip(DescPtr dp_, const StepBufs &b, int strip) : dp(dp_)
     {
@@ -464,10 +506,13 @@ struct Strip {
         lrow_bytes = rb.lrow;
         rest_bytes = rb.rest;
         pair_bytes = rb.pair;
-        const StripOffsets o = strip_offsets(dp->nt, dp->pitch, dp->sector, ROT, (int)sizeof(real), rb, strip, lane);
+        turns = strip_turns(dp->inv2, dp->sector, strip);
+        const StripOffsets o = strip_offsets(turns, dp->inv2, dp->nt, dp->pitch, dp->sector, MIXED, (int)sizeof(real),
+                                             rb, strip, lane);
         pc = o.pc;
-        rot = o.rot;
         useful = o.useful;
+        turn_left = o.turn_left;
+        turn_right = o.turn_right;
         vo = o.vo;
         vo2 = o.vo2;
         vol = o.vol;
@@ -477,71 +522,25 @@ struct Strip {
         vh1 = o.vh1;
         vh2 = o.vh2;
         vhl = o.vhl;
-#pragma unroll
-        for (int dd = 0; dd < 4; ++dd) {
-            poff[dd] = o.poff[dd];
-            pswap[dd] = o.pswap[dd];
-        }
-        turned = ROT && __builtin_amdgcn_ballot_w64(rot != 0) != 0;
+        vhs = o.vhs;
     }
 
     __device__ __forceinline__ void load_row(int row, real f[NQ], double &lam) const
     {
         uint32_t so = (uint32_t)row * row_bytes;
         bload(f[0], fin, vo, so);
-        if (ROT && sizeof(real) == 8 && !turned) {
-            // float64, no lane of the strip holding turned data (every strip
-            // but one with periodic images past the last column): plain pair
-            // loads, half as many as the member loads below (a 1024 x 512
-            // float64 half annulus took 45.9 against 48.4 us per step with
-            // member loads throughout)
+        so = opaque(so + rest_bytes);
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const uint32_t sk = so + (uint32_t)k * 4u * pair_bytes;
-#pragma unroll
-                for (int dd = 0; dd < 4; ++dd) bload2(f[1 + 8 * k + dd], f[5 + 8 * k + dd], fin, poff[dd], sk);
-            }
-        } else if (ROT && sizeof(real) == 8) {
-            // this lane's data of direction dir lives in direction (dir + rot) % 8;
-            // float64: each member loaded on its own, straight into its
-            // register (with a pair load and a select, the one wavefront of
-            // the SIMD waited for each load as it was made: 104.1 against
-            // 63.0 us per step of a 1024 x 512 half annulus)
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const uint32_t sk = so + (uint32_t)k * 4u * pair_bytes;
-#pragma unroll
-                for (int dd = 0; dd < 4; ++dd) {
-                    const uint32_t m = pswap[dd] ? (uint32_t)sizeof(real) : 0u;
-                    bload(f[1 + 8 * k + dd], fin, poff[dd] + m, sk);
-                    bload(f[5 + 8 * k + dd], fin, (poff[dd] + (uint32_t)sizeof(real)) - m, sk);
-                }
-            }
-        } else if (ROT) {
-            // this lane's data of direction dir lives in direction (dir + rot) % 8
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const uint32_t sk = so + (uint32_t)k * 4u * pair_bytes;
-#pragma unroll
-                for (int dd = 0; dd < 4; ++dd) {
-                    real a, b;
-                    bload2(a, b, fin, poff[dd], sk);
-                    f[1 + 8 * k + dd] = pswap[dd] ? b : a;
-                    f[5 + 8 * k + dd] = pswap[dd] ? a : b;
-                }
-            }
-        } else {
-            so = opaque(so + rest_bytes);
-#pragma unroll
-            for (int c = 0; c < 16; ++c) {
-                bload2(f[1 + 8 * (c >> 2) + (c & 3)], f[5 + 8 * (c >> 2) + (c & 3)], fin, vo2, so);
-                so = opaque(so + pair_bytes);
-            }
+        for (int c = 0; c < 16; ++c) {
+            bload2(f[1 + 8 * (c >> 2) + (c & 3)], f[5 + 8 * (c >> 2) + (c & 3)], fin, vo2, so);
+            so = opaque(so + pair_bytes);
         }
         bload(lam, lin, vol, (uint32_t)row * lrow_bytes);
     }
 
-    // The halo values of row `row`: h[0], h[1] for f, h[2] for lambda.
+    // The halo values of row `row`, in the frame of the strip's lane beside
+    // them: every plane (h[0], h[1]; one-step march) or the upwind ones (hs;
+    // two-step march), and lambda.
     __device__ __forceinline__ void load_halo(int row, real h[2], double &hl) const
     {
         const uint32_t so = (uint32_t)row * row_bytes;
@@ -549,29 +548,12 @@ struct Strip {
         bload(h[1], fin, vh2, so);
         bload(hl, lin, vhl, (uint32_t)row * lrow_bytes);
     }
+    __device__ __forceinline__ void load_upwind_halo(int row, real &hs, double &hl) const
+    {
+        bload(hs, fin, vhs, (uint32_t)row * row_bytes);
+        bload(hl, lin, vhl, (uint32_t)row * lrow_bytes);
+    }
 };
-
-// (cos, sin) of an angle turned by m pi / 4: the angle of a periodic image
-// of a rotated sector, m sector widths on, from that of its physical column.
-__device__ __forceinline__ double2 turn_cs(double2 cs, int m)
-{
-    double c = cs.x, s = cs.y;
-    if (m & 1) {
-        const double c1 = SQH * (c - s), s1 = SQH * (c + s);
-        c = c1;
-        s = s1;
-    }
-    if (m & 2) {
-        const double c1 = -s;
-        s = c;
-        c = c1;
-    }
-    if (m & 4) {
-        c = -c;
-        s = -s;
-    }
-    return make_double2(c, s);
-}
 
 // Wave-uniform copy of lane l of v.
 __device__ __forceinline__ float lane_value(float v, int l)
@@ -604,7 +586,7 @@ template <typename real>
 struct Cell {
     real rho, e, ux, uy, u2, T, beta, omega, keep, Bz;
     double Td, a, b;
-    bool on;
+    bool on, any;  // the cell reacts; some cell of the wavefront does
     real F[5];
     EqPoly<real> EP;
 
@@ -619,42 +601,81 @@ struct Cell {
     // from rho, e (members) and the momentum jx, jy
     __device__ __forceinline__ void init_moments(DescPtr dp, real jx, real jy, double lc, real om)
     {
+        init_state(dp, jx, jy, lc, om);
+        weights(dp->A, Td, F);
+    }
+    // ... everything but the weights F
+    __device__ __forceinline__ void init_state(DescPtr dp, real jx, real jy, double lc, real om)
+    {
         const real irho = inv(rho);
         ux = jx * irho;
         uy = jy * irho;
-        u2 = ux * ux + uy * uy;
-        T = e * irho - (real)0.5 * u2;
+        u2 = fma(ux, ux, uy * uy);
+        T = fma(e, irho, (real)-0.5 * u2);
         Td = (double)T;
-        weights(dp->A, Td, F);
         EP = EqPoly<real>(ux, uy, u2, T);
         a = 0.0;
         b = 0.0;
         beta = (real)0;  // no reaction: R = 0
         on = dp->reacts && Td > dp->T_th;
-        if (on) {
+        any = __builtin_amdgcn_ballot_w64(on) != 0;
+        if (any) {
             const double p = (double)rho * Td;
-            a = dp->w1 * ipow(p, dp->m);
-            b = dp->w2 * ipow(p, dp->n);
-            const double R = (1.0 - lc) * (a + b * lc);
-            beta = (real)(dp->Q * R * dp->dt / (2.0 * Td * Td));
+            a = on ? dp->w1 * ipow(p, dp->m) : 0.0;
+            b = on ? dp->w2 * ipow(p, dp->n) : 0.0;
+            const double R = (1.0 - lc) * fma(b, lc, a);
+            beta = on ? (real)(dp->Q * R * dp->dt / (2.0 * Td * Td)) : (real)0;
         }
         omega = om;
         keep = (real)1 - omega;
         Bz = (real)-2 * beta * T;
     }
-    // the rest particle after collision (it does not stream)
-    __device__ __forceinline__ real rest(real x0) const
+    // the BGK and chemical factor of speed v: 1 - omega + beta (v^2 + u^2 - 2T)
+    __device__ __forceinline__ real factor(real v) const { return fma(beta, fma((real)-2, T, v * v + u2), keep); }
+    // the rest particle after collision (it does not stream), F0 its weight
+    __device__ __forceinline__ real rest(real x0, real F0) const
     {
-        return rho * F[0] * EP.c0 * (keep + beta * (u2 - (real)2 * T)) + omega * x0;
+        return fma(omega, x0, rho * F0 * EP.c0 * factor((real)0));
     }
+    // what an opposite pair of speed v keeps of itself: omega - v (acr + act)
+    __device__ __forceinline__ real stay(real v, real a) const { return fma(-v, a, omega); }
     // lambda after the closed-form Cochran step
     __device__ __forceinline__ double reacted(DescPtr dp, double lc) const
     {
-        if (on && a + b > 0.0) {
-            const double q1 = (1.0 - lc) * exp(-(a + b) * dp->dt);
-            return 1.0 - (a + b) * q1 / ((a + b * lc) + b * q1);
-        }
-        return lc;
+        if (!any) return lc;
+        const double q1 = (1.0 - lc) * exp(-(a + b) * dp->dt);
+        const double l = 1.0 - (a + b) * q1 / fma(b, q1, fma(b, lc, a));
+        return on && a + b > 0.0 ? l : lc;
+    }
+    // u_r and u_theta at polar angle (cos, sin) = cs
+    __device__ __forceinline__ double ur(double2 cs) const { return fma((double)ux, cs.x, (double)uy * cs.y); }
+    __device__ __forceinline__ double ut(double2 cs) const { return fma((double)uy, cs.x, -((double)ux * cs.y)); }
+    // lambda after the step, from its upwind neighbours: radial Courant
+    // factor kr = dt/dr, azimuthal kt = dt/(r dtheta)
+    __device__ __forceinline__ double lambda(DescPtr dp, double lc, double urp, double utp, double kr, double kt,
+                                             double lr, double lt) const
+    {
+        return fma(-(fabs(utp) * kt), lc - lt, fma(-(fabs(urp) * kr), lc - lr, reacted(dp, lc)));
+    }
+};
+
+// Courant magnitudes per unit speed of the directions dd = 0..3 (dd + 4 the
+// same) at polar angle theta' (cos, sin) = cs, and their polar components.
+template <typename real>
+struct Polar {
+    real r[4], t[4];
+    __device__ __forceinline__ explicit Polar(double2 cs)
+    {
+        const real c = (real)cs.x, s = (real)cs.y;
+        // v_r = v (cos(dd pi/4) cos + sin(dd pi/4) sin), v_theta = v (sin(dd pi/4) cos - cos(dd pi/4) sin)
+        r[0] = c;
+        r[1] = (real)SQH * (c + s);
+        r[2] = s;
+        r[3] = (real)SQH * (s - c);
+        t[0] = -s;
+        t[1] = (real)SQH * (c - s);
+        t[2] = c;
+        t[3] = (real)SQH * (c + s);
     }
 };
 
@@ -678,12 +699,10 @@ __device__ __forceinline__ real omega_at(DescPtr dp, uint32_t vo, uint32_t so)
 
 // Row `row` of the strip into f, or a ghost row outside [0, nr): below r_min
 // the zero-gradient copy of row 0 or the disc-centre rule f(-1, j, k, i) =
-// f(0, j, k, (i+4)%8) (Sec. II.D; discs are sectors 1, 2 or 4, so only the
-// rotated-sector variant meets one at run time); above r_max the
-// zero-gradient copy of row nr-1.  `edge` holds the boundary row the ghost
-// copies.
-template <typename real, bool ROT>
-__device__ __forceinline__ void row_or_ghost(const Strip<real, ROT> &S, int row, real f[NQ], double &lam,
+// f(0, j, k, (i+4)%8) (Sec. II.D); above r_max the zero-gradient copy of row
+// nr-1.  `edge` holds the boundary row the ghost copies.
+template <typename real, bool MIXED>
+__device__ __forceinline__ void row_or_ghost(const Strip<real, MIXED> &S, int row, real f[NQ], double &lam,
                                              const real edge[NQ], double ledge)
 {
     if (row >= 0 && row < S.dp->nr) {
@@ -705,14 +724,14 @@ __device__ __forceinline__ void row_or_ghost(const Strip<real, ROT> &S, int row,
 // (down = false): prev (LDS, this lane's column) holds row i-1 and fn row
 // i+1; marching inward the roles swap.  prev is replaced by row i as it is
 // consumed.  mr[dd] / mt[dd]: which side is upwind for direction dd (its
-// opposite dd+4 takes the other side).
-template <typename real, bool ROT, bool TAUF>
-__device__ __forceinline__ void update_row(const Strip<real, ROT> &S, int ir, real (*prev)[64], const real fc[NQ],
+// opposite dd+4 takes the other side); evaluated from the angle here, for
+// either marching direction, which costs selects the two-step kernel avoids.
+template <typename real, bool MIXED, bool TAUF>
+__device__ __forceinline__ void update_row(const Strip<real, MIXED> &S, int ir, real (*prev)[64], const real fc[NQ],
                                            const real fn[NQ], const real hf[2], double hlam, double lbehind,
                                            double lc, double lahead,
                                            const bool mr[4], const bool mt[4], const real acr[4], const real ctv[4],
-                                           bool lr_behind, double csx, double csy, real om, double red[5],
-                                           bool diag)
+                                           bool lr_behind, double2 cs, real om, double red[5], bool diag)
 {
     const DescPtr dp = S.dp;
     // the cell's exp(-dt/tau): with TAUF `om`, loaded by march a row ahead
@@ -723,21 +742,14 @@ __device__ __forceinline__ void update_row(const Strip<real, ROT> &S, int ir, re
         omc = omega_at<real, TAUF>(dp, S.vo, (uint32_t)ir * S.rest_bytes);
     // (1)-(3) moments, weights, f^eq polynomial, BGK and chemical factors
     const Cell<real> C(dp, fc, lc, omc);
-    const real rho = C.rho, e = C.e, ux = C.ux, uy = C.uy, u2 = C.u2, T = C.T;
-    const real beta = C.beta, omega = C.omega, keep = C.keep, Bz = C.Bz;
-    const double Td = C.Td;
-    const real *F = C.F;
-    const EqPoly<real> &EP = C.EP;
 
     // azimuthal Courant magnitudes of this row (the geometric 1/r term)
     const double ri = dp->r_min + ((double)ir + 0.5) * dp->dr;
-    const real kt = (real)(dp->dt_dth / ri);
-    real act[4], aa[4];
+    const double ktd = dp->dt_dth / ri;
+    const real kt = (real)ktd;
+    real act[4];
 #pragma unroll
-    for (int dd = 0; dd < 4; ++dd) {
-        act[dd] = fabs(ctv[dd]) * kt;
-        aa[dd] = acr[dd] + act[dd];
-    }
+    for (int dd = 0; dd < 4; ++dd) act[dd] = fabs(ctv[dd]) * kt;
 
     const bool store = S.useful;
     const int lane = S.lane;
@@ -750,28 +762,26 @@ __device__ __forceinline__ void update_row(const Strip<real, ROT> &S, int ir, re
     // rest particle: no streaming
     // every lane stores, periodic images into their own column of the row
     // padding (see stage_row)
-    const real rest = rho * F[0] * EP.c0 * (keep + beta * (u2 - (real)2 * T)) + omega * fc[0];
-    bstore(rest, S.fout, S.vos, rowoff);
+    bstore(C.rest(fc[0], C.F[0]), S.fout, S.vos, rowoff);
 
 #pragma unroll
     for (int k = 1; k <= 4; ++k) {
         const real v = (real)speed(k);
-        const real rF = rho * F[k];
-        const real rA = rF * (keep + beta * (v * v + u2 - (real)2 * T)), rB = rF * Bz;
+        const real rF = C.rho * C.F[k];
+        const real rA = rF * C.factor(v), rB = rF * C.Bz;
         const int base = 1 + 8 * (k - 1);
         // the ring's new values, stored together under one lane mask (in
-        // halves where the rotated sector's per-lane plane offsets already
-        // hold registers)
-        constexpr int G = ROT ? 2 : 4;  // directions dd per store group
+        // halves where the turned neighbours already hold registers)
+        constexpr int G = MIXED ? 2 : 4;  // directions dd per store group
         real o[8];
 #pragma unroll
         for (int dd = 0; dd < 4; ++dd) {
             real E, O;
-            pair_coll(EP, v * EP.w(dd), rA, rB, E, O);
-            const real s = omega - v * aa[dd];
+            pair_coll(C.EP, v * C.EP.w(dd), rA, rB, E, O);
+            const real s = C.stay(v, acr[dd] + act[dd]);
 #pragma unroll
             for (int sgn = 0; sgn < 2; ++sgn) {
-                const int q = base + dd + 4 * sgn;
+                const int dir = dd + 4 * sgn, q = base + dir;
                 const real x = fc[q];
                 // upwind neighbours: C >= 0 takes the lower one (Sec. II.C)
                 const real behind = prev[q][lane];
@@ -781,16 +791,22 @@ __device__ __forceinline__ void update_row(const Strip<real, ROT> &S, int ir, re
                 // both shifts and both halo values are taken by every lane
                 // (a DPP read of a lane switched off by a branch would return
                 // 0), then selected; lanes 0 and 63 take the halo columns
-                const real sl = from_left(x), sr = from_right(x);
+                real sl = from_left(x), sr = from_right(x);
+                if constexpr (MIXED) {
+                    // a neighbour in the next octant: its directions are turned by one
+                    const real tl = from_left(fc[base + ((dir + 1) & 7)]), tr = from_right(fc[base + ((dir + 7) & 7)]);
+                    sl = S.turn_left ? tl : sl;
+                    sr = S.turn_right ? tr : sr;
+                }
                 const real hl = halo_left(hf, q), hr = halo_right(hf, q);
                 const real left = lane == 0 ? hl : sl;
                 const real right = lane == 63 ? hr : sr;
                 const bool tl = sgn == 0 ? mt[dd] : !mt[dd];
                 const real nbt = tl ? left : right;
-                o[dd + 4 * sgn] = dir_new(sgn == 0 ? E + O : E - O, s, x, v, acr[dd], act[dd], nbr, nbt);
+                o[dir] = dir_new(sgn == 0 ? E + O : E - O, s, x, v, acr[dd], act[dd], nbr, nbt);
             }
-            // lanes holding rotated sector images store into the padding
-            // too (their values are never read)
+            // lanes holding periodic images store into the padding too
+            // (their values are never read)
             if (dd % G == G - 1) {
 #pragma unroll
                 for (int e = dd + 1 - G; e <= dd; ++e)
@@ -800,45 +816,38 @@ __device__ __forceinline__ void update_row(const Strip<real, ROT> &S, int ir, re
     }
 
     // (4) lambda: closed-form Cochran step, then upwind by own-cell u
-    const double uxd = (double)ux, uyd = (double)uy;
-    const double urp = uxd * csx + uyd * csy;
-    const double utp = -uxd * csy + uyd * csx;
-    const double lreac = C.reacted(dp, lc);
+    const double urp = C.ur(cs), utp = C.ut(cs);
     const double sll = from_left(lc), slr = from_right(lc);
     const double hll = lane_value(hlam, 0), hlr = lane_value(hlam, 1);
     const double lleft = lane == 0 ? hll : sll;
     const double lright = lane == 63 ? hlr : slr;
     const double lr = (urp >= 0.0) == lr_behind ? lbehind : lahead;
     const double lt = utp >= 0.0 ? lleft : lright;
-    const double lnew = lreac - fabs(urp) * dp->dt_dr * (lc - lr) - fabs(utp) * (dp->dt_dth / ri) * (lc - lt);
-    bstore(lnew, S.lout, S.vols, (uint32_t)ir * S.lrow_bytes);
+    bstore(C.lambda(dp, lc, urp, utp, dp->dt_dr, ktd, lr, lt), S.lout, S.vols, (uint32_t)ir * S.lrow_bytes);
 
-    if (diag && store) diag_cell(red, (double)rho, uxd, uyd, Td, (double)e, lc, ri * dp->dr * dp->dth, dp->Q);
+    if (diag)
+        diag_cell(red, store, (double)C.rho, (double)C.ux, (double)C.uy, C.Td, (double)C.e, lc, ri * dp->dr * dp->dth,
+                  dp->Q);
 }
 
 // Work of one wavefront: strip `strip`, rows [i0, i1), marched outward or,
 // with `down`, inward.  prev: this wavefront's [NQ][64] LDS slots.
-template <typename real, bool ROT, bool TAUF>
+template <typename real, bool MIXED, bool TAUF>
 __device__ __forceinline__ void march(DescPtr dp, const StepBufs &bufs, int strip, int i0, int i1, bool down,
                                       real (*prev)[64], double red[5], bool diag)
 {
-    const Strip<real, ROT> S(dp, bufs, strip);
+    const Strip<real, MIXED> S(dp, bufs, strip);
     const int lane = S.lane;
     const double2 cs = dp->cs[S.pc];
-    const real cth = (real)cs.x, sth = (real)cs.y;
-    // polar components of directions dd = 0..3 at theta_j (dd+4 is the negative):
-    // v_r = v (cos(dd pi/4) cos th + sin(dd pi/4) sin th),
-    // v_theta = v (sin(dd pi/4) cos th - cos(dd pi/4) sin th)
-    const real crv[4] = {cth, (real)SQH * (cth + sth), sth, (real)SQH * (sth - cth)};
-    const real ctv[4] = {-sth, (real)SQH * (cth - sth), cth, (real)SQH * (cth + sth)};
+    const Polar<real> V(cs);
     const real kr = (real)dp->dt_dr;
     real acr[4];
     bool mr[4], mt[4];
 #pragma unroll
     for (int dd = 0; dd < 4; ++dd) {
-        acr[dd] = fabs(crv[dd]) * kr;
-        mr[dd] = (crv[dd] >= (real)0) != down;  // true: the upwind radial neighbour is the row behind
-        mt[dd] = ctv[dd] >= (real)0;            // true: the upwind azimuthal neighbour is lane-1
+        acr[dd] = fabs(V.r[dd]) * kr;
+        mr[dd] = (V.r[dd] >= (real)0) != down;  // true: the upwind radial neighbour is the row behind
+        mt[dd] = V.t[dd] >= (real)0;            // true: the upwind azimuthal neighbour is lane-1
     }
     const int step = down ? -1 : 1;
     const int first = down ? i1 - 1 : i0;
@@ -868,8 +877,8 @@ __device__ __forceinline__ void march(DescPtr dp, const StepBufs &bufs, int stri
         if constexpr (TAUF) {
             if (n + 1 < count) on = omega_at<real, true>(dp, S.vo, (uint32_t)(ir + step) * S.rest_bytes);
         }
-        update_row<real, ROT, TAUF>(S, ir, prev, fc, fn, hc, hlc, lp, lc, ln, mr, mt, acr, ctv, !down, cs.x, cs.y, oc,
-                                    red, diag);
+        update_row<real, MIXED, TAUF>(S, ir, prev, fc, fn, hc, hlc, lp, lc, ln, mr, mt, acr, V.t, !down, cs, oc, red,
+                                      diag);
         oc = on;
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
@@ -890,7 +899,6 @@ __device__ __forceinline__ void march(DescPtr dp, const StepBufs &bufs, int stri
         asm volatile("" ::: "memory");
     }
 }
-
 
 // Whether step `s` of a solve makes a drift record.
 __device__ __forceinline__ bool records(DescPtr dp, int64_t s)

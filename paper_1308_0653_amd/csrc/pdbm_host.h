@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "pdbm_internal.h"
+#include "pdbm_offsets.h"
 
 namespace pdbm {
 
@@ -33,7 +34,12 @@ struct Layout {
     size_t esz;
 };
 
+// `rows`: rows per wavefront of the marching kernels, or PATCHES for a solve
+// stepped on patches (patch_geom).
+constexpr int PATCHES = 0;
 Layout layout_of(const pdbm_params &p, int rows);
+// Rows per wavefront of a packed solve, or PATCHES.
+int batch_rows(const pdbm_params &p);
 class Solve;
 // Non-equilibrium measures of the current state into host `out`
 // [NONEQ][nr][ntheta] (staged in the idle f buffer; synchronises st).
@@ -70,14 +76,17 @@ class Solve {
 
     int cur() const { return (int)((step + flip) & 1); }
     // Whether two steps may go in one launch: ntheta > 1 and row blocks of
-    // at most FUSE_ROWS rows (either precision, any sector; PDBM_FUSE=0
-    // turns it off).
+    // at most FUSE_ROWS rows, not stepped on patches (either precision, any
+    // sector; PDBM_FUSE=0 turns it off).
     bool fusable() const;
     // Whether a launch may take up to COL_K steps: a single theta column
     // (PDBM_FUSE=0 turns it off: one step per launch, k_step).
     bool columnar() const;
+    // Whether its launches step patches of the grid, up to geom.k steps each.
+    bool patched() const { return hd.patch.threads > 0; }
+    int patch_steps() const;  // ... of this many steps at most
     int waves() const { return L.nwaves; }
-    bool rot() const { return p.sector != 8; }
+    bool mixed() const { return !whole_octants(p.ntheta, p.sector); }
     bool tauf() const { return hd.omegaf != nullptr; }  // relaxes with a per-cell tau
     // Sets the step count on host and device (stream must be idle).
     int set_step(int64_t s, hipStream_t st);

@@ -20,10 +20,13 @@ constexpr int FUSE_ROWS = 16;   // most rows per wavefront of the two-step kerne
 constexpr int COL_K = 8;                  // steps per launch of the single-column kernel, at most
 constexpr int COL_W = STRIP - 2 * COL_K;  // rows a wavefront owns in a single-column solve (48)
 
+constexpr int PATCH_LANES = 4;            // lanes per cell of the small-grid kernel
+constexpr int PACK_PATCH_THREADS = 256;   // its workgroups in packs
+
 // Layout of f within one r row (33 * pitch elements): the rest particle's
 // plane [pitch], then the 16 pairs of opposite directions of each speed, pair
-// c = 4 (k - 1) + (i mod 4) holding directions i and i + 4 interleaved per
-// column ([pitch][2]).  The pair of a cell is one 16-byte (float64) or
+// c = 4 (k - 1) + (i mod 4) holding directions i and i + 4 (relative to the
+// column's octant, see pdbm_offsets.h) interleaved per column ([pitch][2]).  The pair of a cell is one 16-byte (float64) or
 // 8-byte (float32) access, and the two members are updated together.
 __host__ __device__ constexpr int pair_of(int q) { return 4 * ((q - 1) / 8) + ((q - 1) & 3); }
 __host__ __device__ constexpr int member_of(int q) { return ((q - 1) & 7) >> 2; }
@@ -32,6 +35,14 @@ __host__ __device__ constexpr int64_t elem_of(int q, int64_t col, int64_t pitch)
 {
     return q == 0 ? col : pitch + 2 * pitch * pair_of(q) + 2 * col + member_of(q);
 }
+
+// Patches of the small-grid kernel (pdbm_offsets.h): a workgroup owns rows x
+// cols cells of the grid and holds them with a halo of k rows and columns.
+struct PatchGeom {
+    int rows, cols, k;   // owned rows and columns; halo = most steps per launch
+    int nbc, ntiles;     // patches beside one another; all of them
+    int threads;         // of a workgroup, PATCH_LANES per cell (256 or 512); 0: no patches
+};
 
 // Per-solve state in device memory written by the host.
 struct SolveState {
@@ -44,7 +55,7 @@ struct SolveState {
 struct SolveDesc {
     void *f[2];         // float or double, r rows of NQ * pitch elements in the layout of elem_of
     double *lam[2];     // [nr][pitch]
-    const double2 *cs;  // [ntheta] (cos theta_j, sin theta_j)
+    const double2 *cs;  // [ntheta] (cos, sin) of theta_j above its octant (pdbm_offsets.h)
     SolveState *state;
     double *wpart;      // [PART_RING][nwaves][5] per-wavefront drift partial sums, slot (record % PART_RING)
     pdbm_diag *hist;    // [HIST_CAP] drift reports, record k for step k * diag_every
@@ -56,9 +67,11 @@ struct SolveDesc {
     int64_t nsteps;   // the solve stops advancing once it has taken this many steps
     double r_min, dr, dth;
     double dt_dr, dt_dth;  // dt/dr, dt/dtheta
+    double inv2;           // 1 / (2 nt) (octant_by)
     double omega;          // exp(-dt/tau) of the parameters' tau
     double w1, w2, Q, T_th, dt;
     double A[16];  // F_k(T) = sum_n A[(k-1)*4+n-1] T^n
+    PatchGeom patch;  // its patches, where it is stepped on them (threads > 0)
     void *omegaf;  // float or double [nr][pitch] per-cell exp(-dt/tau) (PDBM_TAU_FIELD), else NULL
 };
 
@@ -75,8 +88,8 @@ struct DiagCtl {
 // One step of every solve listed: `descs` is a device array of solve
 // descriptions; `tiles` maps each wavefront tile of the launch to (solve,
 // tile of that solve), or is NULL for a single solve (descs[0], tiles
-// 0..ntiles-1).  All solves share the precision; `rot` selects the variant
-// for sectors other than the full annulus, `tauf` the variant that relaxes
+// 0..ntiles-1).  All solves share the precision; `mixed` selects the variant
+// for grids whose octants are not whole strips, `tauf` the variant that relaxes
 // each cell with its own exp(-dt/tau) from SolveDesc::omegaf.
 // The step a solve takes is bases[solve] + step_off (bases NULL: step_off);
 // a solve whose step is at or beyond its nsteps is left alone.  A step that
@@ -85,7 +98,7 @@ struct DiagCtl {
 // flips[i] ^ flip (flips NULL: flip), the parity its two-step launches have
 // left.
 hipError_t launch_step(const SolveDesc *descs, const uint2 *tiles, int ntiles, const int64_t *bases, int64_t step_off,
-                       const int *flips, int flip, bool fp32, bool rot, bool tauf, hipStream_t st);
+                       const int *flips, int flip, bool fp32, bool mixed, bool tauf, hipStream_t st);
 // Up to COL_K steps (nk) of single-column solves (ntheta = 1) in one launch
 // of k_column; tiles, bases, step_off, flips and flip as launch_step.  Solve
 // i takes min(nk, steps it has left) steps from buffer (s + flip_i) & 1 into
@@ -96,12 +109,17 @@ hipError_t launch_column(const SolveDesc *descs, const uint2 *tiles, int ntiles,
 // step_off, flips and flip as launch_step): reads buffer (s + flip_i) & 1 and
 // writes the other one, so the caller toggles flip_i.  A solve with one step
 // left, or every solve with `single`, takes one step and keeps its parity.
-// ntheta > 1, rows per wavefront at most FUSE_ROWS; `rot` selects the
-// variant for sectors other than the full annulus (discs included).  Makes the drift
-// records of the steps it takes as launch_step does; `tauf` as launch_step.
+// At least a column per octant and more than one, rows per wavefront at most
+// FUSE_ROWS.  Makes the drift records of the steps it takes as launch_step
+// does; `mixed` and `tauf` as launch_step.
 hipError_t launch_step2(const SolveDesc *descs, const uint2 *tiles, int ntiles, const int64_t *bases,
-                        int64_t step_off, const int *flips, int flip, bool single, bool fp32, bool tauf, bool rot,
+                        int64_t step_off, const int *flips, int flip, bool single, bool fp32, bool tauf, bool mixed,
                         hipStream_t st);
+// Up to nk steps (at most SolveDesc::patch.k) of solves stepped on patches,
+// workgroups of `threads` each; everything else as launch_column (a tile is a
+// workgroup here).
+hipError_t launch_patch(const SolveDesc *descs, const uint2 *tiles, int ntiles, int threads, const int64_t *bases,
+                        int64_t step_off, const int *flips, int flip, int nk, bool fp32, bool tauf, hipStream_t st);
 // Per-cell relaxation factors omegaf[i][j] = exp(-dt / tau[i * nt + j]) from
 // a dense float64 tau field in device memory, or all equal to `uniform`
 // with tau NULL; stored in the solve's precision.

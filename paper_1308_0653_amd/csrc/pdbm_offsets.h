@@ -10,19 +10,60 @@
 // 4 GiB (checked at create).
 #pragma once
 
+#include <math.h>
 #include <stdint.h>
 
 #include "pdbm_internal.h"
 
 namespace pdbm {
 
-constexpr int ROT_NONE = 0;
+// Frames.  Column j keeps its directions relative to its octant o(j), the
+// multiple of pi/4 at or below theta_j: "direction i" of a cell means the
+// Cartesian direction (i + o) % 8, at angle i pi/4 - theta' to e_r with
+// theta' = theta_j - o pi/4 in [0, pi/4).  In that frame the signs of all
+// velocity components are the same in every column: directions 0, 1, 2, 7
+// point outward (C_r >= 0, upwind neighbour below), 3 to 6 inward; 1 to 4
+// point along +theta (upwind neighbour on the left), 5, 6, 7, 0 along -theta.
+// Columns are numbered on past the ends of the sector: column nt is the image
+// of column 0 one sector further round, its data that of column 0, its octant
+// o(0) + sector.  So the rotated periodic halo of Sec. II.D is the plain rule
+// between neighbouring columns, in or out of the grid: direction i of column
+// c is direction i + o(c) - o(c') of column c'.
+__host__ __device__ constexpr int wraps_of(int c, int n) { return c >= 0 ? c / n : -((n - 1 - c) / n); }  // floor(c / n)
+__host__ __device__ constexpr int octant_of(int col, int nt, int sector)
+{
+    return wraps_of((2 * col + 1) * sector, 2 * nt);
+}
+// The same without an integer division, with inv2 = 1 / (2 nt): octants are
+// multiples of 1 / (2 nt) >= 2^-26 apart, the product is off by under 2^-47.
+__host__ __device__ inline int octant_by(int col, double inv2, int sector)
+{
+    return (int)floor((double)((2 * col + 1) * sector) * inv2 + 0x1p-27);
+}
+// Shift of direction indices from column `from` to its neighbour `to`.
+__host__ __device__ constexpr int turn_of(int from, int to, int nt, int sector)
+{
+    return (octant_of(from, nt, sector) - octant_of(to, nt, sector)) & 7;
+}
+// Whether neighbouring columns differ by at most one octant (what the
+// marching kernels take; narrower grids are stepped on patches), and whether
+// none do so within a strip.
+__host__ __device__ constexpr bool marchable(int nt, int sector) { return nt >= sector; }
+__host__ __device__ constexpr bool whole_octants(int nt, int sector) { return nt % (STRIP * sector) == 0; }
 
-// Memory plane of velocity q for data whose direction index is shifted by r.
+// Column c (a little off the grid at most) as a column of the grid.
+__host__ __device__ inline int wrap_col(int c, int nt, double inv2) { return c - nt * octant_by(c, inv2, 1); }
+
+// Plane of velocity q of a neighbour whose frame is turned by r.
 __host__ __device__ constexpr int plane_of(int q, int r)
 {
     return q == 0 ? 0 : 1 + 8 * ((q - 1) / 8) + ((((q - 1) % 8) + r) & 7);
 }
+// The member of pair dd that comes from the left and from the right (see
+// above), and the one that comes from below.
+__host__ __device__ constexpr int left_dir(int dd) { return dd == 0 ? 4 : dd; }
+__host__ __device__ constexpr int right_dir(int dd) { return dd == 0 ? 0 : dd + 4; }
+__host__ __device__ constexpr int low_dir(int dd) { return dd == 3 ? 7 : dd; }
 
 // Row strides of one solve, in bytes.
 struct RowBytes {
@@ -41,29 +82,51 @@ __host__ __device__ inline RowBytes row_bytes_of(int64_t rstride, int64_t pitch,
     return b;
 }
 
+// How frames turn at the two edges of a strip: of the columns bordering it
+// on the left [0] and the right [1], the shifts of direction indices from the
+// strip's lane beside it to it (tc) and from it to its own neighbours (tl,
+// tr).  (Read from a table instead of worked out here, the longer chain of
+// loads ahead of a wavefront's gathers cost float32 launches 2 %.)
+struct StripTurns {
+    int tc[2], tl[2], tr[2];
+};
+__host__ __device__ inline StripTurns strip_turns(double inv2, int sector, int strip)
+{
+    StripTurns t;
+    for (int side = 0; side < 2; ++side) {
+        const int k = side == 0 ? strip * STRIP : strip * STRIP + STRIP - 1, c = side == 0 ? k - 1 : k + 1;
+        const int ok = octant_by(k, inv2, sector), oc = octant_by(c, inv2, sector);
+        const int far = octant_by(side == 0 ? c - 1 : c + 1, inv2, sector);
+        t.tc[side] = (ok - oc) & 7;
+        t.tl[side] = (oc - (side == 0 ? far : ok)) & 7;
+        t.tr[side] = (oc - (side == 0 ? ok : far)) & 7;
+    }
+    return t;
+}
+
 // Per-lane offsets of a wavefront strip (see Strip in pdbm_device.h): lane
 // `lane` of strip `strip` owns column c0 + lane, c0 = 64 strip, or its
-// periodic image (the data of physical column pc, directions turned by
-// `rot` in a rotated sector).
+// periodic image (the data of physical column pc).  `mixed`: the strip may
+// hold columns of more than one octant.
 struct StripOffsets {
     uint32_t vo, vo2, vol;     // this lane's physical column: rest plane, pair, lambda
     uint32_t vos, vos2, vols;  // ... of its own column (the padding for periodic images)
-    uint32_t vh1, vh2, vhl;    // halo gathers (plane and column)
-    uint32_t poff[4];          // rotated sectors: pair holding this lane's directions dd, dd + 4
-    bool pswap[4];             // ... and whether its members come in the other order
-    int pc, rot;
+    uint32_t vh1, vh2, vhl;    // halo gathers of every plane (plane and column)
+    uint32_t vhs;              // halo gather of the upwind planes: lanes 0..15 left, 16..31 right, pair lane % 16
+    uint32_t poff[4];          // the lane's pairs of the slowest speed
+    int pc;
+    bool turn_left, turn_right;  // the lane's neighbour in the strip lies in the octant before or after
     bool useful;               // the lane holds a grid column (not an image)
 };
-__host__ __device__ inline StripOffsets strip_offsets(int nt, int64_t pitch, int sector, bool rotated, int esz,
-                                                      const RowBytes &b, int strip, int lane)
+__host__ __device__ inline StripOffsets strip_offsets(const StripTurns &t, double inv2, int nt, int64_t pitch,
+                                                      int sector, bool mixed, int esz, const RowBytes &b, int strip,
+                                                      int lane)
 {
     StripOffsets o;
     const int c0 = strip * STRIP;
     const int col = c0 + lane;
     // lanes past the last column hold periodic images of the first ones
-    const int wraps = col / nt;
-    o.pc = col - wraps * nt;
-    o.rot = rotated ? ((-wraps * sector) & 7) : ROT_NONE;
+    o.pc = wrap_col(col, nt, inv2);
     o.useful = col < nt;
     o.vo = (uint32_t)o.pc * (uint32_t)esz;
     o.vo2 = 2u * o.vo;
@@ -71,17 +134,14 @@ __host__ __device__ inline StripOffsets strip_offsets(int nt, int64_t pitch, int
     o.vos = (uint32_t)col * (uint32_t)esz;
     o.vos2 = 2u * o.vos;
     o.vols = (uint32_t)col * 8u;
-    for (int dd = 0; dd < 4; ++dd) {
-        // direction dd of this lane's data is direction (dd + rot) % 8
-        o.poff[dd] = o.vo2 + b.rest + (uint32_t)((dd + o.rot) & 3) * b.pair;
-        o.pswap[dd] = ((dd + o.rot) & 4) != 0;
-    }
-    // halo columns: c0 - 1 (0 <= c0 < nt) and c0 + 64, as periodic images
-    const int cl = c0 == 0 ? nt - 1 : c0 - 1;
-    const int rl = rotated && c0 == 0 ? (sector & 7) : 0;
-    const int wr = (c0 + STRIP) / nt;
-    const int cr = c0 + STRIP - wr * nt;
-    const int rr = rotated ? ((-wr * sector) & 7) : 0;
+    for (int dd = 0; dd < 4; ++dd) o.poff[dd] = o.vo2 + b.rest + (uint32_t)dd * b.pair;
+    const int oct = octant_by(col, inv2, sector);  // (each worked out by every lane, whatever the others say)
+    const bool tl = octant_by(col - 1, inv2, sector) != oct, tr = octant_by(col + 1, inv2, sector) != oct;
+    o.turn_left = mixed && lane > 0 && tl;
+    o.turn_right = mixed && lane < STRIP - 1 && tr;
+    // halo columns: c0 - 1 and c0 + 64, as periodic images
+    const int cl = wrap_col(c0 - 1, nt, inv2), rl = t.tc[0];
+    const int cr = wrap_col(c0 + STRIP, nt, inv2), rr = t.tc[1];
     // gather 1: lanes 0..32 left halo of planes 0..32, lanes 33..63 right
     // halo of planes 0..30; gather 2: lanes 0, 1 right halo of planes 31,
     // 32; lambda gather: lane 0 left, lane 1 right (other lanes repeat a
@@ -91,24 +151,31 @@ __host__ __device__ inline StripOffsets strip_offsets(int nt, int64_t pitch, int
     o.vh2 = lane < 2 ? (uint32_t)elem_of(plane_of(31 + lane, rr), cr, pitch) * (uint32_t)esz
                      : (uint32_t)cl * (uint32_t)esz;
     o.vhl = lane == 1 ? (uint32_t)cr * 8u : (uint32_t)cl * 8u;
+    // the upwind halves of them
+    const int k = (lane & 15) >> 2, dd = lane & 3;
+    const bool left = (lane & 16) == 0;
+    const int q = plane_of(1 + 8 * k + (left ? left_dir(dd) : right_dir(dd)), left ? rl : rr);
+    o.vhs = (uint32_t)elem_of(q, left ? cl : cr, pitch) * (uint32_t)esz;
     return o;
 }
-
-// floor(c / n) for n > 0: the periodic image a strip column c belongs to.
-__host__ __device__ constexpr int wraps_of(int c, int n) { return c >= 0 ? c / n : -((n - 1 - c) / n); }
+inline StripOffsets strip_offsets(int nt, int64_t pitch, int sector, bool mixed, int esz, const RowBytes &b, int strip,
+                                  int lane)
+{
+    const double inv2 = 0.5 / nt;
+    return strip_offsets(strip_turns(inv2, sector, strip), inv2, nt, pitch, sector, mixed, esz, b, strip, lane);
+}
 
 // Cells of the two-step kernel's strip edges (edge_cells in pdbm_step2.hip):
-// lane 32 side + 2 e + h takes row r of the column bordering strip `strip`
-// on `side` (0: left, 1: right) and gathers the cell (row r, column pc), its
-// radial neighbours (rows rlo, rhi: zero-gradient ghosts at the ends) and
-// its azimuthal neighbours (columns pl, pr).  Those columns, in the strip's
-// own numbering, may be periodic images: in a rotated sector their data has
-// its directions turned (tc, tl, tr, as `rot` in strip_offsets), and the
-// cell's and lane 0 / 63's angles are those of the physical columns pc and
-// pk turned by the sector (tc, tk).
+// one lane group takes row r of the column bordering strip `strip` on `side`
+// (0: left, 1: right) and gathers the cell (row r, column pc), its radial
+// neighbours (rows rlo, rhi: zero-gradient ghosts at the ends) and its
+// azimuthal neighbours (columns pl, pr), which may be periodic images.
+// Direction i of the cell is direction i + tl of its left neighbour, i + tr
+// of its right one; direction i of the strip's column beside it (pk) is
+// direction i + tc of the cell.
 struct EdgeOffsets {
     int pc, pl, pr, pk;            // the cell's column, its left and right neighbours, the column of lane 0 / 63
-    int tc, tl, tr, tk;            // direction shifts of the data of those columns in the strip's frame
+    int tc, tl, tr, tk;            // shifts of direction indices (tk = 0: the strip's own)
     int rlo, rhi;                  // rows of its radial neighbours
     uint32_t orow, olo, ohi;       // row offsets of f: the cell's row and its radial neighbours
     uint32_t cc, cl, cr;           // pair-column offsets of f: pc, pl, pr
@@ -116,29 +183,20 @@ struct EdgeOffsets {
     uint32_t lc, lb, la, lL, lR;   // lambda: the cell, below, above, left, right
     uint32_t om;                   // the cell's entry of the per-cell tau field
 };
-__host__ __device__ inline EdgeOffsets edge_offsets(int nr, int nt, int sector, bool rotated, int esz,
+__host__ __device__ inline EdgeOffsets edge_offsets(const StripTurns &t, double inv2, int nr, int nt, int esz,
                                                     const RowBytes &b, int strip, int side, int r)
 {
     EdgeOffsets o;
     const int c0 = strip * STRIP;
-    if (!rotated) {
-        o.pc = side == 0 ? (c0 + nt - 1) % nt : (c0 + STRIP) % nt;
-        o.pl = (o.pc + nt - 1) % nt;
-        o.pr = (o.pc + 1) % nt;
-        o.pk = (side == 0 ? c0 : c0 + STRIP - 1) % nt;
-        o.tc = o.tl = o.tr = o.tk = ROT_NONE;
-    } else {
-        const int c = side == 0 ? c0 - 1 : c0 + STRIP, k = side == 0 ? c0 : c0 + STRIP - 1;  // strip numbering
-        const int wc = wraps_of(c, nt), wl = wraps_of(c - 1, nt), wr = wraps_of(c + 1, nt), wk = wraps_of(k, nt);
-        o.pc = c - wc * nt;
-        o.pl = (c - 1) - wl * nt;
-        o.pr = (c + 1) - wr * nt;
-        o.pk = k - wk * nt;
-        o.tc = (-wc * sector) & 7;
-        o.tl = (-wl * sector) & 7;
-        o.tr = (-wr * sector) & 7;
-        o.tk = (-wk * sector) & 7;
-    }
+    const int c = side == 0 ? c0 - 1 : c0 + STRIP, k = side == 0 ? c0 : c0 + STRIP - 1;  // strip numbering
+    o.pc = wrap_col(c, nt, inv2);
+    o.pl = wrap_col(c - 1, nt, inv2);
+    o.pr = wrap_col(c + 1, nt, inv2);
+    o.pk = wrap_col(k, nt, inv2);
+    o.tc = side == 0 ? t.tc[0] : t.tc[1];
+    o.tl = side == 0 ? t.tl[0] : t.tl[1];
+    o.tr = side == 0 ? t.tr[0] : t.tr[1];
+    o.tk = 0;
     o.rlo = r - 1 < 0 ? 0 : r - 1;
     o.rhi = r + 1 > nr - 1 ? nr - 1 : r + 1;
     const uint32_t es = (uint32_t)esz;
@@ -156,6 +214,11 @@ __host__ __device__ inline EdgeOffsets edge_offsets(int nr, int nt, int sector, 
     o.lR = (uint32_t)r * b.lrow + (uint32_t)o.pr * 8u;
     o.om = (uint32_t)o.pc * es + (uint32_t)r * b.rest;
     return o;
+}
+inline EdgeOffsets edge_offsets(int nr, int nt, int sector, bool /*mixed*/, int esz, const RowBytes &b, int strip,
+                                int side, int r)
+{
+    return edge_offsets(strip_turns(0.5 / nt, sector, strip), 0.5 / nt, nr, nt, esz, b, strip, side, r);
 }
 // Offset of pair i (0..15) within a row of f (column 0).
 __host__ __device__ inline uint32_t pair_in_row(const RowBytes &b, int i) { return b.rest + (uint32_t)i * b.pair; }
@@ -214,6 +277,82 @@ __host__ __device__ inline ColumnOffsets column_offsets(int nr, const RowBytes &
     o.vol = (uint32_t)o.re * b.lrow;
     o.om = (uint32_t)o.re * b.rest;
     return o;
+}
+
+// The patches of the multi-step kernel for small grids (k_patch in
+// pdbm_patch.hip): workgroup `tile` of a solve owns rows x cols cells of the
+// grid and holds them with a halo of k rows and columns, PATCH_LANES lanes to
+// a cell, cells row by row.  Rows are clipped to the grid; with cols >= nt
+// the patch holds the whole ring and has no column halo.
+// Patches of a grid; threads = 0: it has none and is marched by wavefronts
+// or, a single column, held by them.  Grids of fewer columns than octants
+// have them, whose neighbouring columns may differ by more than the one
+// octant the marching kernels take.
+inline PatchGeom patch_geom(int nr, int nt, int sector)
+{
+    PatchGeom g{};
+    if (nt == 1 || marchable(nt, sector)) return g;
+    g.threads = PACK_PATCH_THREADS;
+    g.k = 2;
+    g.cols = nt;
+    g.rows = g.threads / PATCH_LANES / nt - 2 * g.k;
+    g.nbc = 1;
+    g.ntiles = (nr + g.rows - 1) / g.rows;
+    return g;
+}
+struct PatchCell {
+    int row, pc, ext;    // its row, physical column, column before wrapping
+    int lr, lc, nrow, ncol;  // place within the patch, rows and columns of the patch
+    int dist;            // how far in from the edge of the halo it sits (-1: no cell, the lane is idle)
+    bool own;            // the patch stores it
+    bool ring;           // the patch holds the whole ring
+};
+__host__ __device__ inline PatchCell patch_cell(const PatchGeom &g, int nr, int nt, double inv2, int tile,
+                                                int cell)
+{
+    PatchCell c;
+    const int rb = tile / g.nbc, cb = tile - rb * g.nbc;
+    const int r0 = rb * g.rows, r1 = r0 + g.rows < nr ? r0 + g.rows : nr;
+    const int rlo = r0 - g.k > 0 ? r0 - g.k : 0, rhi = r1 + g.k < nr ? r1 + g.k : nr;
+    c.ring = g.cols >= nt;
+    const int c0 = cb * g.cols, c1 = c0 + g.cols < nt ? c0 + g.cols : nt;
+    const int clo = c.ring ? 0 : c0 - g.k;
+    c.nrow = rhi - rlo;
+    c.ncol = c.ring ? nt : c1 - c0 + 2 * g.k;
+    c.lr = cell / c.ncol;
+    c.lc = cell - c.lr * c.ncol;
+    const bool in = c.lr < c.nrow;
+    if (!in) c.lr = c.lc = 0;
+    c.row = rlo + c.lr;
+    const int ext = c.ext = clo + c.lc;
+    c.pc = wrap_col(ext, nt, inv2);
+    const int far = 1 << 20;
+    const int below = rlo > 0 ? c.lr : far, above = rhi < nr ? c.nrow - 1 - c.lr : far;
+    const int left = c.ring ? far : c.lc, right = c.ring ? far : c.ncol - 1 - c.lc;
+    const int dr = below < above ? below : above, dc = left < right ? left : right;
+    c.dist = !in ? -1 : dr < dc ? dr : dc;
+    c.own = in && c.row >= r0 && c.row < r1 && ext >= c0 && ext < c1;
+    return c;
+}
+// Places (cells of the patch) of a cell's neighbours: itself beyond the
+// radial ends of the grid (the ghosts of Sec. II.D) and at the edge of the
+// halo (never used by a cell still needed), the other end around a whole
+// ring; and the shifts of direction indices to the azimuthal ones.
+struct PatchNear {
+    int low, high, left, right, turn_left, turn_right;
+};
+__host__ __device__ inline PatchNear patch_near(const PatchCell &c, double inv2, int nt, int sector, int cell)
+{
+    PatchNear p;
+    const bool in = c.dist >= 0;
+    p.low = in && c.lr > 0 ? cell - c.ncol : cell;
+    p.high = in && c.lr < c.nrow - 1 ? cell + c.ncol : cell;
+    p.left = in && c.lc > 0 ? cell - 1 : in && c.ring ? cell + nt - 1 : cell;
+    p.right = in && c.lc < c.ncol - 1 ? cell + 1 : in && c.ring ? cell - (nt - 1) : cell;
+    const int o = octant_by(c.ext, inv2, sector);
+    p.turn_left = (o - octant_by(c.ext - 1, inv2, sector)) & 7;
+    p.turn_right = (o - octant_by(c.ext + 1, inv2, sector)) & 7;
+    return p;
 }
 
 }  // namespace pdbm

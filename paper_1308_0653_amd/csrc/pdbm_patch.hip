@@ -1,0 +1,196 @@
+// Several time steps per launch on patches of a small grid (k_patch): grids
+// too small to fill the GPU with wavefronts that march along r, where a step
+// takes as long as one wavefront's serial chain of instructions.
+#include "pdbm_device.h"
+
+namespace pdbm {
+namespace {
+
+// A workgroup holds one patch of the grid with a halo of g.k rows and
+// columns (patch_cell) and takes up to g.k steps of it; after each step the
+// cells one further in from the edge of the halo still hold the true state,
+// and after the last its own cells, which it stores.  Workgroups never wait
+// for one another.
+//
+// Four lanes take a cell, lane h the ring of speed h + 1 (lane 0 also the
+// rest particle): each keeps its ring's eight distributions in registers,
+// the four add up their partial moments (DPP), and each updates its ring, so
+// the chain of a cell's step is about a quarter of what one lane would run.
+// The upwind neighbours come from LDS, where every cell publishes its
+// distributions at the start of a step in one of two buffers (one barrier
+// per step): element (direction d, thread t) at d * threads + t, so that
+// adjacent lanes read adjacent elements.  A lane's sixteen neighbour
+// addresses are the same in every step: they carry the side that is upwind
+// for the direction, the radial ghosts of Sec. II.D (a cell's own value, at a
+// disc centre that of the opposite direction), the turn of the directions
+// between columns of different octants and, on a patch that holds the whole
+// ring, its closing.
+template <typename real, bool TAUF, int NT>
+__global__ __launch_bounds__(NT, 1) void k_patch(const SolveDesc *descs, const uint2 *tiles, const int64_t *bases,
+                                                 int64_t step_off, const int *flips, int flip, int nk_most)
+{
+    constexpr int LPC = PATCH_LANES;
+    static_assert(LPC == 4, "one ring per lane");
+    __shared__ real planes[2][8][NT];
+    __shared__ double lams[2][NT / LPC];
+    __shared__ double parts[2][NT / 64][5];
+    const int t = threadIdx.x, h = t & (LPC - 1);
+    int tile = xcd_tile(blockIdx.x, gridDim.x), solve = 0;
+    if (tiles) {
+        const uint2 e = tiles[tile];
+        solve = __builtin_amdgcn_readfirstlane((int)e.x);
+        tile = __builtin_amdgcn_readfirstlane((int)e.y);
+    }
+    const DescPtr dp = (DescPtr)(descs + solve);
+    const int64_t step0 = (bases ? bases[solve] : 0) + step_off;
+    if (step0 >= dp->nsteps) return;
+    const int nk = (int)min((int64_t)nk_most, dp->nsteps - step0);
+    const PatchGeom g{dp->patch.rows, dp->patch.cols, dp->patch.k, dp->patch.nbc, dp->patch.ntiles, NT};
+    const int nr = dp->nr, nt = dp->nt;
+    const int cur = (int)((step0 + ((flips ? flips[solve] : 0) ^ flip)) & 1);
+    const __amdgpu_buffer_rsrc_t fin = rsrc_of(dp->f[cur]), fout = rsrc_of(dp->f[cur ^ 1]);
+    const __amdgpu_buffer_rsrc_t lin = rsrc_of(dp->lam[cur]), lout = rsrc_of(dp->lam[cur ^ 1]);
+    const RowBytes b = row_bytes_of(dp->rstride, dp->pitch, (int)sizeof(real));
+    const PatchCell c = patch_cell(g, nr, nt, dp->inv2, tile, t / LPC);
+
+    // the state at step0: this lane's ring, the rest particle, lambda
+    const uint32_t vrow = (uint32_t)c.row * b.row;
+    const uint32_t vrest = vrow + (uint32_t)c.pc * (uint32_t)sizeof(real);
+    const uint32_t vlam = (uint32_t)c.row * b.lrow + (uint32_t)c.pc * 8u;
+    const uint32_t vpair = vrow + 2u * (uint32_t)c.pc * (uint32_t)sizeof(real) + pair_in_row(b, 4 * h);
+    real x[8], x0;
+    double lc;
+#pragma unroll
+    for (int dd = 0; dd < 4; ++dd) bload2(x[dd], x[dd + 4], fin, vpair, (uint32_t)dd * b.pair);
+    bload(x0, fin, vrest, 0u);
+    bload(lc, lin, vlam, 0u);
+    const real om = omega_at<real, TAUF>(dp, (uint32_t)c.row * b.rest + (uint32_t)c.pc * (uint32_t)sizeof(real), 0u);
+    const double A0 = dp->A[4 * h], A1 = dp->A[4 * h + 1], A2 = dp->A[4 * h + 2], A3 = dp->A[4 * h + 3];
+    const real v = h == 0 ? (real)speed(1) : h == 1 ? (real)speed(2) : h == 2 ? (real)speed(3) : (real)speed(4);
+
+    const double2 cs = dp->cs[c.pc];
+    const double ri = dp->r_min + ((double)c.row + 0.5) * dp->dr;
+    const double ktd = dp->dt_dth / ri;
+    const real kr = (real)dp->dt_dr, kt = (real)ktd;
+    const Polar<real> V(cs);
+    real acr[4], act[4];
+#pragma unroll
+    for (int dd = 0; dd < 4; ++dd) {
+        acr[dd] = fabs(V.r[dd]) * kr;
+        act[dd] = fabs(V.t[dd]) * kt;
+    }
+    // elements of the upwind neighbours: below for directions 0, 1, 2 and 7
+    // (from this many planes on), above for 3 to 6, left and right by pair
+    const PatchNear near = patch_near(c, dp->inv2, nt, dp->sector, t / LPC);
+    const int turned = c.row == 0 && dp->disc ? 4 * NT : 0;
+    const int low = near.low * LPC + h + turned, low7 = near.low * LPC + h - turned, high = near.high * LPC + h;
+    int left[4], right[4];
+#pragma unroll
+    for (int dd = 0; dd < 4; ++dd) {
+        left[dd] = ((left_dir(dd) + near.turn_left) & 7) * NT + near.left * LPC + h;
+        right[dd] = ((right_dir(dd) + near.turn_right) & 7) * NT + near.right * LPC + h;
+    }
+    const int spare = g.k - nk;  // halo not used up by a launch of fewer steps
+
+    for (int j = 0; j < nk; ++j) {
+        const int64_t step = step0 + j;
+        real *const P = planes[j & 1][0];
+        double *const Lm = lams[j & 1];
+        double(*const part)[5] = parts[j & 1];
+        const bool rec = records(dp, step);
+        // a wavefront all of whose cells are used up takes no further part
+        const bool publish = __builtin_amdgcn_ballot_w64(c.dist >= j + spare) != 0;
+        const bool update = __builtin_amdgcn_ballot_w64(c.dist > j + spare) != 0;
+        Cell<real> C;
+        real Fk = 0, F0 = 0;
+        if (publish) {
+#pragma unroll
+            for (int d = 0; d < 8; ++d) P[d * NT + t] = x[d];
+            Lm[t / LPC] = lc;  // the same from a cell's four lanes
+        }
+        if (update) {
+            // moments: this ring's part, then the other lanes' added
+            real ring, mx, my, en;
+            ring_moments(x, x + 4, v, ring, mx, my, en);
+            C.rho = cell_sum<LPC>(h == 0 ? x0 + ring : ring);
+            C.e = cell_sum<LPC>(en);
+            C.init_state(dp, cell_sum<LPC>(mx), cell_sum<LPC>(my), lc, om);
+            const double T2 = C.Td * C.Td, T3 = T2 * C.Td, T4 = T2 * T2;
+            const double F = fma(A3, T4, fma(A2, T3, fma(A1, T2, A0 * C.Td)));
+            Fk = (real)F;
+            F0 = (real)fma(-8.0, cell_sum<LPC>(F), 1.0);
+        }
+        if (rec) {
+            double red[5] = {0, 0, 0, 0, 0};
+            if (update)
+                diag_cell(red, c.own && h == 0, (double)C.rho, (double)C.ux, (double)C.uy, C.Td, (double)C.e, lc,
+                          (dp->r_min + ((double)c.row + 0.5) * dp->dr) * dp->dr * dp->dth, dp->Q);
+            double s[5];
+#pragma unroll
+            for (int i = 0; i < 5; ++i) s[i] = wave_sum(red[i]);
+            if ((t & 63) == 0)
+#pragma unroll
+                for (int i = 0; i < 5; ++i) part[t >> 6][i] = s[i];
+        }
+        __syncthreads();
+        if (rec && t == 0) {
+            double *out = dp->wpart + (((size_t)((step / dp->diag_every) % PART_RING)) * dp->nwaves + tile) * 5;
+            for (int i = 0; i < 5; ++i) {
+                double s = part[0][i];
+                for (int w = 1; w < NT / 64; ++w) s += part[w][i];
+                out[i] = s;
+            }
+        }
+        if (update) {
+            const real rF = C.rho * Fk;
+            const real rA = rF * C.factor(v), rB = rF * C.Bz;
+            real o[8];
+#pragma unroll
+            for (int dd = 0; dd < 4; ++dd) {
+                real E, O;
+                pair_coll(C.EP, v * C.EP.w(dd), rA, rB, E, O);
+                const real s = C.stay(v, acr[dd] + act[dd]);
+                const real rad0 = P[dd * NT + (dd < 3 ? low : high)];
+                const real rad4 = P[(dd + 4) * NT + (dd < 3 ? high : low7)];
+                const real azi0 = P[dd > 0 ? left[dd] : right[dd]], azi4 = P[dd > 0 ? right[dd] : left[dd]];
+                o[dd] = dir_new(E + O, s, x[dd], v, acr[dd], act[dd], rad0, azi0);
+                o[dd + 4] = dir_new(E - O, s, x[dd + 4], v, acr[dd], act[dd], rad4, azi4);
+            }
+#pragma unroll
+            for (int d = 0; d < 8; ++d) x[d] = o[d];
+            x0 = C.rest(x0, F0);
+            // lambda: closed-form Cochran step, then upwind by own-cell u
+            const double urp = C.ur(cs), utp = C.ut(cs);
+            const double lr = Lm[urp >= 0.0 ? near.low : near.high];
+            const double lt = Lm[utp >= 0.0 ? near.left : near.right];
+            lc = C.lambda(dp, lc, urp, utp, dp->dt_dr, ktd, lr, lt);
+        }
+    }
+
+    if (c.own) {
+#pragma unroll
+        for (int dd = 0; dd < 4; ++dd) bstore2(x[dd], x[dd + 4], fout, vpair, (uint32_t)dd * b.pair);
+        if (h == 0) {
+            bstore(x0, fout, vrest, 0u);
+            bstore(lc, lout, vlam, 0u);
+        }
+    }
+}
+
+}  // namespace
+
+hipError_t launch_patch(const SolveDesc *descs, const uint2 *tiles, int ntiles, int threads, const int64_t *bases,
+                        int64_t step_off, const int *flips, int flip, int nk, bool fp32, bool tauf, hipStream_t st)
+{
+    if (ntiles == 0 || nk <= 0) return hipSuccess;
+    using L = void (*)(const SolveDesc *, const uint2 *, const int64_t *, int64_t, const int *, int, int);
+    // [threads / 512][fp32][tauf]
+    static const L table[2][2][2] = {
+        {{k_patch<double, false, 256>, k_patch<double, true, 256>}, {k_patch<float, false, 256>, k_patch<float, true, 256>}},
+        {{k_patch<double, false, 512>, k_patch<double, true, 512>}, {k_patch<float, false, 512>, k_patch<float, true, 512>}}};
+    hipLaunchKernelGGL(table[threads / 512][fp32][tauf], dim3(ntiles), dim3(threads), 0, st, descs, tiles, bases,
+                       step_off, flips, flip, nk);
+    return hipGetLastError();
+}
+
+}  // namespace pdbm

@@ -33,6 +33,21 @@ using namespace pdbm;
 
 #define HIPCHK PDBM_HIPCHK
 
+// Rows per wavefront of a packed solve of more than one column: FUSE_ROWS,
+// the longest blocks the two-step kernel takes, which recompute the fewest
+// rows; PDBM_BATCH_ROWS overrides it (tuning).  A single column's
+// wavefronts hold COL_W rows whatever this is.
+int pdbm::batch_rows(const pdbm_params &p)
+{
+    if (patch_geom(p.nr, p.ntheta, p.sector).threads > 0) return PATCHES;
+    static const int env = [] {
+        const char *e = std::getenv("PDBM_BATCH_ROWS");
+        return e ? std::atoi(e) : 0;
+    }();
+    if (env > 0) return env;
+    return FUSE_ROWS;
+}
+
 namespace {
 
 // A set of solves of one precision stepped together.
@@ -46,40 +61,39 @@ class Pack {
 
     // Uploads the description, step-base, buffer-parity and tile tables of
     // the current members and drops the captured graph.  The tables hold the
-    // grids of more than one column first (nwide of them, nwt tiles), then
-    // the single columns (Solve::columnar).  The wide ones step in pairs when
-    // every one of them may (Solve::fusable), with the variant for rotated
-    // sectors when one is, else one step per launch; the columns up to COL_K
-    // steps per launch of their own kernel.  Synchronises st.
+    // marched grids first, then the single columns (Solve::columnar), then
+    // the grids stepped on patches (Solve::patched).  The marched ones step in
+    // pairs when every one of them may (Solve::fusable), with the variant for
+    // mixed strips when one has them, else one step per launch; the others up
+    // to COL_K or patch_steps() steps per launch of their own kernels.
+    // Synchronises st.
     int rebuild(hipStream_t st)
     {
         drop_graph();
-        rot = false;
+        mixed = false;
         pairs = true;
         std::vector<SolveDesc> descs;
         std::vector<uint2> tiles;
         bases_host.clear();
         flips_host.clear();
-        nwide = nwt = 0;
-        for (int pass = 0; pass < 2; ++pass) {
+        for (int k = 0; k < KINDS; ++k) {
+            part[k].m0 = (int)descs.size();
+            part[k].t0 = (int)tiles.size();
             for (Solve *m : members) {
-                if (m->columnar() != (pass == 1)) continue;
+                if (kind_of(*m) != k) continue;
                 const unsigned i = (unsigned)descs.size();
                 descs.push_back(m->hd);
                 bases_host.push_back(m->step);
                 flips_host.push_back(m->flip);
-                if (pass == 0) {
-                    rot = rot || m->rot();
+                if (k == WIDE) {
+                    mixed = mixed || m->mixed();
                     pairs = pairs && m->fusable();
                 }
                 for (int t = 0; t < m->waves(); ++t) tiles.push_back(make_uint2(i, (unsigned)t));
             }
-            if (pass == 0) {
-                nwide = (int)descs.size();
-                nwt = (int)tiles.size();
-            }
+            part[k].nm = (int)descs.size() - part[k].m0;
+            part[k].nt = (int)tiles.size() - part[k].t0;
         }
-        ntiles = (int)tiles.size();
         int rc = grow((void **)&ddescs, cap_descs, descs.size() * sizeof(SolveDesc));
         if (rc == PDBM_OK) rc = grow((void **)&dtiles, cap_tiles, tiles.size() * sizeof(uint2));
         if (rc == PDBM_OK) rc = grow((void **)&dbases, cap_bases, bases_host.size() * sizeof(int64_t));
@@ -138,17 +152,30 @@ class Pack {
     }
 
   private:
-    bool rot = false;
+    // The members by the kernel that steps them, and their part of the tables.
+    enum { WIDE, COLUMNS, PATCHED, KINDS };
+    struct Part {
+        int m0 = 0, nm = 0, t0 = 0, nt = 0;  // members, tiles
+    };
+    static int kind_of(const Solve &m) { return m.patched() ? PATCHED : m.columnar() ? COLUMNS : WIDE; }
+    // steps per launch of the columns and of the patches (the same of every patched member)
+    int most_of(int kind) const
+    {
+        if (kind == COLUMNS) return COL_K;
+        for (const Solve *m : members)
+            if (m->patched()) return m->patch_steps();
+        return 1;
+    }
+    Part part[KINDS];
+    bool mixed = false;
     SolveDesc *ddescs = nullptr;
     uint2 *dtiles = nullptr;
     int64_t *dbases = nullptr;  // step of each member at the start of the next chunk
     int *dflips = nullptr;      // buffer parity of each member (Solve::flip) at that step
     bool pairs = false;         // the wide members step two steps per launch
-    int nwide = 0, nwt = 0;     // wide members (the first in the tables) and their tiles
     std::vector<int64_t> bases_host;
     std::vector<int> flips_host;
     size_t cap_descs = 0, cap_tiles = 0, cap_bases = 0, cap_flips = 0;
-    int ntiles = 0;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     int graph_steps = 0;
@@ -184,43 +211,52 @@ class Pack {
     }
 
     // n <= PART_RING steps of every member, their drift records, and the
-    // advance of the step bases (and, in pairs and for the columns, of the
-    // buffer parities).  The wide members: in pairs, two-step launch i takes
-    // steps 2i and 2i + 1 with parity flips ^ (i & 1) (every member still
-    // running has taken the i launches before), and an odd n ends with a
-    // launch of single steps; otherwise one step per launch.  The columns:
-    // launches of nk = min(COL_K, steps of the chunk left) steps; each
-    // toggles the parity of the members still running when nk is even.
+    // advance of the step bases and buffer parities.  The marched members: in
+    // pairs, two-step launch i takes steps 2i and 2i + 1 with parity flips ^
+    // (i & 1) (every member still running has taken the i launches before),
+    // and an odd n ends with a launch of single steps; otherwise one step per
+    // launch.  The columns and the patches: launches of nk = min(most, steps
+    // of the chunk left) steps; each toggles the parity of the members still
+    // running when nk is even.
     hipError_t enqueue_steps(int n, hipStream_t st)
     {
-        const int nm = (int)members.size(), ncol = nm - nwide;
         hipError_t e = hipSuccess;
-        if (nwide > 0) {
+        const Part &w = part[WIDE];
+        if (w.nm > 0) {
             if (pairs) {
                 for (int i = 0; 2 * i + 1 < n && e == hipSuccess; ++i)
-                    e = launch_step2(ddescs, dtiles, nwt, dbases, 2 * i, dflips, i & 1, false, fp32, false, rot, st);
+                    e = launch_step2(ddescs, dtiles, w.nt, dbases, 2 * i, dflips, i & 1, false, fp32, false, mixed, st);
                 if (e == hipSuccess && (n & 1))
-                    e = launch_step2(ddescs, dtiles, nwt, dbases, n - 1, dflips, (n / 2) & 1, true, fp32, false, rot,
+                    e = launch_step2(ddescs, dtiles, w.nt, dbases, n - 1, dflips, (n / 2) & 1, true, fp32, false, mixed,
                                      st);
             } else {
                 for (int i = 0; i < n && e == hipSuccess; ++i)
-                    e = launch_step(ddescs, dtiles, nwt, dbases, i, dflips, 0, fp32, rot, false, st);
+                    e = launch_step(ddescs, dtiles, w.nt, dbases, i, dflips, 0, fp32, mixed, false, st);
             }
         }
-        if (ncol > 0) {
+        for (int k : {COLUMNS, PATCHED}) {
+            const Part &c = part[k];
+            if (c.nm == 0) continue;
+            const int most = most_of(k);
             int pf = 0;
             for (int done = 0; done < n && e == hipSuccess;) {
-                const int nk = std::min(COL_K, n - done);
-                e = launch_column(ddescs, dtiles + nwt, ntiles - nwt, dbases, done, dflips, pf, nk, fp32, false, st);
+                const int nk = std::min(most, n - done);
+                if (k == COLUMNS)
+                    e = launch_column(ddescs, dtiles + c.t0, c.nt, dbases, done, dflips, pf, nk, fp32, false, st);
+                else
+                    e = launch_patch(ddescs, dtiles + c.t0, c.nt, PACK_PATCH_THREADS, dbases, done, dflips, pf, nk,
+                                     fp32, false, st);
                 pf ^= (nk + 1) & 1;
                 done += nk;
             }
         }
-        if (e == hipSuccess) e = launch_records(ddescs, nm, dbases, 0, n, st);
-        if (e == hipSuccess && nwide > 0)
-            e = launch_advance(ddescs, pairs ? dflips : nullptr, dbases, nwide, n, 0, st);
-        if (e == hipSuccess && ncol > 0)
-            e = launch_advance(ddescs + nwide, dflips + nwide, dbases + nwide, ncol, n, COL_K, st);
+        if (e == hipSuccess) e = launch_records(ddescs, (int)members.size(), dbases, 0, n, st);
+        for (int k = 0; k < KINDS && e == hipSuccess; ++k) {
+            const Part &c = part[k];
+            if (c.nm > 0)
+                e = launch_advance(ddescs + c.m0, k == WIDE && !pairs ? nullptr : dflips + c.m0, dbases + c.m0, c.nm, n,
+                                   k == WIDE ? 0 : most_of(k), st);
+        }
         return e;
     }
 
@@ -229,8 +265,9 @@ class Pack {
     {
         for (Solve *m : members) {
             const int64_t left = std::max<int64_t>(m->hd.nsteps - m->step, 0);
-            if (m->columnar())
-                m->flip ^= column_chunk_toggle(left, n, COL_K);
+            const int k = kind_of(*m);
+            if (k != WIDE)
+                m->flip ^= column_chunk_toggle(left, n, most_of(k));
             else if (pairs)
                 m->flip ^= pair_chunk_toggle(left, n);
             m->step = std::min(m->step + n, m->hd.nsteps);
@@ -246,20 +283,6 @@ class Pack {
         graph_steps = 0;
     }
 };
-
-// Rows per wavefront of a packed solve of more than one column: FUSE_ROWS,
-// the longest blocks the two-step kernel takes, which recompute the fewest
-// rows; PDBM_BATCH_ROWS overrides it (tuning).  A single column's
-// wavefronts hold COL_W rows whatever this is.
-int batch_rows(const pdbm_params &p)
-{
-    static const int env = [] {
-        const char *e = std::getenv("PDBM_BATCH_ROWS");
-        return e ? std::atoi(e) : 0;
-    }();
-    if (env > 0) return env;
-    return FUSE_ROWS;
-}
 
 // Fields [6][nr][ntheta] (host, may be NULL) and drift report of a member.
 int fetch_result(const Solve &s, double *out, pdbm_diag *diag, hipStream_t st)

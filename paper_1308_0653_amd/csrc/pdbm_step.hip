@@ -1,5 +1,5 @@
 // One time step per launch (k_step): every solve of the launch, float64 or
-// float32, full annulus or rotated sector, wavefront strips of 64 theta
+// float32, any sector, wavefront strips of 64 theta
 // columns or, for a single column, wavefronts of 64 rows; and the kernels
 // that add up the drift records (k_records) and move packed solves' step
 // bases on (k_advance).
@@ -53,43 +53,36 @@ __device__ __forceinline__ void radial_block(DescPtr dp, const StepBufs &bufs, i
 
     // (1)-(3) moments, weights, f^eq polynomial, BGK and chemical factors
     const Cell<real> C(dp, fc, lc, omega_at<real, TAUF>(dp, o.om, 0u));
-    const real rho = C.rho, e = C.e, ux = C.ux, uy = C.uy, u2 = C.u2, T = C.T;
-    const real beta = C.beta, omega = C.omega, keep = C.keep, Bz = C.Bz;
-    const double Td = C.Td;
-    const real *F = C.F;
-    const EqPoly<real> &EP = C.EP;
 
     // polar components of directions dd = 0..3 at theta_0 (dd+4 is the negative)
     const double2 cs = dp->cs[0];
-    const real cth = (real)cs.x, sth = (real)cs.y;
-    const real crv[4] = {cth, (real)SQH * (cth + sth), sth, (real)SQH * (sth - cth)};
-    const real ctv[4] = {-sth, (real)SQH * (cth - sth), cth, (real)SQH * (cth + sth)};
+    const Polar<real> V(cs);
     const double ri = dp->r_min + ((double)re + 0.5) * dp->dr;
-    const real kr = (real)dp->dt_dr, kt = (real)(dp->dt_dth / ri);
+    const double ktd = dp->dt_dth / ri;
+    const real kr = (real)dp->dt_dr, kt = (real)ktd;
     real acr[4], act[4];
 #pragma unroll
     for (int dd = 0; dd < 4; ++dd) {
-        acr[dd] = fabs(crv[dd]) * kr;
-        act[dd] = fabs(ctv[dd]) * kt;
+        acr[dd] = fabs(V.r[dd]) * kr;
+        act[dd] = fabs(V.t[dd]) * kt;
     }
     // the cell's distributions, for its rotated azimuthal neighbours
 #pragma unroll
     for (int q = 0; q < NQ; ++q) slot[q][lane] = fc[q];
 
-    const real rest = rho * F[0] * EP.c0 * (keep + beta * (u2 - (real)2 * T)) + omega * fc[0];
-    if (store) bstore(rest, fout, vo, 0u);
+    if (store) bstore(C.rest(fc[0], C.F[0]), fout, vo, 0u);
 #pragma unroll
     for (int k = 1; k <= 4; ++k) {
         const real v = (real)speed(k);
-        const real rF = rho * F[k];
-        const real rA = rF * (keep + beta * (v * v + u2 - (real)2 * T)), rB = rF * Bz;
+        const real rF = C.rho * C.F[k];
+        const real rA = rF * C.factor(v), rB = rF * C.Bz;
         const int base = 1 + 8 * (k - 1);
         real o[8];
 #pragma unroll
         for (int dd = 0; dd < 4; ++dd) {
             real E, O;
-            pair_coll(EP, v * EP.w(dd), rA, rB, E, O);
-            const real s = omega - v * (acr[dd] + act[dd]);
+            pair_coll(C.EP, v * C.EP.w(dd), rA, rB, E, O);
+            const real s = C.stay(v, acr[dd] + act[dd]);
 #pragma unroll
             for (int sgn = 0; sgn < 2; ++sgn) {
                 const int q = base + dd + 4 * sgn;
@@ -100,11 +93,11 @@ __device__ __forceinline__ void radial_block(DescPtr dp, const StepBufs &bufs, i
                 const real hl = halo_left(hf, q), hr = halo_right(hf, q);
                 const real lower = lane == 0 ? hl : sl;
                 const real upper = lane == 63 ? hr : sr;
-                const bool below = sgn == 0 ? crv[dd] >= (real)0 : crv[dd] < (real)0;
+                const bool below = sgn == 0 ? V.r[dd] >= (real)0 : V.r[dd] < (real)0;
                 const real nbr = below ? lower : upper;
                 // azimuthal upwind (C_theta >= 0 takes j-1): this cell with
                 // the direction index turned by +s (j-1) or -s (j+1)
-                const bool left = sgn == 0 ? ctv[dd] >= (real)0 : ctv[dd] < (real)0;
+                const bool left = sgn == 0 ? V.t[dd] >= (real)0 : V.t[dd] < (real)0;
                 const int dir = dd + 4 * sgn;
                 const real nbt = slot[base + ((dir + (left ? sec : 8 - sec)) & 7)][lane];
                 o[dd + 4 * sgn] = dir_new(sgn == 0 ? E + O : E - O, s, x, v, acr[dd], act[dd], nbr, nbt);
@@ -118,18 +111,18 @@ __device__ __forceinline__ void radial_block(DescPtr dp, const StepBufs &bufs, i
 
     // (4) lambda: closed-form Cochran step, then upwind by own-cell u (the
     // azimuthal neighbour of the single column is the cell itself)
-    const double uxd = (double)ux, uyd = (double)uy;
-    const double urp = uxd * cs.x + uyd * cs.y;
-    const double lreac = C.reacted(dp, lc);
+    const double urp = C.ur(cs), utp = C.ut(cs);
     const double sll = from_left(lc), slr = from_right(lc);
     const double hll = lane_value(hlam, 0), hlr = lane_value(hlam, 1);
     const double llow = lane == 0 ? hll : sll;
     const double lup = lane == 63 ? hlr : slr;
     const double lr = urp >= 0.0 ? llow : lup;
-    const double lnew = lreac - fabs(urp) * dp->dt_dr * (lc - lr);
+    const double lnew = C.lambda(dp, lc, urp, utp, dp->dt_dr, ktd, lr, lc);
     if (store) bstore(lnew, lout, vol, 0u);
 
-    if (diag && store) diag_cell(red, (double)rho, uxd, uyd, Td, (double)e, lc, ri * dp->dr * dp->dth, dp->Q);
+    if (diag)
+        diag_cell(red, store, (double)C.rho, (double)C.ux, (double)C.uy, C.Td, (double)C.e, lc, ri * dp->dr * dp->dth,
+                  dp->Q);
 }
 
 // Up to COL_K steps of a single-column solve in one launch (the
@@ -202,16 +195,15 @@ __global__ __launch_bounds__(BLOCK, 1) void k_column(const SolveDesc *descs, con
 
     // polar components of directions dd = 0..3 at theta_0 (dd+4 is the negative)
     const double2 cs = dp->cs[0];
-    const real cth = (real)cs.x, sth = (real)cs.y;
-    const real crv[4] = {cth, (real)SQH * (cth + sth), sth, (real)SQH * (sth - cth)};
-    const real ctv[4] = {-sth, (real)SQH * (cth - sth), cth, (real)SQH * (cth + sth)};
+    const Polar<real> V(cs);
     const double ri = dp->r_min + ((double)o.re + 0.5) * dp->dr;
-    const real kr = (real)dp->dt_dr, kt = (real)(dp->dt_dth / ri);
+    const double ktd = dp->dt_dth / ri;
+    const real kr = (real)dp->dt_dr, kt = (real)ktd;
     real acr[4], act[4];
 #pragma unroll
     for (int dd = 0; dd < 4; ++dd) {
-        acr[dd] = fabs(crv[dd]) * kr;
-        act[dd] = fabs(ctv[dd]) * kt;
+        acr[dd] = fabs(V.r[dd]) * kr;
+        act[dd] = fabs(V.t[dd]) * kt;
     }
     const double w_area = ri * dp->dr * dp->dth;
 
@@ -242,8 +234,7 @@ __global__ __launch_bounds__(BLOCK, 1) void k_column(const SolveDesc *descs, con
         const Cell<real> C(dp, fc, lc, om);
         if (records(dp, step)) {
             double red[5] = {0, 0, 0, 0, 0};
-            if (o.own)
-                diag_cell(red, (double)C.rho, (double)C.ux, (double)C.uy, C.Td, (double)C.e, lc, w_area, dp->Q);
+            diag_cell(red, o.own, (double)C.rho, (double)C.ux, (double)C.uy, C.Td, (double)C.e, lc, w_area, dp->Q);
             double v[5];
 #pragma unroll
             for (int i = 0; i < 5; ++i) v[i] = wave_sum(red[i]);
@@ -257,28 +248,28 @@ __global__ __launch_bounds__(BLOCK, 1) void k_column(const SolveDesc *descs, con
 #pragma unroll
         for (int q = 0; q < NQ; ++q) slot[q][lane] = fc[q];
         real fn[NQ];
-        fn[0] = C.rest(fc[0]);
+        fn[0] = C.rest(fc[0], C.F[0]);
 #pragma unroll
         for (int k = 1; k <= 4; ++k) {
             const real v = (real)speed(k);
             const real rF = C.rho * C.F[k];
-            const real rA = rF * (C.keep + C.beta * (v * v + C.u2 - (real)2 * C.T)), rB = rF * C.Bz;
+            const real rA = rF * C.factor(v), rB = rF * C.Bz;
             const int base = 1 + 8 * (k - 1);
 #pragma unroll
             for (int dd = 0; dd < 4; ++dd) {
                 real E, O;
                 pair_coll(C.EP, v * C.EP.w(dd), rA, rB, E, O);
-                const real s = C.omega - v * (acr[dd] + act[dd]);
+                const real s = C.stay(v, acr[dd] + act[dd]);
 #pragma unroll
                 for (int sgn = 0; sgn < 2; ++sgn) {
                     const int q = base + dd + 4 * sgn;
                     const real x = fc[q];
                     // radial upwind (C_r >= 0 takes the row below, lane - 1)
                     const real lower = from_left(x), upper = from_right(x);
-                    const bool lo = sgn == 0 ? crv[dd] >= (real)0 : crv[dd] < (real)0;
+                    const bool lo = sgn == 0 ? V.r[dd] >= (real)0 : V.r[dd] < (real)0;
                     const real nbr = lo ? lower : upper;
                     // azimuthal upwind: this cell, direction turned by +s or -s
-                    const bool left = sgn == 0 ? ctv[dd] >= (real)0 : ctv[dd] < (real)0;
+                    const bool left = sgn == 0 ? V.t[dd] >= (real)0 : V.t[dd] < (real)0;
                     const int dir = dd + 4 * sgn;
                     const real nbt = slot[base + ((dir + (left ? sec : 8 - sec)) & 7)][lane];
                     fn[q] = dir_new(sgn == 0 ? E + O : E - O, s, x, v, acr[dd], act[dd], nbr, nbt);
@@ -286,12 +277,10 @@ __global__ __launch_bounds__(BLOCK, 1) void k_column(const SolveDesc *descs, con
             }
         }
         // lambda: closed-form Cochran step, then upwind by own-cell u_r
-        const double uxd = (double)C.ux, uyd = (double)C.uy;
-        const double urp = uxd * cs.x + uyd * cs.y;
-        const double lreac = C.reacted(dp, lc);
+        const double urp = C.ur(cs), utp = C.ut(cs);
         const double llow = from_left(lc), lup = from_right(lc);
         const double lr = urp >= 0.0 ? llow : lup;
-        lc = lreac - fabs(urp) * dp->dt_dr * (lc - lr);
+        lc = C.lambda(dp, lc, urp, utp, dp->dt_dr, ktd, lr, lc);
 #pragma unroll
         for (int q = 0; q < NQ; ++q) fc[q] = fn[q];
     }
@@ -320,7 +309,7 @@ struct StepOcc {
 // strip lt % nstrip.  Each wavefront works on its own: no barriers and no
 // atomics.  A drift-report step leaves per-wavefront partial sums in its
 // slot of the solve's partial-sum ring; k_records adds them up later.
-template <typename real, bool ROT, bool TAUF>
+template <typename real, bool MIXED, bool TAUF>
 __global__ __launch_bounds__(BLOCK, StepOcc<real>::waves) void k_step(const SolveDesc *descs, const uint2 *tiles,
                                                                        int ntiles, const int64_t *bases,
                                                                        int64_t step_off, const int *flips,
@@ -357,7 +346,7 @@ __global__ __launch_bounds__(BLOCK, StepOcc<real>::waves) void k_step(const Solv
         const int rb = lt / nstrip, strip = lt - rb * nstrip;
         const int i0 = rb * rows;
         const int i1 = min(i0 + rows, dp->nr);
-        march<real, ROT, TAUF>(dp, bufs, strip, i0, i1, (rb & 1) != 0, prev[threadIdx.x >> 6], red, diag);
+        march<real, MIXED, TAUF>(dp, bufs, strip, i0, i1, (rb & 1) != 0, prev[threadIdx.x >> 6], red, diag);
     }
     if (diag) {
         const int64_t slot = (step / dp->diag_every) % PART_RING;
@@ -437,28 +426,28 @@ int solve_waves(int nr, int nt, int rows)
     return (int)((int64_t)((nr + rows - 1) / rows) * ((nt + STRIP - 1) / STRIP));
 }
 
-template <typename real, bool ROT, bool TAUF>
+template <typename real, bool MIXED, bool TAUF>
 static void launch_k_step(int nb, hipStream_t st, const SolveDesc *descs, const uint2 *tiles, int ntiles,
                           const int64_t *bases, int64_t step_off, const int *flips, int flip)
 {
-    hipLaunchKernelGGL((k_step<real, ROT, TAUF>), dim3(nb), dim3(BLOCK), 0, st, descs, tiles, ntiles, bases, step_off,
+    hipLaunchKernelGGL((k_step<real, MIXED, TAUF>), dim3(nb), dim3(BLOCK), 0, st, descs, tiles, ntiles, bases, step_off,
                        flips, flip);
 }
 
 hipError_t launch_step(const SolveDesc *descs, const uint2 *tiles, int ntiles, const int64_t *bases, int64_t step_off,
-                       const int *flips, int flip, bool fp32, bool rot, bool tauf, hipStream_t st)
+                       const int *flips, int flip, bool fp32, bool mixed, bool tauf, hipStream_t st)
 {
     const int nb = (ntiles + BLOCK / 64 - 1) / (BLOCK / 64);
     if (nb == 0) return hipSuccess;
     using L = void (*)(int, hipStream_t, const SolveDesc *, const uint2 *, int, const int64_t *, int64_t, const int *,
                        int);
-    // [fp32][rot][tauf]
+    // [fp32][mixed][tauf]
     static const L table[2][2][2] = {
         {{launch_k_step<double, false, false>, launch_k_step<double, false, true>},
          {launch_k_step<double, true, false>, launch_k_step<double, true, true>}},
         {{launch_k_step<float, false, false>, launch_k_step<float, false, true>},
          {launch_k_step<float, true, false>, launch_k_step<float, true, true>}}};
-    table[fp32][rot][tauf](nb, st, descs, tiles, ntiles, bases, step_off, flips, flip);
+    table[fp32][mixed][tauf](nb, st, descs, tiles, ntiles, bases, step_off, flips, flip);
     return hipGetLastError();
 }
 

@@ -1,6 +1,6 @@
-// Two time steps per launch, in one pass over f (k_step2): solves with more
-// than one theta column, full annuli and rotated sectors (annuli and discs),
-// single or packed, in float64 (one wavefront per SIMD) and float32 (two).
+// Two time steps per launch, in one pass over f (k_step2): solves of at least
+// a column per octant, any sector (annuli and discs), single or packed, in
+// float64 (one wavefront per SIMD) and float32 (two).
 #include "pdbm_device.h"
 
 namespace pdbm {
@@ -17,39 +17,22 @@ namespace {
 // value is read about 1.3 times (block boundaries, edge-cell gathers) and
 // written once per two steps.
 
-// Azimuthal neighbours of lanes 0 and 63 for stage A: the three gathered
-// loads of a row of the input state, written to an LDS row and read back by
-// every lane (hb[q] left halo of plane q, hb[33 + q] right halo; hl[0], hl[1]
-// lambda).
+// Azimuthal neighbours of lanes 0 and 63 in LDS, read back by every lane: of
+// each opposite pair of directions the member that comes from the left
+// (lane 0: l[pair], left_dir) and the one that comes from the right (lane 63:
+// r[pair], right_dir), and lambda.  For stage A the gathered halo of its row
+// (slots 0..15 and 16..31 of the wavefront's halo row), for stage B the edge
+// cells of the intermediate state.
 template <typename real>
-struct LdsHalo {
-    const real *hb;
-    const double *hl;
-    __device__ __forceinline__ real left(int q) const { return hb[q]; }
-    __device__ __forceinline__ real right(int q) const { return hb[33 + q]; }
-    __device__ __forceinline__ double lleft() const { return hl[0]; }
-    __device__ __forceinline__ double lright() const { return hl[1]; }
+struct Halo {
+    const real *l, *r;
+    double ll, lr;
 };
-// The gathered halo registers of one row (see Strip::load_halo).
+// The gathered halo registers of one row (see Strip::load_upwind_halo).
 template <typename real>
 struct GatherHalo {
-    real h[2];
+    real h;
     double hl;
-};
-
-// ... and from the edge cells of the intermediate state in LDS (stage B).  Of
-// each pair of opposite directions an edge cell keeps only the one lane 0
-// (left side) or lane 63 (right side) takes from that side, in slot
-// 4 (k - 1) + (direction mod 4).
-template <typename real>
-struct EdgeHalo {
-    const real *L, *R;
-    double ll, lr;
-    static __device__ __forceinline__ int slot(int q) { return ((q - 1) >> 3) * 4 + ((q - 1) & 3); }
-    __device__ __forceinline__ real left(int q) const { return L[slot(q)]; }
-    __device__ __forceinline__ real right(int q) const { return R[slot(q)]; }
-    __device__ __forceinline__ double lleft() const { return ll; }
-    __device__ __forceinline__ double lright() const { return lr; }
 };
 
 // Drift sums of one step (mass, energy, chemical energy, non-finite and
@@ -62,28 +45,32 @@ struct LaneDiag {
     __device__ __forceinline__ void add(bool valid, double rho, double ux, double uy, double T, double e, double lam,
                                         double w, double Q)
     {
-        if (valid) diag_cell(red, rho, ux, uy, T, e, lam, w, Q);
+        diag_cell(red, valid, rho, ux, uy, T, e, lam, w, Q);
     }
     __device__ __forceinline__ double total(int i) const { return wave_sum(red[i]); }
 };
 
-// One row of one of the two steps: the arithmetic of update_row, with the
-// azimuthal halo from H.  Radial neighbours: the row behind in compact LDS
-// slots (of each opposite pair of directions only the one that takes its
-// upwind value from behind, slot 4 (k - 1) + (direction mod 4); replaced by
-// this row's as they are read), the row ahead in `fn` (stage A) or in the
-// full LDS row `ga` (stage B).  STAGEA: the new row goes to `ga` and `lout`,
-// for every lane (stage B reads the periodic images too), and the row it
-// replaces in `ga` to `gold`, plane by plane, so that the registers of the
-// old row fill as those of fc empty; otherwise it is stored, for the strip's
-// own columns.
-template <typename real, bool STAGEA, bool TAUF, bool ROT, class Halo, class Diag>
-__device__ __forceinline__ void stage_row(const Strip<real, ROT> &S, int ir, real (*behind)[64], const real fc[NQ],
-                                          const real *fn, real (*ga)[64], real *gold, const Halo &H, double lbehind,
-                                          double lc,
-                                          double lahead, const bool mr[4], const bool mt[4], const real acr[4],
-                                          const real ctv[4], bool lr_behind, double csx, double csy, double &lout,
-                                          real om, Diag &D, bool diag)
+// One row of one of the two steps, marching outward: the arithmetic of
+// update_row with every upwind side known at compile time (the frames of
+// pdbm_offsets.h): below for directions 0, 1, 2, 7, above for 3 to 6, left
+// for 1 to 4, right for 5, 6, 7, 0.  That is one lane shift per direction and
+// no selects, half the LDS reads of the row ahead and of the halo, and no
+// lane masks to hold (with both sides fetched and selected per lane, 1024 x
+// 1024 launches took 155 us in float64 and 94 us in float32; now 140 and
+// 91).  MIXED strips, where a lane's neighbour may lie in the octant
+// beside, shift one value more per side and ring and select between the two.
+// Radial neighbours: the row behind (below) in compact LDS slots (low_dir of
+// each pair, slot 4 (k - 1) + (direction mod 4); replaced by this row's as
+// they are read), the row ahead in `fn` (stage A) or in the full LDS row `ga`
+// (stage B).  STAGEA: the new row goes to `ga` and `lout`, for every lane
+// (stage B reads the periodic images too), and the row it replaces in `ga` to
+// `gold`, plane by plane, so that the registers of the old row fill as those
+// of fc empty; otherwise it is stored, for the strip's own columns.
+template <typename real, bool STAGEA, bool TAUF, bool MIXED, class Diag>
+__device__ __forceinline__ void stage_row(const Strip<real, MIXED> &S, int ir, real (*behind)[64], const real fc[NQ],
+                                          const real *fn, real (*ga)[64], real *gold, const Halo<real> &H,
+                                          double lbehind, double lc, double lahead, const real acr[4],
+                                          const real ctv[4], double2 cs, double &lout, real om, Diag &D, bool diag)
 {
     const DescPtr dp = S.dp;
     // the cell's exp(-dt/tau): with TAUF `om`, loaded by march2 a pass ahead
@@ -94,7 +81,8 @@ __device__ __forceinline__ void stage_row(const Strip<real, ROT> &S, int ir, rea
         omega = omega_at<real, TAUF>(dp, S.vo, (uint32_t)ir * S.rest_bytes);
     const Cell<real> C(dp, fc, lc, omega);
     const double ri = dp->r_min + ((double)ir + 0.5) * dp->dr;
-    const real kt = (real)(dp->dt_dth / ri);
+    const double ktd = dp->dt_dth / ri;
+    const real kt = (real)ktd;
     real act[4], aa[4];
 #pragma unroll
     for (int dd = 0; dd < 4; ++dd) {
@@ -112,7 +100,7 @@ __device__ __forceinline__ void stage_row(const Strip<real, ROT> &S, int ir, rea
     // column of the row padding (nothing reads it): no store sits under a
     // lane mask, which keeps the exec-mask branches and their registers out
     // of the row loop
-    const real rest = C.rest(fc[0]);
+    const real rest = C.rest(fc[0], C.F[0]);
     if (STAGEA) {
         gold[0] = ga[0][lane];
         ga[0][lane] = rest;
@@ -123,36 +111,52 @@ __device__ __forceinline__ void stage_row(const Strip<real, ROT> &S, int ir, rea
     for (int k = 1; k <= 4; ++k) {
         const real v = (real)speed(k);
         const real rF = C.rho * C.F[k];
-        const real rA = rF * (C.keep + C.beta * (v * v + C.u2 - (real)2 * C.T)), rB = rF * C.Bz;
+        const real rA = rF * C.factor(v), rB = rF * C.Bz;
         const int base = 1 + 8 * (k - 1);
+        const real *x = fc + base;
+        // azimuthal neighbours of the ring, every lane taking part in the
+        // shifts (lanes 0 and 63 take the halo)
+        real nt[8];
+#pragma unroll
+        for (int dd = 0; dd < 4; ++dd) {
+            const int c = 4 * (k - 1) + dd;
+            nt[left_dir(dd)] = from_left_or(H.l[c], x[left_dir(dd)]);
+            nt[right_dir(dd)] = from_right_or(H.r[c], x[right_dir(dd)]);
+        }
+        if constexpr (MIXED) {
+            // from the octant beside: the next direction (left), the one before (right)
+            const real s5 = from_left(x[5]), s4 = from_right(x[4]);
+            const real l1 = S.turn_left ? nt[2] : nt[1], l2 = S.turn_left ? nt[3] : nt[2];
+            const real l3 = S.turn_left ? nt[4] : nt[3], l4 = S.turn_left ? s5 : nt[4];
+            const real r5 = S.turn_right ? s4 : nt[5], r6 = S.turn_right ? nt[5] : nt[6];
+            const real r7 = S.turn_right ? nt[6] : nt[7], r0 = S.turn_right ? nt[7] : nt[0];
+            nt[0] = r0;
+            nt[1] = l1;
+            nt[2] = l2;
+            nt[3] = l3;
+            nt[4] = l4;
+            nt[5] = r5;
+            nt[6] = r6;
+            nt[7] = r7;
+        }
         real o[8];
 #pragma unroll
         for (int dd = 0; dd < 4; ++dd) {
             real E, O;
             pair_coll(C.EP, v * C.EP.w(dd), rA, rB, E, O);
-            const real s = C.omega - v * aa[dd];
+            const real s = C.stay(v, aa[dd]);
             const int c = 4 * (k - 1) + dd;
+            constexpr int LOW3 = low_dir(3);
+            const int lo = dd < 3 ? dd : LOW3, hi = dd < 3 ? dd + 4 : dd;  // from below, from above
             const real back = behind[c][lane];
-            behind[c][lane] = mr[dd] ? fc[base + dd] : fc[base + dd + 4];
-#pragma unroll
-            for (int sgn = 0; sgn < 2; ++sgn) {
-                const int q = base + dd + 4 * sgn;
-                const real x = fc[q];
-                const bool rb = sgn == 0 ? mr[dd] : !mr[dd];
-                real ahead;
-                if constexpr (STAGEA)
-                    ahead = fn[q];
-                else
-                    ahead = ga[q][lane];
-                const real nbr = rb ? back : ahead;
-                // every lane takes both shifts (lanes 0 and 63 the halo
-                // values), then selects
-                const real left = from_left_or(H.left(q), x);
-                const real right = from_right_or(H.right(q), x);
-                const bool tl = sgn == 0 ? mt[dd] : !mt[dd];
-                const real nbt = tl ? left : right;
-                o[dd + 4 * sgn] = dir_new(sgn == 0 ? E + O : E - O, s, x, v, acr[dd], act[dd], nbr, nbt);
-            }
+            behind[c][lane] = x[lo];
+            real ahead;
+            if constexpr (STAGEA)
+                ahead = fn[base + hi];
+            else
+                ahead = ga[base + hi][lane];
+            o[lo] = dir_new(lo == dd ? E + O : E - O, s, x[lo], v, acr[dd], act[dd], back, nt[lo]);
+            o[hi] = dir_new(hi == dd ? E + O : E - O, s, x[hi], v, acr[dd], act[dd], ahead, nt[hi]);
         }
         if (STAGEA) {
 #pragma unroll
@@ -167,45 +171,19 @@ __device__ __forceinline__ void stage_row(const Strip<real, ROT> &S, int ir, rea
         }
     }
 
-    const double uxd = (double)C.ux, uyd = (double)C.uy;
-    const double urp = uxd * csx + uyd * csy;
-    const double utp = -uxd * csy + uyd * csx;
-    const double lreac = C.reacted(dp, lc);
-    const double lleft = from_left_or(H.lleft(), lc);
-    const double lright = from_right_or(H.lright(), lc);
-    const double lr = (urp >= 0.0) == lr_behind ? lbehind : lahead;
+    const double urp = C.ur(cs), utp = C.ut(cs);
+    const double lleft = from_left_or(H.ll, lc);
+    const double lright = from_right_or(H.lr, lc);
+    const double lr = urp >= 0.0 ? lbehind : lahead;
     const double lt = utp >= 0.0 ? lleft : lright;
-    const double lnew = lreac - fabs(urp) * dp->dt_dr * (lc - lr) - fabs(utp) * (dp->dt_dth / ri) * (lc - lt);
+    const double lnew = C.lambda(dp, lc, urp, utp, dp->dt_dr, ktd, lr, lt);
     if (STAGEA)
         lout = lnew;
     else
         bstore(lnew, S.lout, S.vols, (uint32_t)ir * S.lrow_bytes);
 
-    if (diag) D.add(store, (double)C.rho, uxd, uyd, C.Td, (double)C.e, lc, ri * dp->dr * dp->dth, dp->Q);
-}
-
-// The value lane l ^ x holds, x = 1 or 2 (a permutation within each group of
-// four lanes).
-template <int X>
-__device__ __forceinline__ float lane_xor(float v)
-{
-    constexpr int ctl = X == 1 ? 0xB1 : 0x4E;  // quad_perm [1,0,3,2] or [2,3,0,1]
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), ctl, 0xf, 0xf, false));
-}
-template <int X>
-__device__ __forceinline__ double lane_xor(double v)
-{
-    constexpr int ctl = X == 1 ? 0xB1 : 0x4E;
-    return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), ctl, 0xf, 0xf, false),
-                            __builtin_amdgcn_mov_dpp(__double2loint(v), ctl, 0xf, 0xf, false));
-}
-// The sum of v over the LPC lanes of a cell (2 or 4 adjacent lanes).
-template <int LPC, typename T>
-__device__ __forceinline__ T cell_sum(T v)
-{
-    v += lane_xor<1>(v);
-    if constexpr (LPC == 4) v += lane_xor<2>(v);
-    return v;
+    if (diag)
+        D.add(store, (double)C.rho, (double)C.ux, (double)C.uy, C.Td, (double)C.e, lc, ri * dp->dr * dp->dth, dp->Q);
 }
 
 // The intermediate state at the columns bordering strip `strip`, c0 - 1
@@ -216,13 +194,12 @@ __device__ __forceinline__ T cell_sum(T v)
 // opposite pair of directions only the one that lane 0 (left side) or lane
 // 63 (right side) takes from there is kept.  Each lane gathers its pairs of
 // the cell (one access per pair) and, for the kept direction of each, its
-// two upwind neighbours (radial ghost rules of Sec. II.D included); the
-// lanes of a cell add up their partial moments, and each updates its kept
-// directions as stage A of the strip owning the column does.  The first
-// lane of a cell keeps lambda.  Every lane runs every instruction up to the
-// final stores (the moment exchange is a lane permutation).
-template <typename real, bool TAUF, int LPC, bool ROT>
-__device__ __forceinline__ void edge_cells(const Strip<real, ROT> &S, int strip, int i0, int i1,
+// two upwind neighbours (radial ghost rules of Sec. II.D included), which
+// side they are on following from the direction alone; the lanes of a cell
+// add up their partial moments, and each updates its kept directions as stage
+// A of the strip owning the column does, to the same bits.
+template <typename real, bool TAUF, int LPC, bool MIXED>
+__device__ __forceinline__ void edge_cells(const Strip<real, MIXED> &S, int strip, int i0, int i1,
                                            real (*ef)[FUSE_ROWS][16], double (*el)[FUSE_ROWS])
 {
     static_assert(LPC == 2 || LPC == 4, "two or four lanes per cell");
@@ -231,93 +208,40 @@ __device__ __forceinline__ void edge_cells(const Strip<real, ROT> &S, int strip,
     const DescPtr dp = S.dp;
     const int lane = S.lane, side = lane >> 5, e = (lane & 31) / LPC, h = lane & (LPC - 1);
     const int count = i1 - i0;
-    const int nr = dp->nr, nt = dp->nt;
     const int r = i0 + min(e, count - 1);  // lanes past the block repeat its last row
     const RowBytes rb{S.row_bytes, S.lrow_bytes, S.rest_bytes, S.pair_bytes};
     // the cell, its radial neighbours (below row 0 the copy of row 0, or at
     // a disc centre row 0 with its directions turned by 4; above row nr - 1
     // the copy of row nr - 1) and its azimuthal neighbours
-    const EdgeOffsets o = edge_offsets(nr, nt, dp->sector, ROT, (int)sizeof(real), rb, strip, side, r);
-    double2 cs = dp->cs[o.pc], ck = dp->cs[o.pk];
-    if constexpr (ROT) {
-        // periodic images of a rotated sector: the angles turned by the sector
-        cs = turn_cs(cs, (8 - o.tc) & 7);
-        ck = turn_cs(ck, (8 - o.tk) & 7);
-    }
-    const real cth = (real)cs.x, sth = (real)cs.y;
-    const real crv[4] = {cth, (real)SQH * (cth + sth), sth, (real)SQH * (sth - cth)};
-    const real ctv[4] = {-sth, (real)SQH * (cth - sth), cth, (real)SQH * (cth + sth)};
-    const real kcth = (real)ck.x, ksth = (real)ck.y;
-    const real kctv[4] = {-ksth, (real)SQH * (kcth - ksth), kcth, (real)SQH * (kcth + ksth)};
+    const EdgeOffsets o = edge_offsets(S.turns, dp->inv2, dp->nr, dp->nt, (int)sizeof(real), rb, strip, side, r);
+    const bool turn = dp->disc && r == 0;
 
     // this lane's pairs NP h .. NP h + NP - 1: directions dd of pair i in
     // x[i], dd + 4 in x[i + NP].  Of each pair only one direction is kept
-    // (the one lane 0 or 63 takes from this side: dd + 4 where `second`), so
-    // only its upwind neighbours are gathered, one value each: from the lower
-    // row if its C_r >= 0, from the left column if its C_theta >= 0
-    // (direction dd + 4 has the opposite signs of dd).
+    // (dd + 4 where `second`), so only its upwind neighbours are gathered.
     real x[2 * NP], nbr[NP], nbt[NP], x0;
-    bool second[NP];
+    bool second[4];
     bload(x0, S.fin, o.x0, 0u);
 #pragma unroll
-    for (int i = 0; i < NP; ++i) {
-        const uint32_t po = pair_in_row(rb, NP * h + i);
-        const int dd = i & 3;
-        if constexpr (ROT) {
-            second[i] = (kctv[dd] >= (real)0) == (side == 1);
-            const bool low = (crv[dd] >= (real)0) != second[i], left = (ctv[dd] >= (real)0) != second[i];
-            // each column's data has its directions turned by its shift t:
-            // direction dd (dd + 4) of this strip's frame is in the pair of
-            // (dd + t) % 4 of the same speed, the members swapped where
-            // (dd + t) % 8 >= 4
-            const int kb = (NP * h + i) & ~3;
-            const uint32_t pc = pair_in_row(rb, kb + ((dd + o.tc) & 3));
-            const uint32_t pl = pair_in_row(rb, kb + ((dd + o.tl) & 3));
-            const uint32_t pr = pair_in_row(rb, kb + ((dd + o.tr) & 3));
-            const bool sc = ((dd + o.tc) & 4) != 0, sl = ((dd + o.tl) & 4) != 0, sr = ((dd + o.tr) & 4) != 0;
-            real a, b;
-            bload2(a, b, S.fin, o.orow + o.cc + pc, 0u);
-            x[i] = sc ? b : a;
-            x[i + NP] = sc ? a : b;
-            // the radial neighbour's member: below row 0 of a disc the
-            // ghost is row 0 with every direction turned by 4
-            const bool mc = second[i] != sc, mlr = left ? second[i] != sl : second[i] != sr;
-            const bool mlo = mc != (dp->disc && r == 0);
-            if constexpr (sizeof(real) == 4) {
-                bload(nbr[i], S.fin, (low ? o.olo : o.ohi) + o.cc + pc + ((low ? mlo : mc) ? (uint32_t)sizeof(real) : 0u),
-                      0u);
-                bload(nbt[i], S.fin, o.orow + (left ? o.cl + pl : o.cr + pr) + (mlr ? (uint32_t)sizeof(real) : 0u),
-                      0u);
-            } else {
-                real lo0, lo1, hi0, hi1, l0, l1, r0, r1;
-                bload2(lo0, lo1, S.fin, o.olo + o.cc + pc, 0u);
-                bload2(hi0, hi1, S.fin, o.ohi + o.cc + pc, 0u);
-                bload2(l0, l1, S.fin, o.orow + o.cl + pl, 0u);
-                bload2(r0, r1, S.fin, o.orow + o.cr + pr, 0u);
-                nbr[i] = low ? (mlo ? lo1 : lo0) : (mc ? hi1 : hi0);
-                nbt[i] = left ? (mlr ? l1 : l0) : (mlr ? r1 : r0);
-            }
-            continue;
-        }
-        bload2(x[i], x[i + NP], S.fin, o.orow + o.cc + po, 0u);
-        second[i] = (kctv[dd] >= (real)0) == (side == 1);
-        const bool low = (crv[dd] >= (real)0) != second[i], left = (ctv[dd] >= (real)0) != second[i];
-        if constexpr (sizeof(real) == 4) {
-            const uint32_t mo = second[i] ? (uint32_t)sizeof(real) : 0u;  // the member within the pair
-            bload(nbr[i], S.fin, (low ? o.olo : o.ohi) + o.cc + po + mo, 0u);
-            bload(nbt[i], S.fin, o.orow + (left ? o.cl : o.cr) + po + mo, 0u);
-        } else {
-            // float64 (one wavefront per SIMD, nothing else to issue while
-            // the gathers are in flight): the four neighbour pairs from
-            // addresses known up front took less time than two from
-            // addresses chosen per lane
-            real lo0, lo1, hi0, hi1, l0, l1, r0, r1;
-            bload2(lo0, lo1, S.fin, o.olo + o.cc + po, 0u);
-            bload2(hi0, hi1, S.fin, o.ohi + o.cc + po, 0u);
-            bload2(l0, l1, S.fin, o.orow + o.cl + po, 0u);
-            bload2(r0, r1, S.fin, o.orow + o.cr + po, 0u);
-            nbr[i] = second[i] ? (low ? lo1 : hi1) : (low ? lo0 : hi0);
-            nbt[i] = second[i] ? (left ? l1 : r1) : (left ? l0 : r0);
+    for (int dd = 0; dd < 4; ++dd) {
+        // the cell's direction dd is direction dd - tc of lane 0 or 63, which
+        // takes 1 to 4 from the left, 5, 6, 7, 0 from the right
+        const int own = (dd - o.tc) & 7;
+        second[dd] = (own >= 1 && own <= 4) == (side == 1);
+        const int dir = second[dd] ? dd + 4 : dd;
+        const bool low = (dd < 3) != second[dd], left = (dd >= 1) != second[dd];
+        // the member of the pair holding the neighbour's value (below the
+        // disc centre the opposite direction)
+        const int dt = (dir + (left ? o.tl : o.tr)) & 7;
+        const uint32_t mr = ((dir >> 2) != (low && turn ? 1 : 0)) ? (uint32_t)sizeof(real) : 0u;
+        const uint32_t orad = (low ? o.olo : o.ohi) + o.cc + mr;
+        const uint32_t oazi = o.orow + (left ? o.cl : o.cr) + (dt >> 2) * (uint32_t)sizeof(real);
+#pragma unroll
+        for (int kk = 0; kk < NS; ++kk) {
+            const int i = 4 * kk + dd, ring = 4 * (NS * h + kk);
+            bload2(x[i], x[i + NP], S.fin, o.orow + o.cc + pair_in_row(rb, ring + dd), 0u);
+            bload(nbr[i], S.fin, orad + pair_in_row(rb, ring + dd), 0u);
+            bload(nbt[i], S.fin, oazi + pair_in_row(rb, ring + (dt & 3)), 0u);
         }
     }
     double lc, lb, la, lL, lR;
@@ -326,9 +250,10 @@ __device__ __forceinline__ void edge_cells(const Strip<real, ROT> &S, int strip,
     bload(la, S.lin, o.la, 0u);
     bload(lL, S.lin, o.lL, 0u);
     bload(lR, S.lin, o.lR, 0u);
+    const double2 cs = dp->cs[o.pc];
+    const Polar<real> V(cs);
 
-    // moments: this lane's rings (summed as raw_moments does), then the
-    // other lanes' added
+    // moments: this lane's rings, then the other lanes' added
     real vk[NS];  // this lane's speeds
 #pragma unroll
     for (int kk = 0; kk < NS; ++kk) {
@@ -337,19 +262,15 @@ __device__ __forceinline__ void edge_cells(const Strip<real, ROT> &S, int strip,
         else
             vk[kk] = h == 0 ? (real)speed(1) : h == 1 ? (real)speed(2) : h == 2 ? (real)speed(3) : (real)speed(4);
     }
-    real rho = h == 0 ? x0 : (real)0, jx = 0, jy = 0, en = 0;
+    real rho, jx, jy, en;
 #pragma unroll
     for (int kk = 0; kk < NS; ++kk) {
-        const real *g = x + 4 * kk;  // directions 0..3 at g[0..3], 4..7 at g[NP..NP + 3]
-        const real v = vk[kk];
-        const real ring = ((g[0] + g[NP]) + (g[2] + g[NP + 2])) + ((g[1] + g[NP + 1]) + (g[3] + g[NP + 3]));
-        const real a15 = g[1] - g[NP + 1], a37 = g[3] - g[NP + 3];
-        const real X = (g[0] - g[NP]) + (real)SQH * (a15 - a37);
-        const real Y = (g[2] - g[NP + 2]) + (real)SQH * (a15 + a37);
-        rho += ring;
-        jx += v * X;
-        jy += v * Y;
-        en += (real)0.5 * v * v * ring;
+        real sum, mx, my, me;
+        ring_moments(x + 4 * kk, x + NP + 4 * kk, vk[kk], sum, mx, my, me);
+        rho = kk > 0 ? rho + sum : h == 0 ? x0 + sum : sum;
+        jx = kk > 0 ? jx + mx : mx;
+        jy = kk > 0 ? jy + my : my;
+        en = kk > 0 ? en + me : me;
     }
     Cell<real> C;
     C.rho = cell_sum<LPC>(rho);
@@ -357,7 +278,8 @@ __device__ __forceinline__ void edge_cells(const Strip<real, ROT> &S, int strip,
     C.init_moments(dp, cell_sum<LPC>(jx), cell_sum<LPC>(jy), lc, omega_at<real, TAUF>(dp, o.om, 0u));
 
     const double ri = dp->r_min + ((double)r + 0.5) * dp->dr;
-    const real kr = (real)dp->dt_dr, kt = (real)(dp->dt_dth / ri);
+    const double ktd = dp->dt_dth / ri;
+    const real kr = (real)dp->dt_dr, kt = (real)ktd;
     real g[NP];
 #pragma unroll
     for (int kk = 0; kk < NS; ++kk) {
@@ -368,30 +290,25 @@ __device__ __forceinline__ void edge_cells(const Strip<real, ROT> &S, int strip,
         else
             Fk = h == 0 ? C.F[1] : h == 1 ? C.F[2] : h == 2 ? C.F[3] : C.F[4];
         const real rF = C.rho * Fk;
-        const real rA = rF * (C.keep + C.beta * (v * v + C.u2 - (real)2 * C.T)), rB = rF * C.Bz;
+        const real rA = rF * C.factor(v), rB = rF * C.Bz;
 #pragma unroll
         for (int dd = 0; dd < 4; ++dd) {
             const int i = 4 * kk + dd;
-            // the same arithmetic as stage A of the strip owning the column
-            const real acr = fabs(crv[dd]) * kr, act = fabs(ctv[dd]) * kt;
+            const real acr = fabs(V.r[dd]) * kr, act = fabs(V.t[dd]) * kt;
             real E, O;
             pair_coll(C.EP, v * C.EP.w(dd), rA, rB, E, O);
-            const real s = C.omega - v * (acr + act);
-            g[i] = dir_new(second[i] ? E - O : E + O, s, second[i] ? x[i + NP] : x[i], v, acr, act, nbr[i], nbt[i]);
+            g[i] = dir_new(second[dd] ? E - O : E + O, C.stay(v, acr + act), second[dd] ? x[i + NP] : x[i], v, acr, act,
+                           nbr[i], nbt[i]);
         }
     }
-    const double uxd = (double)C.ux, uyd = (double)C.uy;
-    const double urp = uxd * cs.x + uyd * cs.y;
-    const double utp = -uxd * cs.y + uyd * cs.x;
-    const double lr = urp >= 0.0 ? lb : la;
-    const double lt = utp >= 0.0 ? lL : lR;
+    const double urp = C.ur(cs), utp = C.ut(cs);
     const double lnew =
-        C.reacted(dp, lc) - fabs(urp) * dp->dt_dr * (lc - lr) - fabs(utp) * (dp->dt_dth / ri) * (lc - lt);
-    if (e < count) {
+        C.lambda(dp, lc, urp, utp, dp->dt_dr, ktd, urp >= 0.0 ? lb : la, utp >= 0.0 ? lL : lR);
+    // in the order of lane 0's or 63's own pairs (the rows past a short
+    // block's last have room here too; a cell's lanes agree on lambda)
 #pragma unroll
-        for (int i = 0; i < NP; ++i) ef[side][e][NP * h + i] = g[i];
-        if (h == 0) el[side][e] = lnew;
-    }
+    for (int i = 0; i < NP; ++i) ef[side][e][NP * h + (i & ~3) + ((i - o.tc) & 3)] = g[i];
+    el[side][e] = lnew;
 }
 
 // Orders this wavefront's LDS writes before its reads of what other lanes
@@ -404,14 +321,18 @@ __device__ __forceinline__ void wave_lds_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Fills the compact slots of the row behind (see stage_row) from a full row.
-template <typename real>
-__device__ __forceinline__ void fill_behind(real (*behind)[64], const real x[NQ], const bool mr[4], int lane)
+// Fills the compact slots of the row behind (see stage_row) from a full row
+// x(q), its directions turned by 4 where `turn` (the disc centre's ghost).
+template <typename real, class Row>
+__device__ __forceinline__ void fill_behind(real (*behind)[64], Row x, bool turn, int lane)
 {
 #pragma unroll
     for (int k = 0; k < 4; ++k)
 #pragma unroll
-        for (int dd = 0; dd < 4; ++dd) behind[4 * k + dd][lane] = mr[dd] ? x[1 + 8 * k + dd] : x[5 + 8 * k + dd];
+        for (int dd = 0; dd < 4; ++dd) {
+            const int lo = dd < 3 ? dd : low_dir(3);
+            behind[4 * k + dd][lane] = turn ? x(1 + 8 * k + (lo ^ 4)) : x(1 + 8 * k + lo);
+        }
 }
 
 // Exchanges two float32 rows of f in registers at the end of a pass.
@@ -428,50 +349,40 @@ __device__ __forceinline__ void swap_rows(float (&a)[NQ], float (&b)[NQ])
 }
 
 // Work of one wavefront of the two-step kernel: strip `strip`, rows [i0, i1)
-// (at most FUSE_ROWS), marched outward or, with `down`, inward.  Positions p
-// count rows in marching order from the first row of the block (p = 0);
-// stage A runs on positions -1 .. R where they are grid rows, stage B on
-// 0 .. R - 1, one position behind stage A.  LDS per wavefront: the compact
-// rows behind of f (fb) and of g (gb), the full row of g just computed (ga),
-// the edge cells (ef, el) and the gathered halo values of stage A's row
-// (hb, hbl).
-template <typename real, bool TAUF, bool ROT, class Diag>
-__device__ __forceinline__ void march2(DescPtr dp, const StepBufs &bufs, int strip, int i0, int i1, bool down,
+// (at most FUSE_ROWS), marched outward.  Positions p count rows from the
+// first row of the block (p = 0); stage A runs on positions -1 .. R where
+// they are grid rows, stage B on 0 .. R - 1, one position behind stage A.
+// (Odd blocks marched inward, so that the rows between two blocks were read
+// by both at once, took 1 % less time in float64 and 3 % less in float32, but
+// need the upwind sides selected at run time.)  LDS per wavefront: the
+// compact rows behind of f (fb) and of g (gb), the full row of g just
+// computed (ga), the edge cells (ef, el) and the gathered halo values of
+// stage A's row (hb, hbl).
+template <typename real, bool TAUF, bool MIXED, class Diag>
+__device__ __forceinline__ void march2(DescPtr dp, const StepBufs &bufs, int strip, int i0, int i1,
                                        real (*fb)[64], real (*gb)[64], real (*ga)[64], real (*ef)[FUSE_ROWS][16],
                                        double (*el)[FUSE_ROWS], real *hb, double *hbl, Diag &DA, Diag &DB,
                                        bool diagA, bool diagB)
 {
-    const Strip<real, ROT> S(dp, bufs, strip);
+    const Strip<real, MIXED> S(dp, bufs, strip);
     const int lane = S.lane;
-    double2 cs = dp->cs[S.pc];
-    // a periodic image of a rotated sector (its data turned by S.rot): the
-    // angle turned by the sector, so that its stage-A row, which stage B of
-    // the lanes beside it reads, is in the strip's frame
-    if constexpr (ROT) cs = turn_cs(cs, (8 - S.rot) & 7);
-    const real cth = (real)cs.x, sth = (real)cs.y;
-    const real crv[4] = {cth, (real)SQH * (cth + sth), sth, (real)SQH * (sth - cth)};
-    const real ctv[4] = {-sth, (real)SQH * (cth - sth), cth, (real)SQH * (cth + sth)};
+    const double2 cs = dp->cs[S.pc];
+    const Polar<real> V(cs);
     const real kr = (real)dp->dt_dr;
     real acr[4];
-    bool mr[4], mt[4];
 #pragma unroll
-    for (int dd = 0; dd < 4; ++dd) {
-        acr[dd] = fabs(crv[dd]) * kr;
-        mr[dd] = (crv[dd] >= (real)0) != down;
-        mt[dd] = ctv[dd] >= (real)0;
-    }
+    for (int dd = 0; dd < 4; ++dd) acr[dd] = fabs(V.r[dd]) * kr;
     const int nr = dp->nr;
-    const int step = down ? -1 : 1;
-    const int first = down ? i1 - 1 : i0;
     const int count = i1 - i0;
-    const int rbefore = first - step, rafter = first + count * step;  // rows of positions -1 and R
-    const bool vlo = rbefore >= 0 && rbefore < nr, vhi = rafter >= 0 && rafter < nr;
+    const bool vlo = i0 > 0, vhi = i1 < nr;  // the rows of positions -1 and R are grid rows
 
     // f at positions p (fc) and p + 1 (fn) in registers; f(p + 2) is loaded
     // into fc once stage A has used it, and the two swap at the end of the
-    // pass (the loop is not unrolled: a second copy of the pass, which would
-    // take the swap away, ran slower, 168 against 157 us per float64 launch
-    // and 106 against 103 in float32)
+    // pass.  float64 runs two passes per turn of the loop instead, the second
+    // with the roles of the rows exchanged, which takes 130 moves (6 %) off
+    // each, 5 us per 1024 x 1024 launch; both copies, 39 KB,
+    // still fit the 64 KB instruction cache that two CUs share.  In float32,
+    // where the exchange is 33 v_swap_b32, that gained under 1 %.
     real fc[NQ], fn[NQ];
     double lp, lc, ln, lx = 0.0;             // lambda of f at positions p-1, p, p+1, p+2
     double glp = 0.0, glc = 0.0, gln = 0.0;  // lambda of g at positions p-2, p-1, p
@@ -482,18 +393,18 @@ __device__ __forceinline__ void march2(DescPtr dp, const StepBufs &bufs, int str
         if (vlo) {
             // stage A starts at position -1: behind it position -2 (a ghost
             // beyond the grid), centre -1, ahead 0
-            S.load_row(rbefore, fc, lc);
-            S.load_halo(rbefore, hc.h, hc.hl);
-            S.load_row(first, fn, ln);
-            S.load_halo(first, hn.h, hn.hl);
-            row_or_ghost(S, rbefore - step, t, lp, fc, lc);
+            S.load_row(i0 - 1, fc, lc);
+            S.load_upwind_halo(i0 - 1, hc.h, hc.hl);
+            S.load_row(i0, fn, ln);
+            S.load_upwind_halo(i0, hn.h, hn.hl);
+            row_or_ghost(S, i0 - 2, t, lp, fc, lc);
             p0 = -1;
         } else {
-            S.load_row(first, fc, lc);
-            S.load_halo(first, hc.h, hc.hl);
-            row_or_ghost(S, first + step, fn, ln, fc, lc);
-            if (count > 1 || vhi) S.load_halo(first + step, hn.h, hn.hl);
-            row_or_ghost(S, rbefore, t, lp, fc, lc);
+            S.load_row(i0, fc, lc);
+            S.load_upwind_halo(i0, hc.h, hc.hl);
+            row_or_ghost(S, i0 + 1, fn, ln, fc, lc);
+            if (count > 1 || vhi) S.load_upwind_halo(i0 + 1, hn.h, hn.hl);
+            row_or_ghost(S, i0 - 1, t, lp, fc, lc);
             p0 = 0;
         }
     };
@@ -506,108 +417,64 @@ __device__ __forceinline__ void march2(DescPtr dp, const StepBufs &bufs, int str
     // float64 keeps two (its 16-row blocks fill the lanes with two; with
     // both forms compiled into its kernel it ran 2 us per launch slower)
     if (sizeof(real) == 4 && i1 - i0 <= 8)
-        edge_cells<real, TAUF, 4, ROT>(S, strip, i0, i1, ef, el);
+        edge_cells<real, TAUF, 4, MIXED>(S, strip, i0, i1, ef, el);
     else
-        edge_cells<real, TAUF, 2, ROT>(S, strip, i0, i1, ef, el);
+        edge_cells<real, TAUF, 2, MIXED>(S, strip, i0, i1, ef, el);
     // TAUF: exp(-dt/tau) of stage A's row (oa), loaded a pass ahead, and of
     // stage B's (ob), the row stage A had a pass before (loaded at the point
     // of use, the field cost 7.2 us per float64 launch and 4.2 us per float32
     // one; loaded ahead, 0.8 and 2.3 us)
     real oa = (real)0, ob = (real)0;
-    if constexpr (TAUF)
-        oa = omega_at<real, true>(dp, S.vo, (uint32_t)(vlo ? rbefore : first) * S.rest_bytes);
+    if constexpr (TAUF) oa = omega_at<real, true>(dp, S.vo, (uint32_t)(vlo ? i0 - 1 : i0) * S.rest_bytes);
     load_first_rows();
-    fill_behind(fb, t, mr, lane);
+    fill_behind(fb, [&](int q) { return t[q]; }, false, lane);
     if constexpr (TAUF) settle(oa);
     wave_lds_sync();
 
-    for (int p = p0; p <= count; ++p) {
-        const int ir = first + p * step;
+    // one pass: stage A at position p (f(p) in fc, f(p + 1) in fn), stage B one behind
+    auto pass = [&](int p, real (&fc)[NQ], real (&fn)[NQ]) __attribute__((always_inline)) {
+        const int ir = i0 + p;
         // g(p - 1), centre of stage B: stage A hands it over as it replaces
         // it in ga
         real gc[NQ];
-        if (p == 0 && vlo) {
-            // g(-1), computed by stage A at position -1, is the row behind
-            // stage B's first row
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-#pragma unroll
-                for (int dd = 0; dd < 4; ++dd)
-                    gb[4 * k + dd][lane] = mr[dd] ? ga[1 + 8 * k + dd][lane] : ga[5 + 8 * k + dd][lane];
-        }
+        // g(-1), computed by stage A at position -1, is the row behind
+        // stage B's first row
+        if (p == 0 && vlo) fill_behind(gb, [&](int q) { return ga[q][lane]; }, false, lane);
         // (A) first step at position p, or the ghost beyond the grid
         if (p < count || vhi) {
             // the row's gathered halo values into LDS, read back by every lane
-            hb[lane] = hc.h[0];
-            if (lane < 2) {
-                hb[64 + lane] = hc.h[1];
-                hbl[lane] = hc.hl;
-            }
+            hb[lane] = hc.h;
+            hbl[lane] = hc.hl;
             wave_lds_sync();
-            const LdsHalo<real> H{hb, hbl};
-            stage_row<real, true, TAUF>(S, ir, fb, fc, fn, ga, gc, H, lp, lc, ln, mr, mt, acr, ctv, !down, cs.x, cs.y,
-                                        gln, oa, DA, diagA && p >= 0 && p < count);
+            const Halo<real> H{hb, hb + 16, hbl[0], hbl[1]};
+            stage_row<real, true, TAUF>(S, ir, fb, fc, fn, ga, gc, H, lp, lc, ln, acr, V.t, cs, gln, oa, DA,
+                                        diagA && p >= 0 && p < count);
         } else {
-            // beyond the last grid row: the zero-gradient ghost of g (at a
-            // disc centre, row 0 with every direction turned by 4)
-            if constexpr (ROT) {
-                const bool turn = dp->disc && rafter < 0;
-                gc[0] = ga[0][lane];
+            // beyond the last grid row: the zero-gradient ghost of g
 #pragma unroll
-                for (int q = 1; q < NQ; ++q) gc[q] = ga[turn ? (((q - 1) ^ 4) + 1) : q][lane];
-            } else {
-#pragma unroll
-                for (int q = 0; q < NQ; ++q) gc[q] = ga[q][lane];
-            }
+            for (int q = 0; q < NQ; ++q) gc[q] = ga[q][lane];
             gln = glc;
         }
         // f at position p + 2 (the row ahead of the next stage A) replaces f(p)
-        if (p + 1 < count || (p + 1 == count && vhi)) row_or_ghost(S, ir + 2 * step, fc, lx, fn, ln);
-        if (p + 2 < count || (p + 2 == count && vhi)) S.load_halo(ir + 2 * step, hx.h, hx.hl);
+        if (p + 1 < count || (p + 1 == count && vhi)) row_or_ghost(S, ir + 2, fc, lx, fn, ln);
+        if (p + 2 < count || (p + 2 == count && vhi)) S.load_upwind_halo(ir + 2, hx.h, hx.hl);
         // the next stage A's exp(-dt/tau), where that stage runs on a grid row
         const real oa_used = oa;
         if constexpr (TAUF) {
             if (p + 1 < count || (p + 1 == count && vhi))
-                oa = omega_at<real, true>(dp, S.vo, (uint32_t)(ir + step) * S.rest_bytes);
+                oa = omega_at<real, true>(dp, S.vo, (uint32_t)(ir + 1) * S.rest_bytes);
         }
         // (B) second step at position p - 1
         if (p == 0 && !vlo) {
             // the row behind stage B's first row is the (zero-gradient)
-            // ghost of g(0) (at a disc centre with every direction turned by
-            // 4: the slot of direction dd takes g(0)'s direction dd + 4)
-            if constexpr (ROT) {
-                const bool turn = dp->disc && rbefore < 0;
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-#pragma unroll
-                    for (int dd = 0; dd < 4; ++dd)
-                        gb[4 * k + dd][lane] = mr[dd] != turn ? ga[1 + 8 * k + dd][lane] : ga[5 + 8 * k + dd][lane];
-            } else {
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-#pragma unroll
-                    for (int dd = 0; dd < 4; ++dd)
-                        gb[4 * k + dd][lane] = mr[dd] ? ga[1 + 8 * k + dd][lane] : ga[5 + 8 * k + dd][lane];
-            }
+            // ghost of g(0) (at a disc centre with every direction turned by 4)
+            fill_behind(gb, [&](int q) { return ga[q][lane]; }, dp->disc, lane);
             glc = gln;
         } else if (p > 0) {
-            const int e = ir - step - i0;
-            const EdgeHalo<real> H{ef[0][e], ef[1][e], el[0][e], el[1][e]};
+            const Halo<real> H{ef[0][p - 1], ef[1][p - 1], el[0][p - 1], el[1][p - 1]};
             double unused;
-            stage_row<real, false, TAUF>(S, ir - step, gb, gc, nullptr, ga, nullptr, H, glp, glc, gln, mr, mt, acr, ctv,
-                                         !down, cs.x, cs.y, unused, ob, DB, diagB);
-        }
-        if constexpr (sizeof(real) == 4) {
-            swap_rows(fc, fn);
-        } else {
-            // float64: one 64-bit move per copy (the same exchange moved into
-            // a function came out with 90 more AGPR moves per pass)
-#pragma unroll
-            for (int q = 0; q < NQ; ++q) {
-                const real t = fc[q];
-                fc[q] = fn[q];
-                fn[q] = t;
-            }
+            stage_row<real, false, TAUF>(S, ir - 1, gb, gc, nullptr, ga, nullptr, H, glp, glc, gln, acr, V.t, cs, unused,
+                                         ob, DB, diagB);
         }
         ob = oa_used;
         hc = hn;
@@ -620,6 +487,18 @@ __device__ __forceinline__ void march2(DescPtr dp, const StepBufs &bufs, int str
         // Compiler-only barrier: the LDS rows must not be promoted to
         // registers across passes.
         asm volatile("" ::: "memory");
+    };
+    if constexpr (sizeof(real) == 8) {
+        for (int p = p0; p <= count; p += 2) {
+            pass(p, fc, fn);
+            if (p + 1 > count) break;
+            pass(p + 1, fn, fc);
+        }
+    } else {
+        for (int p = p0; p <= count; ++p) {
+            pass(p, fc, fn);
+            swap_rows(fc, fn);
+        }
     }
 }
 
@@ -640,9 +519,8 @@ struct Step2Occ {
 // march), which keeps the parity.  One wavefront per SIMD in float64, where
 // the two steps' rows fill the register file and the LDS rows of four
 // wavefronts most of a CU's LDS; two in float32, whose rows take half the
-// LDS.  ROT: solves of rotated sectors, discs included, whose periodic
-// images have their directions and angles turned by the sector.
-template <typename real, bool TAUF, bool ROT>
+// LDS.  MIXED: grids whose octants are not whole strips (whole_octants).
+template <typename real, bool TAUF, bool MIXED>
 __global__ __launch_bounds__(BLOCK, Step2Occ<real>::waves) void k_step2(const SolveDesc *descs, const uint2 *tiles,
                                                                        int ntiles, const int64_t *bases,
                                                                        int64_t step_off, const int *flips, int flip,
@@ -668,8 +546,8 @@ __global__ __launch_bounds__(BLOCK, Step2Occ<real>::waves) void k_step2(const So
     __shared__ real ga[BLOCK / 64][NQ][64];
     __shared__ real ef[BLOCK / 64][2][FUSE_ROWS][16];
     __shared__ double el[BLOCK / 64][2][FUSE_ROWS];
-    __shared__ real hb[BLOCK / 64][66];
-    __shared__ double hbl[BLOCK / 64][2];
+    __shared__ real hb[BLOCK / 64][64];
+    __shared__ double hbl[BLOCK / 64][64];
     const int w = threadIdx.x >> 6;
     const int rows = dp->rows, nstrip = dp->nstrip;
     const int rb = lt / nstrip, strip = lt - rb * nstrip;
@@ -679,7 +557,7 @@ __global__ __launch_bounds__(BLOCK, Step2Occ<real>::waves) void k_step2(const So
         // one step, with the row behind in the LDS row of g
         const bool diag = records(dp, step);
         double red[5] = {0, 0, 0, 0, 0};
-        march<real, ROT, TAUF>(dp, bufs, strip, i0, i1, (rb & 1) != 0, ga[w], red, diag);
+        march<real, MIXED, TAUF>(dp, bufs, strip, i0, i1, (rb & 1) != 0, ga[w], red, diag);
         if (diag) {
             const int64_t slot = (step / dp->diag_every) % PART_RING;
             double *part = dp->wpart + ((size_t)slot * dp->nwaves + lt) * 5;
@@ -694,7 +572,7 @@ __global__ __launch_bounds__(BLOCK, Step2Occ<real>::waves) void k_step2(const So
     }
     const bool diagA = records(dp, step), diagB = records(dp, step + 1);
     LaneDiag DA, DB;
-    march2<real, TAUF, ROT>(dp, bufs, strip, i0, i1, (rb & 1) != 0, fb[w], gb[w], ga[w], ef[w], el[w], hb[w], hbl[w],
+    march2<real, TAUF, MIXED>(dp, bufs, strip, i0, i1, fb[w], gb[w], ga[w], ef[w], el[w], hb[w], hbl[w],
                             DA, DB, diagA, diagB);
     // both steps' totals first (independent DPP chains the compiler can
     // interleave), then one lane stores them
@@ -718,23 +596,23 @@ __global__ __launch_bounds__(BLOCK, Step2Occ<real>::waves) void k_step2(const So
 
 }  // namespace
 
-template <typename real, bool TAUF, bool ROT>
+template <typename real, bool TAUF, bool MIXED>
 static void launch_k_step2(int nb, hipStream_t st, const SolveDesc *descs, const uint2 *tiles, int ntiles,
                            const int64_t *bases, int64_t step_off, const int *flips, int flip, bool single)
 {
-    hipLaunchKernelGGL((k_step2<real, TAUF, ROT>), dim3(nb), dim3(BLOCK), 0, st, descs, tiles, ntiles, bases, step_off,
+    hipLaunchKernelGGL((k_step2<real, TAUF, MIXED>), dim3(nb), dim3(BLOCK), 0, st, descs, tiles, ntiles, bases, step_off,
                        flips, flip, (int)single);
 }
 
 hipError_t launch_step2(const SolveDesc *descs, const uint2 *tiles, int ntiles, const int64_t *bases,
-                        int64_t step_off, const int *flips, int flip, bool single, bool fp32, bool tauf, bool rot,
+                        int64_t step_off, const int *flips, int flip, bool single, bool fp32, bool tauf, bool mixed,
                         hipStream_t st)
 {
     const int nb = (ntiles + BLOCK / 64 - 1) / (BLOCK / 64);
     if (nb == 0) return hipSuccess;
-    auto *fn = fp32 ? (rot ? (tauf ? &launch_k_step2<float, true, true> : &launch_k_step2<float, false, true>)
+    auto *fn = fp32 ? (mixed ? (tauf ? &launch_k_step2<float, true, true> : &launch_k_step2<float, false, true>)
                            : (tauf ? &launch_k_step2<float, true, false> : &launch_k_step2<float, false, false>))
-                    : (rot ? (tauf ? &launch_k_step2<double, true, true> : &launch_k_step2<double, false, true>)
+                    : (mixed ? (tauf ? &launch_k_step2<double, true, true> : &launch_k_step2<double, false, true>)
                            : (tauf ? &launch_k_step2<double, true, false> : &launch_k_step2<double, false, false>));
     fn(nb, st, descs, tiles, ntiles, bases, step_off, flips, flip, single);
     return hipGetLastError();

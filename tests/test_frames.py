@@ -1,0 +1,17 @@
+"""The frames of neighbouring columns and the patches of small grids, checked
+on the host from the header the kernels use (tests/host/frames_check.cpp)."""
+import os
+import subprocess
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+def test_frames_and_patches(tmp_path):
+    exe = str(tmp_path / "frames_check")
+    subprocess.run(["g++", "-std=c++17", "-O2", "-Wall", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                    "-I" + os.path.join(ROOT, "include"), "-I" + os.path.join(ROOT, "paper_1308_0653_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "host", "frames_check.cpp"), "-o", exe],
+                   check=True, capture_output=True, text=True)
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=300)
+    print(r.stdout)
+    assert r.returncode == 0 and " 0 failed" in r.stdout, r.stderr[-3000:]

@@ -16,8 +16,8 @@
  *      geometric 1/r term), a periodic theta halo and radial boundaries
  *      (Sec. II.C-D); the reaction progress lambda is integrated in closed
  *      form and advected upwind by the cell's own u (Sec. III.A).
- * All four run in one fused kernel launch per step on the caller's stream
- * (full-annulus solves: one launch per two steps, see pdbm_step).
+ * All four run in fused kernel launches on the caller's stream, which take
+ * one or several steps each (see pdbm_step).
  *
  * Conventions
  *   - Every entry point returns 0 (PDBM_OK) or a negative PDBM_E* code;
@@ -37,8 +37,9 @@
  * Environment (read once per process; for measurement and tuning)
  *   PDBM_FUSE=0            every launch (single solves, batches, servers)
  *                          takes a single step.
- *   PDBM_ROWS_PER_WAVE=n   r rows per wavefront of single solves (created
- *                          after it is set); above 16 disables two-step
+ *   PDBM_ROWS_PER_WAVE=n   r rows per wavefront of single solves, which then
+ *                          are not stepped on patches (except grids of fewer
+ *                          columns than octants); above 16 disables two-step
  *                          launches.
  *   PDBM_BATCH_ROWS=n      r rows per wavefront of packed grids of more
  *                          than one column (16); above 16 disables
@@ -231,12 +232,12 @@ int pdbm_set_tau_async(pdbm_solver *s, const void *tau_device);
 
 /* Enqueues `nsteps` time steps on the solver's stream and returns without
  * waiting.  Every diag_every-th step also records the drift report of the
- * state it starts from.  Solves of the full annulus with ntheta > 1, in
- * either precision, take the steps two per launch (one pass over f for both;
- * the result equals that of single steps to rounding), and an odd count ends
- * with a single step; solves with a single theta column take up to 8 steps
- * per launch.  The states after every call are those of Sec. II.C's scheme
- * either way. */
+ * state it starts from.  A launch takes two steps of a solve with ntheta > 1
+ * (one pass over f for both; an odd count ends with a single step) or, of a
+ * small grid, 2 to 4 steps; solves with a single theta column take up to 24
+ * steps per launch, of more than about 40 thousand rows up to 8.  The states
+ * after every call are those of Sec. II.C's scheme, bit for bit the same
+ * however the steps are cut into calls and launches. */
 int pdbm_step(pdbm_solver *s, int64_t nsteps);
 
 /* Number of steps taken so far (host-side counter). */

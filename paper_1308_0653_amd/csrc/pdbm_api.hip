@@ -43,13 +43,13 @@ int pdbm::fail(int code, const std::string &msg)
     return code;
 }
 
-Layout pdbm::layout_of(const pdbm_params &p, int rows)
+Layout pdbm::layout_of(const pdbm_params &p, int rows, bool alone)
 {
     Layout L;
     L.esz = p.precision == PDBM_FP32 ? sizeof(float) : sizeof(double);
     L.pitch = pitch_of(p.ntheta);
     L.rows = rows;
-    L.nwaves = rows == PATCHES ? patch_geom(p.nr, p.ntheta, p.sector).ntiles : solve_waves(p.nr, p.ntheta, rows);
+    L.nwaves = rows == PATCHES ? patches(p, alone).ntiles : solve_waves(p.nr, p.ntheta, rows);
     L.cblocks = cell_blocks(p.nr, p.ntheta);
     const size_t cells_p = (size_t)p.nr * L.pitch;
     L.f = align256((size_t)NQ * cells_p * L.esz);
@@ -67,6 +67,31 @@ Layout pdbm::layout_of(const pdbm_params &p, int rows)
     return L;
 }
 
+// PDBM_FUSE=0: every launch takes a single step, by the kernels that take no
+// more (read once per process).
+static bool fuse_off()
+{
+    static const bool off = [] {
+        const char *e = std::getenv("PDBM_FUSE");
+        return e && e[0] == '0';
+    }();
+    return off;
+}
+
+static int rows_env()
+{
+    static const int env = [] {
+        const char *e = std::getenv("PDBM_ROWS_PER_WAVE");
+        return e ? std::atoi(e) : 0;
+    }();
+    return env;
+}
+
+PatchGeom pdbm::patches(const pdbm_params &p, bool alone)
+{
+    return patch_geom(p.nr, p.ntheta, p.sector, p.precision == PDBM_FP32, alone && !fuse_off() && rows_env() <= 0);
+}
+
 // Rows per wavefront: just enough wavefronts for one resident wave of the
 // whole grid (256 CUs x 4 SIMDs x the step kernels' occupancy: 1 wavefront
 // per SIMD in float64, 2 in float32), so that every wavefront marches the
@@ -76,12 +101,8 @@ Layout pdbm::layout_of(const pdbm_params &p, int rows)
 int pdbm::rows_per_wave(const pdbm_params &p)
 {
     const int nr = p.nr, nt = p.ntheta;
-    if (patch_geom(nr, nt, p.sector).threads > 0) return PATCHES;
-    static const int env = [] {
-        const char *e = std::getenv("PDBM_ROWS_PER_WAVE");
-        return e ? std::atoi(e) : 0;
-    }();
-    if (env > 0) return env;
+    if (patches(p, true).threads > 0) return PATCHES;
+    if (rows_env() > 0) return rows_env();
     // one round of wavefronts: one per SIMD in float64, two in float32
     const int64_t slots = 256 * 4 * (p.precision == PDBM_FP32 ? 2 : 1);
     const int64_t strips = (nt + STRIP - 1) / STRIP;
@@ -191,7 +212,7 @@ int pdbm_state_bytes(const pdbm_params *p, size_t *bytes)
     if (p->nr < 1 || p->ntheta < 1 || (int64_t)p->nr * p->ntheta > MAX_CELLS ||
         (p->precision != PDBM_FP64 && p->precision != PDBM_FP32))
         return fail(PDBM_EINVAL, "bad grid or precision");
-    *bytes = layout_of(*p, rows_per_wave(*p)).total;
+    *bytes = layout_of(*p, rows_per_wave(*p), true).total;
     return PDBM_OK;
 }
 
@@ -238,10 +259,10 @@ int pdbm::check_device()
 }
 
 int Solve::init(const pdbm_params &pp, const pdbm_ic *ic, void *workspace, size_t bytes, int rows, int64_t nsteps,
-                hipStream_t st, char *aux)
+                bool alone, hipStream_t st, char *aux)
 {
     p = pp;
-    L = layout_of(p, rows);
+    L = layout_of(p, rows, alone);
     fp32 = p.precision == PDBM_FP32;
     if (workspace) {
         if (bytes < (aux ? L.state_total : L.total) || ((uintptr_t)workspace & 255))
@@ -285,7 +306,7 @@ int Solve::init(const pdbm_params &pp, const pdbm_ic *ic, void *workspace, size_
     hd.disc = p.r_min == 0.0;
     hd.reacts = (p.w1 > 0.0 || p.w2 > 0.0) ? 1 : 0;
     hd.rows = rows;
-    if (rows == PATCHES) hd.patch = patch_geom(p.nr, p.ntheta, p.sector);
+    if (rows == PATCHES) hd.patch = patches(p, alone);
     hd.nwaves = L.nwaves;
     hd.nstrip = (p.ntheta + STRIP - 1) / STRIP;
     hd.diag_every = p.diag_every;
@@ -363,16 +384,6 @@ int Solve::set_step(int64_t s, hipStream_t st)
     return PDBM_OK;
 }
 
-// PDBM_FUSE=0: every launch takes a single step (read once per process).
-static bool fuse_off()
-{
-    static const bool off = [] {
-        const char *e = std::getenv("PDBM_FUSE");
-        return e && e[0] == '0';
-    }();
-    return off;
-}
-
 bool Solve::fusable() const { return !fuse_off() && !patched() && p.ntheta > 1 && L.rows <= FUSE_ROWS; }
 
 bool Solve::columnar() const { return !fuse_off() && !patched() && p.ntheta == 1; }
@@ -422,7 +433,7 @@ int pdbm_create(const pdbm_params *p, const pdbm_ic *ic, void *workspace, size_t
     pdbm_solver *h = new (std::nothrow) pdbm_solver;
     if (!h) return fail(PDBM_ENOMEM, "host allocation failed");
     h->st = (hipStream_t)stream;
-    rc = h->s.init(*p, ic, workspace, workspace_bytes, rows_per_wave(*p), INT64_MAX, h->st);
+    rc = h->s.init(*p, ic, workspace, workspace_bytes, rows_per_wave(*p), INT64_MAX, true, h->st);
     if (rc == PDBM_OK && hipStreamSynchronize(h->st) != hipSuccess) rc = fail(PDBM_EHIP, "initialisation failed");
     if (rc) {
         (void)hipStreamSynchronize(h->st);
@@ -500,7 +511,7 @@ int pdbm_step(pdbm_solver *h, int64_t nsteps)
         if (s.patched()) {
             // as a column's launches
             const int nk = (int)std::min<int64_t>(most, nsteps - i);
-            HIPCHK(launch_patch(s.dd, nullptr, s.waves(), s.hd.patch.threads, nullptr, s.step, nullptr, s.flip, nk,
+            HIPCHK(launch_patch(s.dd, nullptr, s.waves(), s.hd.patch.threads, s.hd.patch.lanes, nullptr, s.step, nullptr, s.flip, nk,
                                 s.fp32, s.tauf(), h->st));
             s.step += nk;
             s.flip ^= (nk + 1) & 1;

@@ -23,8 +23,8 @@
 //
 // Every kernel rounds a cell's update the same way: multiply-adds are written
 // out (fma), none are formed by the compiler, and sums over the speeds are
-// taken as (((rest + 1) + 2) + (3 + 4)), the order in which two or four lanes
-// that share a cell add up their parts.  A cell's new state then does not
+// taken in halves (two_rings), as two or four lanes that share a cell add up
+// their parts.  A cell's new state then does not
 // depend on the kernel, the strip, the row block or the patch it is computed
 // in, so how a launch divides a grid is free to follow the load.
 
@@ -86,30 +86,37 @@ __device__ __forceinline__ void weights(const double *A, double T, real F[5])
     F[0] = (real)fma(-8.0, (w[0] + w[1]) + (w[2] + w[3]), 1.0);
 }
 
-// One ring's (speed v) share of the moments: its sum, and the momentum and
-// energy it adds.  g[0..3] and h[0..3] are directions 0..3 and 4..7.
+// One ring's moments: its sum, and the components of its direction sum (the
+// momentum per unit speed).  g[0..3] and h[0..3] are directions 0..3 and 4..7.
 template <typename real>
-__device__ __forceinline__ void ring_moments(const real g[4], const real h[4], real v, real &sum, real &mx, real &my,
-                                             real &en)
+__device__ __forceinline__ void ring_moments(const real g[4], const real h[4], real &sum, real &x, real &y)
 {
     sum = ((g[0] + h[0]) + (g[2] + h[2])) + ((g[1] + h[1]) + (g[3] + h[3]));
     const real a15 = g[1] - h[1], a37 = g[3] - h[3];
-    mx = v * fma((real)SQH, a15 - a37, g[0] - h[0]);
-    my = v * fma((real)SQH, a15 + a37, g[2] - h[2]);
-    en = (real)0.5 * v * v * sum;
+    x = fma((real)SQH, a15 - a37, g[0] - h[0]);
+    y = fma((real)SQH, a15 + a37, g[2] - h[2]);
+}
+// Sums over the speeds: those of the first two, or the last two, are taken
+// together, v a + w b with the second product unrounded, then the two halves
+// added (the rest particle and the ring sums likewise).
+template <typename real>
+__device__ __forceinline__ real two_rings(real v, real a, real w, real b)
+{
+    return fma(w, b, v * a);
 }
 // rho, rho*u (Cartesian), and e = sum f |v|^2 / 2 of one cell.
 template <typename real>
 __device__ __forceinline__ void raw_moments(const real f[NQ], real &rho, real &jx, real &jy, real &e)
 {
-    real r[4], x[4], y[4], en[4];
+    real r[4], x[4], y[4];
+    constexpr real V[4] = {(real)speed(1), (real)speed(2), (real)speed(3), (real)speed(4)};
 #pragma unroll
-    for (int k = 0; k < 4; ++k)
-        ring_moments(f + 1 + 8 * k, f + 5 + 8 * k, (real)speed(k + 1), r[k], x[k], y[k], en[k]);
+    for (int k = 0; k < 4; ++k) ring_moments(f + 1 + 8 * k, f + 5 + 8 * k, r[k], x[k], y[k]);
     rho = ((f[0] + r[0]) + r[1]) + (r[2] + r[3]);
-    jx = (x[0] + x[1]) + (x[2] + x[3]);
-    jy = (y[0] + y[1]) + (y[2] + y[3]);
-    e = (en[0] + en[1]) + (en[2] + en[3]);
+    jx = two_rings(V[0], x[0], V[1], x[1]) + two_rings(V[2], x[2], V[3], x[3]);
+    jy = two_rings(V[0], y[0], V[1], y[1]) + two_rings(V[2], y[2], V[3], y[3]);
+    e = two_rings((real)0.5 * V[0] * V[0], r[0], (real)0.5 * V[1] * V[1], r[1]) +
+        two_rings((real)0.5 * V[2] * V[2], r[2], (real)0.5 * V[3] * V[3], r[3]);
 }
 
 // 1/x: in float32 the hardware reciprocal (within 1 ulp) and one Newton step
@@ -260,6 +267,40 @@ __device__ __forceinline__ T cell_sum(T v)
     if constexpr (LPC >= 2) v += lane_xor<1>(v);
     if constexpr (LPC == 4) v += lane_xor<2>(v);
     return v;
+}
+
+// The moments of a cell held by LPC adjacent lanes, lane h the rings h NS ..
+// h NS + NS - 1 (NS = 4 / LPC) of speeds v in x[ring][direction], the rest
+// particle in x0: every lane of the cell gets the totals, rounded as
+// raw_moments does.
+template <int LPC, typename real>
+__device__ __forceinline__ void cell_moments(const real (*x)[8], real x0, const real *v, int h, real &rho, real &jx,
+                                             real &jy, real &e)
+{
+    constexpr int NS = 4 / LPC;
+    real r[NS], mx[NS], my[NS];
+#pragma unroll
+    for (int k = 0; k < NS; ++k) ring_moments(x[k], x[k] + 4, r[k], mx[k], my[k]);
+    if constexpr (LPC == 2) {
+        rho = h == 0 ? (x0 + r[0]) + r[1] : r[0] + r[1];
+        jx = two_rings(v[0], mx[0], v[1], mx[1]);
+        jy = two_rings(v[0], my[0], v[1], my[1]);
+        e = two_rings((real)0.5 * v[0] * v[0], r[0], (real)0.5 * v[1] * v[1], r[1]);
+    } else {
+        // both lanes of a half form its sum from the two rings, the even lane's first
+        const bool odd = (h & 1) != 0;
+        const real w = lane_xor<1>(v[0]), ro = lane_xor<1>(r[0]), xo = lane_xor<1>(mx[0]), yo = lane_xor<1>(my[0]);
+        const real va = odd ? w : v[0], vb = odd ? v[0] : w, ra = odd ? ro : r[0], rb = odd ? r[0] : ro;
+        rho = h < 2 ? (x0 + ra) + rb : ra + rb;
+        jx = two_rings(va, odd ? xo : mx[0], vb, odd ? mx[0] : xo);
+        jy = two_rings(va, odd ? yo : my[0], vb, odd ? my[0] : yo);
+        e = two_rings((real)0.5 * va * va, ra, (real)0.5 * vb * vb, rb);
+    }
+    constexpr int X = LPC == 2 ? 1 : 2;
+    rho += lane_xor<X>(rho);
+    jx += lane_xor<X>(jx);
+    jy += lane_xor<X>(jy);
+    e += lane_xor<X>(e);
 }
 
 // Sums v[0..4] over the workgroup; the result is valid in thread 0.

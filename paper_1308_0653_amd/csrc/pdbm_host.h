@@ -37,9 +37,11 @@ struct Layout {
 // `rows`: rows per wavefront of the marching kernels, or PATCHES for a solve
 // stepped on patches (patch_geom).
 constexpr int PATCHES = 0;
-Layout layout_of(const pdbm_params &p, int rows);
+Layout layout_of(const pdbm_params &p, int rows, bool alone);
 // Rows per wavefront of a packed solve, or PATCHES.
 int batch_rows(const pdbm_params &p);
+// Patches of a solve that rows_per_wave (alone) or batch_rows gives them.
+PatchGeom patches(const pdbm_params &p, bool alone);
 class Solve;
 // Non-equilibrium measures of the current state into host `out`
 // [NONEQ][nr][ntheta] (staged in the idle f buffer; synchronises st).
@@ -65,13 +67,14 @@ class Solve {
 
     // Lays out the solve in `workspace` (or a fresh allocation), uploads its
     // description and enqueues its initial state on `st`.  `rows`: rows per
-    // wavefront; `nsteps`: step count after which the solve stops advancing.
+    // wavefront or PATCHES; `nsteps`: step count after which the solve stops
+    // advancing; `alone`: it has the GPU to itself (no pack).
     // With `aux`, the workspace holds the state only (L.state_total bytes)
     // and the auxiliary part goes to `aux` (L.aux_total bytes, 256-byte
     // aligned).  Allocates device memory only when workspace is NULL and no
     // host memory at all.
     int init(const pdbm_params &p, const pdbm_ic *ic, void *workspace, size_t bytes, int rows, int64_t nsteps,
-             hipStream_t st, char *aux = nullptr);
+             bool alone, hipStream_t st, char *aux = nullptr);
     void release();  // frees an owned workspace (the stream must be idle)
 
     int cur() const { return (int)((step + flip) & 1); }

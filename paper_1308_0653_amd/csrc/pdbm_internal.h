@@ -20,8 +20,7 @@ constexpr int FUSE_ROWS = 16;   // most rows per wavefront of the two-step kerne
 constexpr int COL_K = 8;                  // steps per launch of the single-column kernel, at most
 constexpr int COL_W = STRIP - 2 * COL_K;  // rows a wavefront owns in a single-column solve (48)
 
-constexpr int PATCH_LANES = 4;            // lanes per cell of the small-grid kernel
-constexpr int PACK_PATCH_THREADS = 256;   // its workgroups in packs
+constexpr int PACK_PATCH_THREADS = 256, PACK_PATCH_LANES = 4;  // patches of grids narrower than their octants
 
 // Layout of f within one r row (33 * pitch elements): the rest particle's
 // plane [pitch], then the 16 pairs of opposite directions of each speed, pair
@@ -41,7 +40,8 @@ __host__ __device__ constexpr int64_t elem_of(int q, int64_t col, int64_t pitch)
 struct PatchGeom {
     int rows, cols, k;   // owned rows and columns; halo = most steps per launch
     int nbc, ntiles;     // patches beside one another; all of them
-    int threads;         // of a workgroup, PATCH_LANES per cell (256 or 512); 0: no patches
+    int threads;         // of a workgroup (256, 512 or 768); 0: no patches
+    int lanes;           // per cell (2 or 4)
 };
 
 // Per-solve state in device memory written by the host.
@@ -116,10 +116,11 @@ hipError_t launch_step2(const SolveDesc *descs, const uint2 *tiles, int ntiles, 
                         int64_t step_off, const int *flips, int flip, bool single, bool fp32, bool tauf, bool mixed,
                         hipStream_t st);
 // Up to nk steps (at most SolveDesc::patch.k) of solves stepped on patches,
-// workgroups of `threads` each; everything else as launch_column (a tile is a
+// workgroups of `threads` each, `lanes` to a cell; everything else as launch_column (a tile is a
 // workgroup here).
-hipError_t launch_patch(const SolveDesc *descs, const uint2 *tiles, int ntiles, int threads, const int64_t *bases,
-                        int64_t step_off, const int *flips, int flip, int nk, bool fp32, bool tauf, hipStream_t st);
+hipError_t launch_patch(const SolveDesc *descs, const uint2 *tiles, int ntiles, int threads, int lanes,
+                        const int64_t *bases, int64_t step_off, const int *flips, int flip, int nk, bool fp32, bool tauf,
+                        hipStream_t st);
 // Per-cell relaxation factors omegaf[i][j] = exp(-dt / tau[i * nt + j]) from
 // a dense float64 tau field in device memory, or all equal to `uniform`
 // with tau NULL; stored in the solve's precision.

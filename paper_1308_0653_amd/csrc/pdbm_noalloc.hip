@@ -58,7 +58,7 @@ extern "C" int pdbm_create_noalloc(const pdbm_params *p, const pdbm_ic *ic, void
     int rc = pdbm_validate(p, ic, nullptr);
     if (rc) return rc;
     const int rows = rows_per_wave(*p);
-    const Layout L = layout_of(*p, rows);
+    const Layout L = layout_of(*p, rows, true);
     if (!state) {
         *state_bytes = L.state_total;
         return PDBM_OK;
@@ -85,7 +85,7 @@ extern "C" int pdbm_create_noalloc(const pdbm_params *p, const pdbm_ic *ic, void
         h->scratch_dev = dev;
     }
     h->st = (hipStream_t)stream;
-    rc = h->s.init(*p, ic, state, *state_bytes, rows, INT64_MAX, h->st, aux);
+    rc = h->s.init(*p, ic, state, *state_bytes, rows, INT64_MAX, true, h->st, aux);
     if (rc == PDBM_OK && hipStreamSynchronize(h->st) != hipSuccess) rc = fail(PDBM_EHIP, "initialisation failed");
     if (rc) {
         (void)hipStreamSynchronize(h->st);

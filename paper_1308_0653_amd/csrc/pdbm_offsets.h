@@ -281,24 +281,80 @@ __host__ __device__ inline ColumnOffsets column_offsets(int nr, const RowBytes &
 
 // The patches of the multi-step kernel for small grids (k_patch in
 // pdbm_patch.hip): workgroup `tile` of a solve owns rows x cols cells of the
-// grid and holds them with a halo of k rows and columns, PATCH_LANES lanes to
-// a cell, cells row by row.  Rows are clipped to the grid; with cols >= nt
+// grid and holds them with a halo of k rows and columns, `lanes` lanes to a
+// cell, cells row by row.  Rows are clipped to the grid; with cols >= nt
 // the patch holds the whole ring and has no column halo.
-// Patches of a grid; threads = 0: it has none and is marched by wavefronts
-// or, a single column, held by them.  Grids of fewer columns than octants
-// have them, whose neighbouring columns may differ by more than the one
-// octant the marching kernels take.
-inline PatchGeom patch_geom(int nr, int nt, int sector)
+// Shapes of patches a solve alone on the GPU chooses from (choose_patches):
+// the cells of a workgroup (rows x cols, halo included), its threads, lanes
+// per cell and halo k, and what a launch takes in ns, t0 + rounds c with 256
+// workgroups to a round, one per CU, fitted to grids of 100 x 100 to 400 x
+// 300 cells.
+struct PatchShape {
+    int rows, cols, k, threads, lanes, t0, c;
+};
+constexpr PatchShape PATCH_FP64[] = {
+    {16, 16, 2, 512, 2, 2500, 6400}, {16, 16, 3, 512, 2, 2800, 8400}, {16, 16, 4, 512, 2, 3200, 9200},
+    {10, 10, 3, 512, 4, 2800, 5000}};
+constexpr PatchShape PATCH_FP32[] = {
+    {16, 16, 2, 512, 2, 2700, 5000}, {16, 16, 3, 512, 2, 3000, 6100},  {16, 16, 4, 512, 2, 3000, 6800},
+    {12, 12, 4, 768, 4, 2800, 6000}, {19, 20, 3, 768, 2, 3000, 10500}};
+// One theta column: 128 rows, 24 steps.
+constexpr PatchShape PATCH_COLUMN = {128, 1, 24, 256, 2, 0, 0};
+// Rounds up to which patches are the faster: of the 16 x 16 shape with k = 2
+// (110 thousand cells), and of the column's (41 thousand rows).
+constexpr int PATCH_ROUNDS = 3, PATCH_COLUMN_ROUNDS = 2;
+
+inline PatchGeom patches_of(const PatchShape &s, int nr, int nt)
 {
     PatchGeom g{};
-    if (nt == 1 || marchable(nt, sector)) return g;
-    g.threads = PACK_PATCH_THREADS;
-    g.k = 2;
-    g.cols = nt;
-    g.rows = g.threads / PATCH_LANES / nt - 2 * g.k;
-    g.nbc = 1;
-    g.ntiles = (nr + g.rows - 1) / g.rows;
+    g.k = s.k;
+    g.threads = s.threads;
+    g.lanes = s.lanes;
+    if (nt <= s.cols) {  // the patch closes the ring and takes more rows instead
+        g.cols = nt;
+        g.rows = s.rows * s.cols / nt - 2 * s.k;
+    } else {
+        g.cols = s.cols - 2 * s.k;
+        g.rows = s.rows - 2 * s.k;
+    }
+    g.nbc = (nt + g.cols - 1) / g.cols;
+    g.ntiles = g.nbc * ((nr + g.rows - 1) / g.rows);
     return g;
+}
+// Patches of a grid (`alone` on the GPU, or in a pack); threads = 0: it has
+// none and is marched by wavefronts or, a single column, held by them.
+// - Fewer columns than octants: always, as neighbouring columns may then
+//   differ by more than the one octant the marching kernels take.
+// - Alone and too small to fill the GPU with marching wavefronts: a launch of
+//   those takes as long as one wavefront's chain of rows however few there
+//   are, 25 us in float64 and 20 us in float32 for two steps of up to 60
+//   thousand cells.  Patches took, per step, against marching: 64 x 64 2.6
+//   against 12.2 us (float64), 2.2 against 9.8 (float32); 100 x 100 3.2 / 12.6
+//   and 2.4 / 10.1; 300 x 130 6.4 / 13.2 and 4.5 / 10.4; 300 x 200 8.1 / 13.8
+//   and 6.3 / 10.4; 400 x 300 16.1 / 15.3 and 11.6 / 10.9 (marched).  A single
+//   column of 20000 rows: 2.0 against 3.6 us (float64), 1.6 against 2.6.
+inline PatchGeom patch_geom(int nr, int nt, int sector, bool fp32, bool alone)
+{
+    if (nt > 1 && !marchable(nt, sector)) return patches_of({8, 8, 2, PACK_PATCH_THREADS, PACK_PATCH_LANES, 0, 0}, nr, nt);
+    if (!alone) return PatchGeom{};
+    if (nt == 1) {
+        const PatchGeom g = patches_of(PATCH_COLUMN, nr, 1);
+        return g.ntiles <= 256 * PATCH_COLUMN_ROUNDS ? g : PatchGeom{};
+    }
+    const PatchShape *shapes = fp32 ? PATCH_FP32 : PATCH_FP64;
+    const int n = fp32 ? (int)(sizeof PATCH_FP32 / sizeof *PATCH_FP32) : (int)(sizeof PATCH_FP64 / sizeof *PATCH_FP64);
+    if (patches_of(shapes[0], nr, nt).ntiles > 256 * PATCH_ROUNDS) return PatchGeom{};
+    PatchGeom best{};
+    double least = 0.0;
+    for (int i = 0; i < n; ++i) {
+        const PatchGeom g = patches_of(shapes[i], nr, nt);
+        const double ns = (shapes[i].t0 + (double)((g.ntiles + 255) / 256) * shapes[i].c) / shapes[i].k;
+        if (i == 0 || ns < least) {
+            best = g;
+            least = ns;
+        }
+    }
+    return best;
 }
 struct PatchCell {
     int row, pc, ext;    // its row, physical column, column before wrapping

@@ -25,13 +25,13 @@ namespace {
 // disc centre that of the opposite direction), the turn of the directions
 // between columns of different octants and, on a patch that holds the whole
 // ring, its closing.
-template <typename real, bool TAUF, int NT>
+template <typename real, bool TAUF, int LPC, int NT>
 __global__ __launch_bounds__(NT, 1) void k_patch(const SolveDesc *descs, const uint2 *tiles, const int64_t *bases,
                                                  int64_t step_off, const int *flips, int flip, int nk_most)
 {
-    constexpr int LPC = PATCH_LANES;
-    static_assert(LPC == 4, "one ring per lane");
-    __shared__ real planes[2][8][NT];
+    static_assert(LPC == 2 || LPC == 4, "two or four lanes per cell");
+    constexpr int NS = 4 / LPC;  // rings per lane
+    __shared__ real planes[2][NS * 8][NT];
     __shared__ double lams[2][NT / LPC];
     __shared__ double parts[2][NT / 64][5];
     const int t = threadIdx.x, h = t & (LPC - 1);
@@ -45,7 +45,7 @@ __global__ __launch_bounds__(NT, 1) void k_patch(const SolveDesc *descs, const u
     const int64_t step0 = (bases ? bases[solve] : 0) + step_off;
     if (step0 >= dp->nsteps) return;
     const int nk = (int)min((int64_t)nk_most, dp->nsteps - step0);
-    const PatchGeom g{dp->patch.rows, dp->patch.cols, dp->patch.k, dp->patch.nbc, dp->patch.ntiles, NT};
+    const PatchGeom g{dp->patch.rows, dp->patch.cols, dp->patch.k, dp->patch.nbc, dp->patch.ntiles, NT, LPC};
     const int nr = dp->nr, nt = dp->nt;
     const int cur = (int)((step0 + ((flips ? flips[solve] : 0) ^ flip)) & 1);
     const __amdgpu_buffer_rsrc_t fin = rsrc_of(dp->f[cur]), fout = rsrc_of(dp->f[cur ^ 1]);
@@ -57,28 +57,31 @@ __global__ __launch_bounds__(NT, 1) void k_patch(const SolveDesc *descs, const u
     const uint32_t vrow = (uint32_t)c.row * b.row;
     const uint32_t vrest = vrow + (uint32_t)c.pc * (uint32_t)sizeof(real);
     const uint32_t vlam = (uint32_t)c.row * b.lrow + (uint32_t)c.pc * 8u;
-    const uint32_t vpair = vrow + 2u * (uint32_t)c.pc * (uint32_t)sizeof(real) + pair_in_row(b, 4 * h);
-    real x[8], x0;
+    const uint32_t vpair = vrow + 2u * (uint32_t)c.pc * (uint32_t)sizeof(real) + pair_in_row(b, 4 * NS * h);
+    real x[NS][8], x0;
     double lc;
 #pragma unroll
-    for (int dd = 0; dd < 4; ++dd) bload2(x[dd], x[dd + 4], fin, vpair, (uint32_t)dd * b.pair);
+    for (int i = 0; i < 4 * NS; ++i) bload2(x[i >> 2][i & 3], x[i >> 2][(i & 3) + 4], fin, vpair, (uint32_t)i * b.pair);
     bload(x0, fin, vrest, 0u);
     bload(lc, lin, vlam, 0u);
     const real om = omega_at<real, TAUF>(dp, (uint32_t)c.row * b.rest + (uint32_t)c.pc * (uint32_t)sizeof(real), 0u);
-    const double A0 = dp->A[4 * h], A1 = dp->A[4 * h + 1], A2 = dp->A[4 * h + 2], A3 = dp->A[4 * h + 3];
-    const real v = h == 0 ? (real)speed(1) : h == 1 ? (real)speed(2) : h == 2 ? (real)speed(3) : (real)speed(4);
+    // this ring's row of the moment inversion, read again in every step
+    __shared__ double Arow[16];
+    if (t < 16) Arow[t] = dp->A[t];
+    __syncthreads();
+    real v[NS];
+#pragma unroll
+    for (int kk = 0; kk < NS; ++kk) {
+        if constexpr (LPC == 4)
+            v[kk] = h == 0 ? (real)speed(1) : h == 1 ? (real)speed(2) : h == 2 ? (real)speed(3) : (real)speed(4);
+        else
+            v[kk] = h == 0 ? (real)speed(1 + kk) : (real)speed(3 + kk);
+    }
 
     const double2 cs = dp->cs[c.pc];
     const double ri = dp->r_min + ((double)c.row + 0.5) * dp->dr;
     const double ktd = dp->dt_dth / ri;
     const real kr = (real)dp->dt_dr, kt = (real)ktd;
-    const Polar<real> V(cs);
-    real acr[4], act[4];
-#pragma unroll
-    for (int dd = 0; dd < 4; ++dd) {
-        acr[dd] = fabs(V.r[dd]) * kr;
-        act[dd] = fabs(V.t[dd]) * kt;
-    }
     // elements of the upwind neighbours: below for directions 0, 1, 2 and 7
     // (from this many planes on), above for 3 to 6, left and right by pair
     const PatchNear near = patch_near(c, dp->inv2, nt, dp->sector, t / LPC);
@@ -102,23 +105,26 @@ __global__ __launch_bounds__(NT, 1) void k_patch(const SolveDesc *descs, const u
         const bool publish = __builtin_amdgcn_ballot_w64(c.dist >= j + spare) != 0;
         const bool update = __builtin_amdgcn_ballot_w64(c.dist > j + spare) != 0;
         Cell<real> C;
-        real Fk = 0, F0 = 0;
+        real Fk[NS] = {}, F0 = 0;
         if (publish) {
 #pragma unroll
-            for (int d = 0; d < 8; ++d) P[d * NT + t] = x[d];
-            Lm[t / LPC] = lc;  // the same from a cell's four lanes
+            for (int i = 0; i < 8 * NS; ++i) P[i * NT + t] = x[i >> 3][i & 7];
+            Lm[t / LPC] = lc;  // the same from each of a cell's lanes
         }
         if (update) {
-            // moments: this ring's part, then the other lanes' added
-            real ring, mx, my, en;
-            ring_moments(x, x + 4, v, ring, mx, my, en);
-            C.rho = cell_sum<LPC>(h == 0 ? x0 + ring : ring);
-            C.e = cell_sum<LPC>(en);
-            C.init_state(dp, cell_sum<LPC>(mx), cell_sum<LPC>(my), lc, om);
+            real jx, jy;
+            cell_moments<LPC>(x, x0, v, h, C.rho, jx, jy, C.e);
+            C.init_state(dp, jx, jy, lc, om);
             const double T2 = C.Td * C.Td, T3 = T2 * C.Td, T4 = T2 * T2;
-            const double F = fma(A3, T4, fma(A2, T3, fma(A1, T2, A0 * C.Td)));
-            Fk = (real)F;
-            F0 = (real)fma(-8.0, cell_sum<LPC>(F), 1.0);
+            double sum = 0.0;
+#pragma unroll
+            for (int kk = 0; kk < NS; ++kk) {
+                const double *A = Arow + 4 * (NS * h + kk);
+                const double F = fma(A[3], T4, fma(A[2], T3, fma(A[1], T2, A[0] * C.Td)));
+                Fk[kk] = (real)F;
+                sum = kk > 0 ? sum + F : F;
+            }
+            F0 = (real)fma(-8.0, cell_sum<LPC>(sum), 1.0);
         }
         if (rec) {
             double red[5] = {0, 0, 0, 0, 0};
@@ -142,22 +148,34 @@ __global__ __launch_bounds__(NT, 1) void k_patch(const SolveDesc *descs, const u
             }
         }
         if (update) {
-            const real rF = C.rho * Fk;
-            const real rA = rF * C.factor(v), rB = rF * C.Bz;
-            real o[8];
+            // worked out again in every step, which takes fewer registers
+            double2 a = cs;
+            asm volatile("" : "+v"(a.x), "+v"(a.y));
+            const Polar<real> V(a);
+            real acr[4], act[4];
 #pragma unroll
             for (int dd = 0; dd < 4; ++dd) {
-                real E, O;
-                pair_coll(C.EP, v * C.EP.w(dd), rA, rB, E, O);
-                const real s = C.stay(v, acr[dd] + act[dd]);
-                const real rad0 = P[dd * NT + (dd < 3 ? low : high)];
-                const real rad4 = P[(dd + 4) * NT + (dd < 3 ? high : low7)];
-                const real azi0 = P[dd > 0 ? left[dd] : right[dd]], azi4 = P[dd > 0 ? right[dd] : left[dd]];
-                o[dd] = dir_new(E + O, s, x[dd], v, acr[dd], act[dd], rad0, azi0);
-                o[dd + 4] = dir_new(E - O, s, x[dd + 4], v, acr[dd], act[dd], rad4, azi4);
+                acr[dd] = fabs(V.r[dd]) * kr;
+                act[dd] = fabs(V.t[dd]) * kt;
             }
 #pragma unroll
-            for (int d = 0; d < 8; ++d) x[d] = o[d];
+            for (int kk = 0; kk < NS; ++kk) {
+                const real *Pk = P + kk * 8 * NT;
+                const real rF = C.rho * Fk[kk];
+                const real rA = rF * C.factor(v[kk]), rB = rF * C.Bz;
+#pragma unroll
+                for (int dd = 0; dd < 4; ++dd) {
+                    real E, O;
+                    pair_coll(C.EP, v[kk] * C.EP.w(dd), rA, rB, E, O);
+                    const real s = C.stay(v[kk], acr[dd] + act[dd]);
+                    const real rad0 = Pk[dd * NT + (dd < 3 ? low : high)];
+                    const real rad4 = Pk[(dd + 4) * NT + (dd < 3 ? high : low7)];
+                    const real azi0 = Pk[dd > 0 ? left[dd] : right[dd]], azi4 = Pk[dd > 0 ? right[dd] : left[dd]];
+                    const real o0 = dir_new(E + O, s, x[kk][dd], v[kk], acr[dd], act[dd], rad0, azi0);
+                    x[kk][dd + 4] = dir_new(E - O, s, x[kk][dd + 4], v[kk], acr[dd], act[dd], rad4, azi4);
+                    x[kk][dd] = o0;
+                }
+            }
             x0 = C.rest(x0, F0);
             // lambda: closed-form Cochran step, then upwind by own-cell u
             const double urp = C.ur(cs), utp = C.ut(cs);
@@ -169,7 +187,8 @@ __global__ __launch_bounds__(NT, 1) void k_patch(const SolveDesc *descs, const u
 
     if (c.own) {
 #pragma unroll
-        for (int dd = 0; dd < 4; ++dd) bstore2(x[dd], x[dd + 4], fout, vpair, (uint32_t)dd * b.pair);
+        for (int i = 0; i < 4 * NS; ++i)
+            bstore2(x[i >> 2][i & 3], x[i >> 2][(i & 3) + 4], fout, vpair, (uint32_t)i * b.pair);
         if (h == 0) {
             bstore(x0, fout, vrest, 0u);
             bstore(lc, lout, vlam, 0u);
@@ -179,17 +198,32 @@ __global__ __launch_bounds__(NT, 1) void k_patch(const SolveDesc *descs, const u
 
 }  // namespace
 
-hipError_t launch_patch(const SolveDesc *descs, const uint2 *tiles, int ntiles, int threads, const int64_t *bases,
-                        int64_t step_off, const int *flips, int flip, int nk, bool fp32, bool tauf, hipStream_t st)
+// A kernel per precision, tau field, lanes per cell and workgroup size.
+template <typename real, bool TAUF, int LPC>
+static void launch_k_patch(int ntiles, int threads, hipStream_t st, const SolveDesc *descs, const uint2 *tiles,
+                           const int64_t *bases, int64_t step_off, const int *flips, int flip, int nk)
+{
+    // (in float64, two lanes to a cell in workgroups of 768 would need 200 KB of LDS)
+    constexpr int MOST = LPC == 4 || sizeof(real) == 4 ? 768 : 512;
+    auto *fn = threads == 256   ? &k_patch<real, TAUF, LPC, 256>
+               : threads == 512 ? &k_patch<real, TAUF, LPC, 512>
+                                : &k_patch<real, TAUF, LPC, MOST>;
+    hipLaunchKernelGGL(fn, dim3(ntiles), dim3(threads), 0, st, descs, tiles, bases, step_off, flips, flip, nk);
+}
+
+hipError_t launch_patch(const SolveDesc *descs, const uint2 *tiles, int ntiles, int threads, int lanes,
+                        const int64_t *bases, int64_t step_off, const int *flips, int flip, int nk, bool fp32, bool tauf,
+                        hipStream_t st)
 {
     if (ntiles == 0 || nk <= 0) return hipSuccess;
-    using L = void (*)(const SolveDesc *, const uint2 *, const int64_t *, int64_t, const int *, int, int);
-    // [threads / 512][fp32][tauf]
-    static const L table[2][2][2] = {
-        {{k_patch<double, false, 256>, k_patch<double, true, 256>}, {k_patch<float, false, 256>, k_patch<float, true, 256>}},
-        {{k_patch<double, false, 512>, k_patch<double, true, 512>}, {k_patch<float, false, 512>, k_patch<float, true, 512>}}};
-    hipLaunchKernelGGL(table[threads / 512][fp32][tauf], dim3(ntiles), dim3(threads), 0, st, descs, tiles, bases,
-                       step_off, flips, flip, nk);
+    using L = void (*)(int, int, hipStream_t, const SolveDesc *, const uint2 *, const int64_t *, int64_t, const int *, int,
+                       int);
+    // [lanes / 4][fp32][tauf]
+    static const L table[2][2][2] = {{{launch_k_patch<double, false, 2>, launch_k_patch<double, true, 2>},
+                                      {launch_k_patch<float, false, 2>, launch_k_patch<float, true, 2>}},
+                                     {{launch_k_patch<double, false, 4>, launch_k_patch<double, true, 4>},
+                                      {launch_k_patch<float, false, 4>, launch_k_patch<float, true, 4>}}};
+    table[lanes / 4][fp32][tauf](ntiles, threads, st, descs, tiles, bases, step_off, flips, flip, nk);
     return hipGetLastError();
 }
 

@@ -39,7 +39,7 @@ using namespace pdbm;
 // wavefronts hold COL_W rows whatever this is.
 int pdbm::batch_rows(const pdbm_params &p)
 {
-    if (patch_geom(p.nr, p.ntheta, p.sector).threads > 0) return PATCHES;
+    if (patches(p, false).threads > 0) return PATCHES;
     static const int env = [] {
         const char *e = std::getenv("PDBM_BATCH_ROWS");
         return e ? std::atoi(e) : 0;
@@ -244,7 +244,7 @@ class Pack {
                 if (k == COLUMNS)
                     e = launch_column(ddescs, dtiles + c.t0, c.nt, dbases, done, dflips, pf, nk, fp32, false, st);
                 else
-                    e = launch_patch(ddescs, dtiles + c.t0, c.nt, PACK_PATCH_THREADS, dbases, done, dflips, pf, nk,
+                    e = launch_patch(ddescs, dtiles + c.t0, c.nt, PACK_PATCH_THREADS, PACK_PATCH_LANES, dbases, done, dflips, pf, nk,
                                      fp32, false, st);
                 pf ^= (nk + 1) & 1;
                 done += nk;
@@ -342,7 +342,7 @@ int pdbm_batch_create(int32_t n, const pdbm_params *ps, const pdbm_ic *ics, int3
     b->pack.fp32 = ps[0].precision == PDBM_FP32;
     for (int i = 0; i < n && rc == PDBM_OK; ++i) {
         b->solves.emplace_back(new Solve);
-        rc = b->solves.back()->init(ps[i], ics ? ics + i : nullptr, nullptr, 0, batch_rows(ps[i]), INT64_MAX, b->st);
+        rc = b->solves.back()->init(ps[i], ics ? ics + i : nullptr, nullptr, 0, batch_rows(ps[i]), INT64_MAX, false, b->st);
         if (rc == PDBM_OK && hipStreamSynchronize(b->st) != hipSuccess) rc = fail(PDBM_EHIP, "initialisation failed");
         b->pack.members.push_back(b->solves.back().get());
     }
@@ -527,7 +527,7 @@ int pdbm_server::admit_and_step(std::vector<Request *> &admitted)
 {
     for (Request *r : admitted) {
         r->solve.reset(new Solve);
-        int rc = r->solve->init(r->p, &r->ic, nullptr, 0, batch_rows(r->p), r->nsteps, st);
+        int rc = r->solve->init(r->p, &r->ic, nullptr, 0, batch_rows(r->p), r->nsteps, false, st);
         if (rc == PDBM_OK && hipStreamSynchronize(st) != hipSuccess) rc = PDBM_EHIP;
         if (rc) {
             retire(r, rc);
@@ -636,7 +636,7 @@ int pdbm_submit(pdbm_server *s, const pdbm_params *p, const pdbm_ic *ic, int64_t
     r->ic = *ic;
     r->nsteps = nsteps;
     r->flags = flags;
-    r->bytes = layout_of(*p, batch_rows(*p)).total;
+    r->bytes = layout_of(*p, batch_rows(*p), false).total;
     if (r->bytes > s->led.cap) return fail(PDBM_ENOMEM, "request larger than the server's memory cap");
     std::lock_guard<std::mutex> g(s->mu);
     if (s->stop) return fail(PDBM_EINVAL, "server is shutting down");

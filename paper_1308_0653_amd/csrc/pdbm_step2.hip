@@ -253,7 +253,6 @@ __device__ __forceinline__ void edge_cells(const Strip<real, MIXED> &S, int stri
     const double2 cs = dp->cs[o.pc];
     const Polar<real> V(cs);
 
-    // moments: this lane's rings, then the other lanes' added
     real vk[NS];  // this lane's speeds
 #pragma unroll
     for (int kk = 0; kk < NS; ++kk) {
@@ -262,20 +261,16 @@ __device__ __forceinline__ void edge_cells(const Strip<real, MIXED> &S, int stri
         else
             vk[kk] = h == 0 ? (real)speed(1) : h == 1 ? (real)speed(2) : h == 2 ? (real)speed(3) : (real)speed(4);
     }
-    real rho, jx, jy, en;
+    real xr[NS][8];
 #pragma unroll
-    for (int kk = 0; kk < NS; ++kk) {
-        real sum, mx, my, me;
-        ring_moments(x + 4 * kk, x + NP + 4 * kk, vk[kk], sum, mx, my, me);
-        rho = kk > 0 ? rho + sum : h == 0 ? x0 + sum : sum;
-        jx = kk > 0 ? jx + mx : mx;
-        jy = kk > 0 ? jy + my : my;
-        en = kk > 0 ? en + me : me;
+    for (int i = 0; i < NP; ++i) {
+        xr[i >> 2][i & 3] = x[i];
+        xr[i >> 2][(i & 3) + 4] = x[i + NP];
     }
     Cell<real> C;
-    C.rho = cell_sum<LPC>(rho);
-    C.e = cell_sum<LPC>(en);
-    C.init_moments(dp, cell_sum<LPC>(jx), cell_sum<LPC>(jy), lc, omega_at<real, TAUF>(dp, o.om, 0u));
+    real jx, jy;
+    cell_moments<LPC>(xr, x0, vk, h, C.rho, jx, jy, C.e);
+    C.init_moments(dp, jx, jy, lc, omega_at<real, TAUF>(dp, o.om, 0u));
 
     const double ri = dp->r_min + ((double)r + 0.5) * dp->dr;
     const double ktd = dp->dt_dth / ri;

@@ -67,7 +67,7 @@ static void strips(int nt, int s, int esz)
 static void patches(int nr, int nt, int s, const PatchGeom &g)
 {
     std::vector<int> owned((size_t)nr * nt, 0);
-    const int cells = g.threads / PATCH_LANES;
+    const int cells = g.threads / g.lanes;
     for (int tile = 0; tile < g.ntiles; ++tile) {
         std::vector<PatchCell> P;
         for (int i = 0; i < cells; ++i) P.push_back(patch_cell(g, nr, nt, 0.5 / nt, tile, i));
@@ -114,20 +114,34 @@ int main()
                 if (marchable(nt, s)) strips(nt, s, esz);
         for (int nr : {1, 2, 5, 17, 64, 130})
             for (int nt : {1, 2, 3, 4, 5, 7, 8, 17, 33, 64, 65, 130}) {
-                const PatchGeom g = patch_geom(nr, nt, s);
-                if (g.threads) patches(nr, nt, s, g);
-                else check(marchable(nt, s) || nt == 1, "every grid has a kernel", nr, nt, s, 0);
+                for (int form = 0; form < 4; ++form) {
+                    const PatchGeom g = patch_geom(nr, nt, s, form & 1, form & 2);
+                    if (g.threads) patches(nr, nt, s, g);
+                    else check(marchable(nt, s) || nt == 1, "every grid has a kernel", nr, nt, s, form);
+                }
                 // and patches of other shapes: cut both ways, closing the ring, one cell
                 for (int rows : {1, 4, 9})
                     for (int cols : {1, 4, 8, nt})
                         for (int k : {1, 2, 3}) {
-                            PatchGeom o{rows, cols < nt ? cols : nt, k, 0, 0, 512};
+                            PatchGeom o{rows, cols < nt ? cols : nt, k, 0, 0, 512, 4};
                             o.nbc = (nt + o.cols - 1) / o.cols;
                             o.ntiles = o.nbc * ((nr + rows - 1) / rows);
                             const int ncol = o.cols >= nt ? nt : o.cols + 2 * k;
-                            if ((rows + 2 * k) * ncol * PATCH_LANES <= o.threads) patches(nr, nt, s, o);
+                            if ((rows + 2 * k) * ncol * o.lanes <= o.threads) patches(nr, nt, s, o);
                         }
             }
+    }
+    // every shape of the rule, on grids at the ends of its ranges
+    for (bool fp32 : {false, true})
+        for (int nr : {1, 9, 64, 100, 300, 700})
+            for (int nt : {8, 15, 16, 17, 20, 64, 130, 200, 333}) {
+                const PatchGeom g = patch_geom(nr, nt, 8, fp32, true);
+                if (g.threads) patches(nr, nt, 8, g);
+            }
+    for (int nr : {1, 79, 80, 81, 20000, 40960, 40961}) {
+        const PatchGeom g = patch_geom(nr, 1, 8, false, true);
+        check((g.threads != 0) == (nr <= 40960), "column limit", nr, g.threads, 0, 0);
+        if (g.threads) patches(nr, 1, 8, g);
     }
     std::printf("%lld checks, %lld failed\n", n, bad);
     return bad ? 1 : 0;

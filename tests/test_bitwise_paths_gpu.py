@@ -5,7 +5,8 @@ Each case is run by the launches chosen for it, by other row blocks
 counts), the environment being read once per process, and every value of f
 and lambda must come out bitwise equal.  The grids: octants that are whole
 strips, cut by strips and narrower than one, periodic images past the last
-column, sectors, a disc, fewer columns than octants, a single column."""
+column, sectors, a disc, fewer columns than octants, single columns, and one
+grid for each shape of patch."""
 import os
 import subprocess
 import sys
@@ -21,7 +22,8 @@ pytestmark = pytest.mark.gpu
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 GRIDS = [(37, 512, 8), (20, 200, 8), (21, 65, 8), (9, 20, 8), (18, 8, 8), (11, 5, 8), (3, 2, 8), (24, 130, 3),
-         (12, 64, 1), (17, 128, 2), (40, 1, 8), (33, 1, 1)]
+         (12, 64, 1), (17, 128, 2), (40, 1, 8), (33, 1, 1), (500, 1, 2), (64, 64, 8), (100, 100, 8), (200, 180, 8),
+         (300, 130, 8)]
 DISCS = [(14, 40, 4), (19, 24, 1), (10, 3, 4)]
 VARIANTS = [{}, {"PDBM_ROWS_PER_WAVE": "3"}, {"PDBM_ROWS_PER_WAVE": "16"}, {"PDBM_FUSE": "0"}]
 

@@ -37,13 +37,13 @@
  * Environment (read once per process; for measurement and tuning)
  *   PDBM_FUSE=0            every launch (single solves, batches, servers)
  *                          takes a single step.
- *   PDBM_ROWS_PER_WAVE=n   r rows per wavefront of single solves, which then
+ *   PDBM_ROWS_PER_WAVE=n   n rows per wavefront of single solves, which then
  *                          are not stepped on patches (except grids of fewer
  *                          columns than octants); above 16 disables two-step
  *                          launches.
- *   PDBM_BATCH_ROWS=n      r rows per wavefront of packed grids of more
- *                          than one column (16); above 16 disables
- *                          two-step launches.
+ *   PDBM_BATCH_ROWS=n      n rows per wavefront of packed grids of more
+ *                          than one column (else 2 to 16, by what fills the
+ *                          device); above 16 disables two-step launches.
  */
 #ifndef PDBM_H
 #define PDBM_H

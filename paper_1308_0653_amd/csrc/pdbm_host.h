@@ -38,8 +38,12 @@ struct Layout {
 // stepped on patches (patch_geom).
 constexpr int PATCHES = 0;
 Layout layout_of(const pdbm_params &p, int rows, bool alone);
-// Rows per wavefront of a packed solve, or PATCHES.
+// Rows per wavefront a packed solve starts with, or PATCHES (Pack::rebuild
+// chooses them anew with every change of the pack, between FEWEST_ROWS and
+// FUSE_ROWS, unless PDBM_BATCH_ROWS fixes them).
+constexpr int FEWEST_ROWS = 2;
 int batch_rows(const pdbm_params &p);
+int batch_rows_env();
 // Patches of a solve that rows_per_wave (alone) or batch_rows gives them.
 PatchGeom patches(const pdbm_params &p, bool alone);
 class Solve;
@@ -88,7 +92,16 @@ class Solve {
     // Whether its launches step patches of the grid, up to geom.k steps each.
     bool patched() const { return hd.patch.threads > 0; }
     int patch_steps() const;  // ... of this many steps at most
-    int waves() const { return L.nwaves; }
+    int waves() const { return hd.nwaves; }
+    // Marches blocks of `rows` rows from now on (a member of a pack).  A
+    // solve that makes drift records keeps the blocks it has memory for the
+    // partial sums of.
+    void set_rows(int rows)
+    {
+        hd.rows = p.diag_every > 0 ? L.rows : rows;
+        hd.nwaves = waves_at(rows);
+    }
+    int waves_at(int rows) const { return solve_waves(p.nr, p.ntheta, p.diag_every > 0 ? L.rows : rows); }
     bool mixed() const { return !whole_octants(p.ntheta, p.sector); }
     bool tauf() const { return hd.omegaf != nullptr; }  // relaxes with a per-cell tau
     // Sets the step count on host and device (stream must be idle).

@@ -15,6 +15,7 @@
 #include <algorithm>
 #include <chrono>
 #include <climits>
+#include <cmath>
 #include <condition_variable>
 #include <cstring>
 #include <deque>
@@ -33,19 +34,19 @@ using namespace pdbm;
 
 #define HIPCHK PDBM_HIPCHK
 
-// Rows per wavefront of a packed solve of more than one column: FUSE_ROWS,
-// the longest blocks the two-step kernel takes, which recompute the fewest
-// rows; PDBM_BATCH_ROWS overrides it (tuning).  A single column's
-// wavefronts hold COL_W rows whatever this is.
-int pdbm::batch_rows(const pdbm_params &p)
+int pdbm::batch_rows_env()
 {
-    if (patches(p, false).threads > 0) return PATCHES;
     static const int env = [] {
         const char *e = std::getenv("PDBM_BATCH_ROWS");
         return e ? std::atoi(e) : 0;
     }();
-    if (env > 0) return env;
-    return FUSE_ROWS;
+    return env;
+}
+
+int pdbm::batch_rows(const pdbm_params &p)
+{
+    if (patches(p, false).threads > 0) return PATCHES;
+    return batch_rows_env() > 0 ? batch_rows_env() : FUSE_ROWS;
 }
 
 namespace {
@@ -72,6 +73,7 @@ class Pack {
         drop_graph();
         mixed = false;
         pairs = true;
+        const int rows = row_block();
         std::vector<SolveDesc> descs;
         std::vector<uint2> tiles;
         bases_host.clear();
@@ -81,6 +83,7 @@ class Pack {
             part[k].t0 = (int)tiles.size();
             for (Solve *m : members) {
                 if (kind_of(*m) != k) continue;
+                if (k == WIDE) m->set_rows(rows);
                 const unsigned i = (unsigned)descs.size();
                 descs.push_back(m->hd);
                 bases_host.push_back(m->step);
@@ -179,6 +182,46 @@ class Pack {
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     int graph_steps = 0;
+
+    // Rows per wavefront of the marched members.  A full GPU wants the
+    // longest blocks the two-step kernel takes (the fewest rows computed and
+    // read twice); with fewer wavefronts than the GPU holds at once a launch
+    // takes as long as one of them, so blocks are shortened until they fill
+    // it.  A block of r rows takes a wavefront about 2 r + 5 rows' time (both
+    // steps' rows, the two beside the block, its start); `rounds` is how many
+    // such times a launch takes, from packs of 1 to 40 solves.  A launch of
+    // one 300 x 380 solve took 83 us (float32) and 114 us (float64) in blocks
+    // of 16 rows and takes 23 and 32; four of 500 x 256 91 and 122, now 50
+    // and 83; ten 144 and 246, now 108 and 193; from 16 on the blocks stay
+    // at 16 rows.
+    int row_block() const
+    {
+        if (batch_rows_env() > 0) return batch_rows_env();
+        int best = FUSE_ROWS;
+        double least = 0.0;
+        for (int r = FUSE_ROWS; r >= FEWEST_ROWS; --r) {
+            double waves = 0.0;
+            for (const Solve *m : members)
+                if (kind_of(*m) == WIDE) waves += m->waves_at(r);
+            const double t = (2 * r + 5) * rounds(waves);
+            if (r == FUSE_ROWS || t < least) {
+                best = r;
+                least = t;
+            }
+        }
+        return best;
+    }
+    double rounds(double waves) const
+    {
+        const double simds = 1024.0;
+        if (fp32) {  // two wavefronts per SIMD; one runs faster alone
+            if (waves <= simds) return 0.62;
+            const double x = waves / (2.0 * simds);
+            return x <= 1.0 ? 1.0 : x + 0.4 * (std::ceil(x) - x);
+        }
+        const double x = waves / simds;
+        return x <= 1.0 ? 1.0 : x + 0.6 * (std::ceil(x) - x);
+    }
 
     static int grow(void **p, size_t &cap, size_t need)
     {

@@ -9,13 +9,19 @@ namespace {
 // ------------------------------------------------------ two steps per pass --
 // Steps s and s + 1 in one pass over f.  Stage A computes the state after
 // step s (g) one row ahead of stage B, which computes the state after step
-// s + 1 from g and stores it: g never leaves the wavefront.  Stage B's
+// s + 1 from g and stores it: g never leaves the workgroup.  Stage B's
 // azimuthal neighbours of lanes 0 and 63 are g at the columns bordering the
-// strip; the wavefront computes those cells itself at the start
-// (edge_cells), as the adjacent strips do in their own stage A.  A block of
-// R rows runs stage A on R + 2 rows and reads R + 4 rows of f, so each f
-// value is read about 1.3 times (block boundaries, edge-cell gathers) and
-// written once per two steps.
+// strip.  Where the strip beside is marched by another wavefront of the
+// workgroup (consecutive tiles are strips side by side), that wavefront hands
+// them on through LDS, row by row, as its stage A makes them (Beside);
+// at the workgroup's ends the wavefront computes those cells itself at the
+// start (edge_cells).  With every wavefront computing its own, their gathers
+// touched half of f's cache lines a second time in float32 (a quarter in
+// float64), and 1024 x 1024 launches took 90 us (135 in float64); now 80 and
+// 130, as with no edge cells at all but for 2 us.  A barrier per row in place
+// of the counts took 145 us in float64, where a SIMD has no other wavefront
+// to run.  A block of R rows runs stage A on R + 2 rows and reads R + 4 rows
+// of f; each value is written once per two steps.
 
 // Azimuthal neighbours of lanes 0 and 63 in LDS, read back by every lane: of
 // each opposite pair of directions the member that comes from the left
@@ -188,7 +194,8 @@ __device__ __forceinline__ void stage_row(const Strip<real, MIXED> &S, int ir, r
 
 // The intermediate state at the columns bordering strip `strip`, c0 - 1
 // (left) and c0 + 64 (right) as periodic images, for the rows [i0, i1) of the
-// block.  LPC lanes (2, or 4 for blocks of at most 8 rows) take one cell:
+// block, on both sides or on side `only` (every lane then works on that one:
+// no more cells are gathered).  LPC lanes (2, or 4 for blocks of at most 8 rows) take one cell:
 // lane 32 side + LPC e + h takes row i0 + e of its side and the speeds
 // 4 h / LPC + 1 .. 4 (h + 1) / LPC (h = 0 also the rest particle).  Of each
 // opposite pair of directions only the one that lane 0 (left side) or lane
@@ -200,13 +207,13 @@ __device__ __forceinline__ void stage_row(const Strip<real, MIXED> &S, int ir, r
 // A of the strip owning the column does, to the same bits.
 template <typename real, bool TAUF, int LPC, bool MIXED>
 __device__ __forceinline__ void edge_cells(const Strip<real, MIXED> &S, int strip, int i0, int i1,
-                                           real (*ef)[FUSE_ROWS][16], double (*el)[FUSE_ROWS])
+                                           real (*ef)[FUSE_ROWS][16], double (*el)[FUSE_ROWS], int only)
 {
     static_assert(LPC == 2 || LPC == 4, "two or four lanes per cell");
     constexpr int NP = 16 / LPC;  // pairs per lane
     constexpr int NS = 4 / LPC;   // speeds per lane
     const DescPtr dp = S.dp;
-    const int lane = S.lane, side = lane >> 5, e = (lane & 31) / LPC, h = lane & (LPC - 1);
+    const int lane = S.lane, side = only < 0 ? lane >> 5 : only, e = (lane & 31) / LPC, h = lane & (LPC - 1);
     const int count = i1 - i0;
     const int r = i0 + min(e, count - 1);  // lanes past the block repeat its last row
     const RowBytes rb{S.row_bytes, S.lrow_bytes, S.rest_bytes, S.pair_bytes};
@@ -343,6 +350,26 @@ __device__ __forceinline__ void swap_rows(float (&a)[NQ], float (&b)[NQ])
     asm volatile("s_nop 1");
 }
 
+// The wavefronts of the workgroup that march the strips beside this one's (w)
+// over the same rows: to the left and to the right (-1: in another
+// workgroup), and how many rows of g each wavefront has handed on.
+struct Beside {
+    int w, l, r;
+    int *done;
+};
+
+// Waits until a wavefront beside has handed on `rows` rows.  It is in the
+// same workgroup, so resident, and waits itself only for rows before that.
+// LDS carries out a wavefront's operations in order, so what was written
+// before the count is there once the count is.
+__device__ __forceinline__ void await(int &done, int rows)
+{
+    while (__builtin_amdgcn_readfirstlane(
+               __hip_atomic_load(&done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) < rows)
+        __builtin_amdgcn_s_sleep(1);
+    wave_lds_sync();
+}
+
 // Work of one wavefront of the two-step kernel: strip `strip`, rows [i0, i1)
 // (at most FUSE_ROWS), marched outward.  Positions p count rows from the
 // first row of the block (p = 0); stage A runs on positions -1 .. R where
@@ -351,13 +378,14 @@ __device__ __forceinline__ void swap_rows(float (&a)[NQ], float (&b)[NQ])
 // by both at once, took 1 % less time in float64 and 3 % less in float32, but
 // need the upwind sides selected at run time.)  LDS per wavefront: the
 // compact rows behind of f (fb) and of g (gb), the full row of g just
-// computed (ga), the edge cells (ef, el) and the gathered halo values of
-// stage A's row (hb, hbl).
+// computed (ga), g at the columns beside the strip (of efs and els, which the
+// wavefronts beside write too) and the gathered halo values of stage A's row
+// (hb, hbl).
 template <typename real, bool TAUF, bool MIXED, class Diag>
 __device__ __forceinline__ void march2(DescPtr dp, const StepBufs &bufs, int strip, int i0, int i1,
-                                       real (*fb)[64], real (*gb)[64], real (*ga)[64], real (*ef)[FUSE_ROWS][16],
-                                       double (*el)[FUSE_ROWS], real *hb, double *hbl, Diag &DA, Diag &DB,
-                                       bool diagA, bool diagB)
+                                       real (*fb)[64], real (*gb)[64], real (*ga)[64],
+                                       real (*efs)[2][FUSE_ROWS][16], double (*els)[2][FUSE_ROWS], real *hb,
+                                       double *hbl, const Beside &W, Diag &DA, Diag &DB, bool diagA, bool diagB)
 {
     const Strip<real, MIXED> S(dp, bufs, strip);
     const int lane = S.lane;
@@ -411,10 +439,28 @@ __device__ __forceinline__ void march2(DescPtr dp, const StepBufs &bufs, int str
     // 2 x 8 cells keep all 64 lanes busy (93.9 against 95.3 us per launch);
     // float64 keeps two (its 16-row blocks fill the lanes with two; with
     // both forms compiled into its kernel it ran 2 us per launch slower)
-    if (sizeof(real) == 4 && i1 - i0 <= 8)
-        edge_cells<real, TAUF, 4, MIXED>(S, strip, i0, i1, ef, el);
-    else
-        edge_cells<real, TAUF, 2, MIXED>(S, strip, i0, i1, ef, el);
+    real (*ef)[FUSE_ROWS][16] = efs[W.w];
+    double (*el)[FUSE_ROWS] = els[W.w];
+    const bool hasl = W.l >= 0, hasr = W.r >= 0;
+    if (!(hasl && hasr)) {
+        const int only = hasl ? 1 : hasr ? 0 : -1;
+        if (sizeof(real) == 4 && i1 - i0 <= 8)
+            edge_cells<real, TAUF, 4, MIXED>(S, strip, i0, i1, ef, el, only);
+        else
+            edge_cells<real, TAUF, 2, MIXED>(S, strip, i0, i1, ef, el, only);
+    }
+    // What this lane hands on of each row of g: lanes 0 to 15 the 16 values
+    // that the strip to the left takes from lane 0, lanes 16 to 31 those the
+    // strip to the right takes from lane 63, in the order and the frame of
+    // edge_cells (the turn is the opposite of this strip's to its neighbour),
+    // and lanes 0 and 63 their lambda.  Lanes with nothing to hand on write to
+    // their places in hb and hbl, which the next stage A fills anew.
+    const int hl = lane >> 4 & 1, hdd = lane & 3;
+    const int hdir = ((hl ? left_dir(hdd) : right_dir(hdd)) - (hl ? S.turns.tc[1] : S.turns.tc[0])) & 7;
+    const real *hsrc = &ga[1 + 8 * (lane >> 2 & 3) + hdir][hl ? 63 : 0];
+    const bool hands = lane < 32 && (hl ? hasr : hasl), handsl = lane == 0 ? hasl : lane == 63 && hasr;
+    real *hdst = hands ? &efs[hl ? W.r : W.l][hl ? 0 : 1][0][lane & 15] : hb + lane;
+    double *hdstl = handsl ? &els[lane ? W.r : W.l][lane ? 0 : 1][0] : hbl + lane;
     // TAUF: exp(-dt/tau) of stage A's row (oa), loaded a pass ahead, and of
     // stage B's (ob), the row stage A had a pass before (loaded at the point
     // of use, the field cost 7.2 us per float64 launch and 4.2 us per float32
@@ -450,6 +496,14 @@ __device__ __forceinline__ void march2(DescPtr dp, const StepBufs &bufs, int str
             for (int q = 0; q < NQ; ++q) gc[q] = ga[q][lane];
             gln = glc;
         }
+        // hand the row's ends on
+        if ((hasl || hasr) && p >= 0 && p < count) {
+            wave_lds_sync();
+            hdst[hands ? p * 16 : 0] = *hsrc;
+            hdstl[handsl ? p : 0] = gln;
+            wave_lds_sync();
+            __hip_atomic_store(&W.done[W.w], p + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
         // f at position p + 2 (the row ahead of the next stage A) replaces f(p)
         if (p + 1 < count || (p + 1 == count && vhi)) row_or_ghost(S, ir + 2, fc, lx, fn, ln);
         if (p + 2 < count || (p + 2 == count && vhi)) S.load_upwind_halo(ir + 2, hx.h, hx.hl);
@@ -466,6 +520,8 @@ __device__ __forceinline__ void march2(DescPtr dp, const StepBufs &bufs, int str
             fill_behind(gb, [&](int q) { return ga[q][lane]; }, dp->disc, lane);
             glc = gln;
         } else if (p > 0) {
+            if (hasl) await(W.done[W.l], p);
+            if (hasr) await(W.done[W.r], p);
             const Halo<real> H{ef[0][p - 1], ef[1][p - 1], el[0][p - 1], el[1][p - 1]};
             double unused;
             stage_row<real, false, TAUF>(S, ir - 1, gb, gc, nullptr, ga, nullptr, H, glp, glc, gln, acr, V.t, cs, unused,
@@ -523,7 +579,11 @@ __global__ __launch_bounds__(BLOCK, Step2Occ<real>::waves) void k_step2(const So
 {
     const int nb = gridDim.x;
     const int blk = xcd_tile(blockIdx.x, nb);
-    const int t = __builtin_amdgcn_readfirstlane(blk * (BLOCK / 64) + (threadIdx.x >> 6));
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    __shared__ int done[BLOCK / 64];
+    done[w] = 0;
+    __syncthreads();
+    const int t = blk * (BLOCK / 64) + w;
     if (t >= ntiles) return;
     int solve = 0, lt = t;
     if (tiles) {
@@ -543,7 +603,6 @@ __global__ __launch_bounds__(BLOCK, Step2Occ<real>::waves) void k_step2(const So
     __shared__ double el[BLOCK / 64][2][FUSE_ROWS];
     __shared__ real hb[BLOCK / 64][64];
     __shared__ double hbl[BLOCK / 64][64];
-    const int w = threadIdx.x >> 6;
     const int rows = dp->rows, nstrip = dp->nstrip;
     const int rb = lt / nstrip, strip = lt - rb * nstrip;
     const int i0 = rb * rows;
@@ -567,7 +626,12 @@ __global__ __launch_bounds__(BLOCK, Step2Occ<real>::waves) void k_step2(const So
     }
     const bool diagA = records(dp, step), diagB = records(dp, step + 1);
     LaneDiag DA, DB;
-    march2<real, TAUF, MIXED>(dp, bufs, strip, i0, i1, fb[w], gb[w], ga[w], ef[w], el[w], hb[w], hbl[w],
+    // the strips beside, where whole strips or more columns follow
+    const bool wraps = dp->nt % STRIP == 0;
+    const int wl = w + (strip > 0 ? -1 : nstrip - 1), wr = w + (strip < nstrip - 1 ? 1 : 1 - nstrip);
+    const Beside W{w, (strip > 0 || wraps) && wl >= 0 && wl < BLOCK / 64 ? wl : -1,
+                   (strip < nstrip - 1 || wraps) && wr >= 0 && wr < BLOCK / 64 ? wr : -1, done};
+    march2<real, TAUF, MIXED>(dp, bufs, strip, i0, i1, fb[w], gb[w], ga[w], ef, el, hb[w], hbl[w], W,
                             DA, DB, diagA, diagB);
     // both steps' totals first (independent DPP chains the compiler can
     // interleave), then one lane stores them

@@ -92,26 +92,17 @@ PatchGeom pdbm::patches(const pdbm_params &p, bool alone)
     return patch_geom(p.nr, p.ntheta, p.sector, p.precision == PDBM_FP32, alone && !fuse_off() && rows_env() <= 0);
 }
 
-// Rows per wavefront: just enough wavefronts for one resident wave of the
-// whole grid (256 CUs x 4 SIMDs x the step kernels' occupancy: 1 wavefront
-// per SIMD in float64, 2 in float32), so that every wavefront marches the
-// longest possible column and none waits for a second round; at most
-// FUSE_ROWS (the two-step kernel's limit), so grids of more than 16 rows per
-// SIMD run several rounds.  PDBM_ROWS_PER_WAVE overrides it (tuning).
+// Rows per wavefront of a single solve (best_rows); PDBM_ROWS_PER_WAVE
+// overrides it (tuning).  Shorter blocks than FUSE_ROWS make no more than
+// MOST_WAVES wavefronts, whose drift partial sums a solve of
+// pdbm_create_noalloc has room for; beyond, they gain less than 3 %.
 int pdbm::rows_per_wave(const pdbm_params &p)
 {
-    const int nr = p.nr, nt = p.ntheta;
+    constexpr int64_t MOST_WAVES = 4096;
     if (patches(p, true).threads > 0) return PATCHES;
     if (rows_env() > 0) return rows_env();
-    // one round of wavefronts: one per SIMD in float64, two in float32
-    const int64_t slots = 256 * 4 * (p.precision == PDBM_FP32 ? 2 : 1);
-    const int64_t strips = (nt + STRIP - 1) / STRIP;
-    int64_t rows = ((int64_t)nr * strips + slots - 1) / slots;
-    if (rows < 2) rows = 2;
-    while (strips * ((nr + rows - 1) / rows) > slots) ++rows;
-    // short enough for the two-step kernel (large grids then run more than
-    // one round of wavefronts)
-    return (int)std::min<int64_t>(rows, FUSE_ROWS);
+    return best_rows([&](int r) { return (int64_t)solve_waves(p.nr, p.ntheta, r); }, p.precision == PDBM_FP32,
+                     MOST_WAVES);
 }
 
 // Largest |C_r| + |C_theta| over the grid for the fastest speed: the

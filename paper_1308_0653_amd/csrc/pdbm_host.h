@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <cmath>
 #include <cstdint>
 #include <string>
 #include <vector>
@@ -37,11 +38,51 @@ struct Layout {
 // `rows`: rows per wavefront of the marching kernels, or PATCHES for a solve
 // stepped on patches (patch_geom).
 constexpr int PATCHES = 0;
+
+// How long a launch of this many wavefronts takes, in the times one of them
+// takes on a full GPU (1024 SIMDs; one wavefront on each in float64, two in
+// float32, where one alone runs faster, and memory serves fewer of them
+// faster).  From timings of 300 x 380 to 3000 x 1024 grids and packs of 1 to
+// 40 in blocks of 2 to 16 rows: the wavefronts of a last round that is not
+// full take 0.6 of its time longer than their share (0.4 in float32).
+inline double launch_rounds(int64_t waves, bool fp32)
+{
+    const double x = (double)waves / (fp32 ? 2048 : 1024);
+    if (fp32 && x <= 0.5) return 0.55 + 0.25 * x;
+    if (x <= 1.0) return fp32 ? 0.6 + 0.4 * x : 1.0;
+    return x + (fp32 ? 0.4 : 0.6) * (std::ceil(x) - x);
+}
+// Rows per wavefront of the marching kernels for a launch of waves(r)
+// wavefronts in blocks of r rows: long blocks compute and read the fewest
+// rows twice, but a wavefront of r rows takes about 2 r + 5 rows' time (both
+// steps' rows, the two beside the block, its start), whole rounds of which
+// make the launch.  Between FEWEST_ROWS and FUSE_ROWS rows, more than `most`
+// wavefronts only where FUSE_ROWS needs them.  With the fewest rows that make
+// one round, else 16, 1100 x 1024 took 220 us per two steps in float64 and
+// takes 161 (1.92 rounds of 9 rows instead of 1.08 of 16), 1500 x 1024 229
+// and 200; in float32 2400 x 1024 207 and 182, 1280 x 1800 217 and 187.
+constexpr int FEWEST_ROWS = 2;
+template <class Waves>
+int best_rows(Waves waves, bool fp32, int64_t most)
+{
+    int best = FUSE_ROWS;
+    double least = 0.0;
+    for (int r = FUSE_ROWS; r >= FEWEST_ROWS; --r) {
+        const int64_t n = waves(r);
+        if (r < FUSE_ROWS && n > most) break;
+        const double t = (2 * r + 5) * launch_rounds(n, fp32);
+        if (r == FUSE_ROWS || t < least) {
+            best = r;
+            least = t;
+        }
+    }
+    return best;
+}
+
 Layout layout_of(const pdbm_params &p, int rows, bool alone);
 // Rows per wavefront a packed solve starts with, or PATCHES (Pack::rebuild
-// chooses them anew with every change of the pack, between FEWEST_ROWS and
-// FUSE_ROWS, unless PDBM_BATCH_ROWS fixes them).
-constexpr int FEWEST_ROWS = 2;
+// chooses them anew with every change of the pack, unless PDBM_BATCH_ROWS
+// fixes them).
 int batch_rows(const pdbm_params &p);
 int batch_rows_env();
 // Patches of a solve that rows_per_wave (alone) or batch_rows gives them.

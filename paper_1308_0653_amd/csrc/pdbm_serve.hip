@@ -16,7 +16,6 @@
 #include <algorithm>
 #include <chrono>
 #include <climits>
-#include <cmath>
 #include <condition_variable>
 #include <cstdlib>
 #include <cstring>
@@ -185,44 +184,21 @@ class Pack {
     hipGraphExec_t exec = nullptr;
     int graph_steps = 0;
 
-    // Rows per wavefront of the marched members.  A full GPU wants the
-    // longest blocks the two-step kernel takes (the fewest rows computed and
-    // read twice); with fewer wavefronts than the GPU holds at once a launch
-    // takes as long as one of them, so blocks are shortened until they fill
-    // it.  A block of r rows takes a wavefront about 2 r + 5 rows' time (both
-    // steps' rows, the two beside the block, its start); `rounds` is how many
-    // such times a launch takes, from packs of 1 to 40 solves.  A launch of
-    // one 300 x 380 solve took 83 us (float32) and 114 us (float64) in blocks
-    // of 16 rows and takes 23 and 32; four of 500 x 256 91 and 122, now 50
-    // and 83; ten 144 and 246, now 108 and 193; from 16 on the blocks stay
-    // at 16 rows.
+    // Rows per wavefront of the marched members.  In blocks of 16 rows a
+    // launch of one 300 x 380 solve took 83 us (float32) and 114 us
+    // (float64), of four of 500 x 256 91 and 122, of ten 144 and 246; now 23
+    // and 30, 50 and 83, 108 and 193; from 16 on the blocks stay near 16 rows.
     int row_block() const
     {
         if (batch_rows_env() > 0) return batch_rows_env();
-        int best = FUSE_ROWS;
-        double least = 0.0;
-        for (int r = FUSE_ROWS; r >= FEWEST_ROWS; --r) {
-            double waves = 0.0;
-            for (const Solve *m : members)
-                if (kind_of(*m) == WIDE) waves += m->waves_at(r);
-            const double t = (2 * r + 5) * rounds(waves);
-            if (r == FUSE_ROWS || t < least) {
-                best = r;
-                least = t;
-            }
-        }
-        return best;
-    }
-    double rounds(double waves) const
-    {
-        const double simds = 1024.0;
-        if (fp32) {  // two wavefronts per SIMD; one runs faster alone
-            if (waves <= simds) return 0.62;
-            const double x = waves / (2.0 * simds);
-            return x <= 1.0 ? 1.0 : x + 0.4 * (std::ceil(x) - x);
-        }
-        const double x = waves / simds;
-        return x <= 1.0 ? 1.0 : x + 0.6 * (std::ceil(x) - x);
+        return best_rows(
+            [&](int r) {
+                int64_t n = 0;
+                for (const Solve *m : members)
+                    if (kind_of(*m) == WIDE) n += m->waves_at(r);
+                return n;
+            },
+            fp32, INT64_MAX);
     }
 
     static int grow(void **p, size_t &cap, size_t need)

@@ -35,3 +35,26 @@ def test_packs_of_any_size_equal_solo_runs_bitwise(members, diag_every, precisio
         assert np.array_equal(F, Fb), (i, shapes[i], np.abs(F - Fb).max())
         s.close()
     b.close()
+
+
+# more wavefronts than the device holds at once: 9 and 10 rows alone, 16 in a pack that makes drift records
+@pytest.mark.parametrize("nr,nt,precision", [(1100, 1024, P.PDBM_FP64), (2400, 1024, P.PDBM_FP32)])
+def test_single_solves_beyond_one_round_equal_blocks_of_16_rows_bitwise(nr, nt, precision):
+    p, ic = _params(nr, nt, 4, precision, 1)
+    s = P.Solver(p, ic)
+    s.step(7)
+    b = P.Batch([p], [ic], chunk_steps=4)
+    b.step(7)
+    F, _ = s.moments()
+    assert np.array_equal(F, b.moments(0)[0])
+    hist = s.diag_history()
+    assert [r["step"] for r in hist] == list(range(7))
+    # the record of step k is that of the state k steps in (the same 1e6 or more terms, added up in another order)
+    t = P.Solver(p, ic)
+    t.step(6)
+    d = t.moments()[1]
+    assert abs(hist[6]["mass"] - d["mass"]) <= 1e-11 * d["mass"] and hist[6]["n_nonfinite"] == 0
+    assert abs(hist[6]["energy"] - d["energy"]) <= 1e-11 * abs(d["energy"])
+    t.close()
+    s.close()
+    b.close()

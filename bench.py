@@ -269,7 +269,7 @@ def side_kernels(P, w, torch, steps=200, calls=20, warm_ms=60.0):
       same steps of the plain solve, the two timed in turn twice (the
       second pair is reported); the field adds 8 B read per cell per
       launch;
-    - k_step2<double, ROT>, two steps per launch of a rotated sector (Sec.
+    - k_step2<double>, two steps per launch of a rotated sector (Sec.
       II.D: the periodic images of a sector turn the directions): the same
       gas on half the annulus (sector 4, 1024 x 512 cells, the same dtheta),
       `steps` steps."""
@@ -325,7 +325,7 @@ def side_kernels(P, w, torch, steps=200, calls=20, warm_ms=60.0):
                       "extra_bytes_per_launch": 8 * w.cells,
                       "effective_gbs": round(per_launch / (t_tauf / launches) / 1e9, 1),
                       "effective_frac_of_peak": round(per_launch / (t_tauf / launches) / 1e9 / HBM_PEAK_GBS, 4)},
-        "sector": {"kernel": "k_step2<double, ROT>", "sector": 4, "nr": w.nr, "ntheta": w.ntheta // 2, "steps": steps,
+        "sector": {"kernel": "k_step2<double>", "sector": 4, "nr": w.nr, "ntheta": w.ntheta // 2, "steps": steps,
                    "steps_per_launch": 2, "avg_launch_us": round(t_half / launches * 1e6, 2),
                    "effective_gbs": round(BYTES_PER_CELL["f64"] * half_cells / (t_half / steps) / 1e9, 1),
                    "effective_frac_of_peak": round(

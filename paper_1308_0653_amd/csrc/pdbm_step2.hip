@@ -62,7 +62,7 @@ struct LaneDiag {
 // for 1 to 4, right for 5, 6, 7, 0.  That is one lane shift per direction and
 // no selects, half the LDS reads of the row ahead and of the halo, and no
 // lane masks to hold (with both sides fetched and selected per lane, 1024 x
-// 1024 launches took 155 us in float64 and 94 us in float32; now 140 and
+// 1024 launches took 155 us in float64 and 94 us in float32, then 140 and
 // 91).  MIXED strips, where a lane's neighbour may lie in the octant
 // beside, shift one value more per side and ring and select between the two.
 // Radial neighbours: the row behind (below) in compact LDS slots (low_dir of
@@ -374,9 +374,14 @@ __device__ __forceinline__ void await(int &done, int rows)
 // (at most FUSE_ROWS), marched outward.  Positions p count rows from the
 // first row of the block (p = 0); stage A runs on positions -1 .. R where
 // they are grid rows, stage B on 0 .. R - 1, one position behind stage A.
-// (Odd blocks marched inward, so that the rows between two blocks were read
-// by both at once, took 1 % less time in float64 and 3 % less in float32, but
-// need the upwind sides selected at run time.)  LDS per wavefront: the
+// (Odd blocks marched inward read the rows between two blocks at the same
+// time as the block beside, 12 % less traffic in float32.  With the sides
+// selected at run time that was 1 % faster in float64 and 3 % in float32
+// than selecting them for outward marches alone, far less than the selects
+// cost; with a march compiled for each direction, 113 KB of code, float64
+// took 132 us instead of 126 per 1024 x 1024 launch, float32 79 instead of
+// 80, and larger grids 1 to 2 % more: the instruction cache, 64 KB for two
+// CUs.)  LDS per wavefront: the
 // compact rows behind of f (fb) and of g (gb), the full row of g just
 // computed (ga), g at the columns beside the strip (of efs and els, which the
 // wavefronts beside write too) and the gathered halo values of stage A's row

@@ -58,7 +58,10 @@ Layout pdbm::layout_of(const pdbm_params &p, int rows, bool alone)
     L.cs = align256((size_t)p.ntheta * sizeof(double2));
     L.desc = align256(sizeof(SolveDesc));
     L.state = align256(sizeof(SolveState));
-    L.wpart = align256((size_t)PART_RING * L.nwaves * 5 * sizeof(double));
+    // drift partial sums of this form's wavefronts or patches (without
+    // records none are written)
+    const int parts = p.diag_every > 0 ? L.nwaves : solve_waves(p.nr, p.ntheta, FUSE_ROWS);
+    L.wpart = align256((size_t)PART_RING * parts * 5 * sizeof(double));
     L.hist = align256((size_t)(HIST_CAP + 1) * sizeof(pdbm_diag));
     L.cpart = align256((size_t)L.cblocks * 5 * sizeof(double));
     L.state_total = 2 * L.f + 2 * L.lam + L.omega;
@@ -89,7 +92,8 @@ static int rows_env()
 
 PatchGeom pdbm::patches(const pdbm_params &p, bool alone)
 {
-    return patch_geom(p.nr, p.ntheta, p.sector, p.precision == PDBM_FP32, alone && !fuse_off() && rows_env() <= 0);
+    return patch_geom(p.nr, p.ntheta, p.sector, p.precision == PDBM_FP32, alone && !fuse_off() && rows_env() <= 0,
+                      p.diag_every > 0);
 }
 
 // Rows per wavefront of a single solve (best_rows); PDBM_ROWS_PER_WAVE

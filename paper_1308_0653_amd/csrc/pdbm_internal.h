@@ -20,8 +20,6 @@ constexpr int FUSE_ROWS = 16;   // most rows per wavefront of the two-step kerne
 constexpr int COL_K = 8;                  // steps per launch of the single-column kernel, at most
 constexpr int COL_W = STRIP - 2 * COL_K;  // rows a wavefront owns in a single-column solve (48)
 
-constexpr int PACK_PATCH_THREADS = 256, PACK_PATCH_LANES = 4;  // patches of grids narrower than their octants
-
 // Layout of f within one r row (33 * pitch elements): the rest particle's
 // plane [pitch], then the 16 pairs of opposite directions of each speed, pair
 // c = 4 (k - 1) + (i mod 4) holding directions i and i + 4 (relative to the

@@ -298,6 +298,15 @@ constexpr PatchShape PATCH_FP64[] = {
 constexpr PatchShape PATCH_FP32[] = {
     {16, 16, 2, 512, 2, 2700, 5000}, {16, 16, 3, 512, 2, 3000, 6100},  {16, 16, 4, 512, 2, 3000, 6800},
     {12, 12, 4, 768, 4, 2800, 6000}, {19, 20, 3, 768, 2, 3000, 10500}};
+// Grids of fewer columns than octants, alone or packed: NARROW, and with
+// drift records NARROW_TALL instead of more than NARROW_MOST patches.  A
+// patch keeps a drift partial sum per step; a tall one owns 32 rows or more,
+// so that these sums take no more memory than those of wavefronts marching 16
+// rows.  Per step, tall against not: 64 x 4 4.2 against 3.2 us (float64) and
+// 3.6 / 3.1 (float32), 4000 x 5 4.9 / 4.3 and 4.2 / 3.9, 20000 x 6 17.6 / 17.1
+// and 14.4 / 13.4, 40000 x 7 29.9 / 38.2 and 23.7 / 27.2.
+constexpr PatchShape NARROW = {8, 8, 2, 256, 4, 0, 0}, NARROW_TALL = {32, 8, 2, 512, 2, 0, 0};
+constexpr int NARROW_MOST = 1024;
 // One theta column: 128 rows, 24 steps.
 constexpr PatchShape PATCH_COLUMN = {128, 1, 24, 256, 2, 0, 0};
 // Rounds up to which patches are the faster: of the 16 x 16 shape with k = 2
@@ -321,8 +330,8 @@ inline PatchGeom patches_of(const PatchShape &s, int nr, int nt)
     g.ntiles = g.nbc * ((nr + g.rows - 1) / g.rows);
     return g;
 }
-// Patches of a grid (`alone` on the GPU, or in a pack); threads = 0: it has
-// none and is marched by wavefronts or, a single column, held by them.
+// Patches of a grid (`alone` on the GPU, or in a pack; with drift `records`
+// or not); threads = 0: it has none and is marched by wavefronts or, a single column, held by them.
 // - Fewer columns than octants: always, as neighbouring columns may then
 //   differ by more than the one octant the marching kernels take.
 // - Alone and too small to fill the GPU with marching wavefronts: a launch of
@@ -333,9 +342,12 @@ inline PatchGeom patches_of(const PatchShape &s, int nr, int nt)
 //   and 2.4 / 10.1; 300 x 130 6.4 / 13.2 and 4.5 / 10.4; 300 x 200 8.1 / 13.8
 //   and 6.3 / 10.4; 400 x 300 16.1 / 15.3 and 11.6 / 10.9 (marched).  A single
 //   column of 20000 rows: 2.0 against 3.6 us (float64), 1.6 against 2.6.
-inline PatchGeom patch_geom(int nr, int nt, int sector, bool fp32, bool alone)
+inline PatchGeom patch_geom(int nr, int nt, int sector, bool fp32, bool alone, bool records = false)
 {
-    if (nt > 1 && !marchable(nt, sector)) return patches_of({8, 8, 2, PACK_PATCH_THREADS, PACK_PATCH_LANES, 0, 0}, nr, nt);
+    if (nt > 1 && !marchable(nt, sector)) {
+        const PatchGeom g = patches_of(NARROW, nr, nt);
+        return records && g.ntiles > NARROW_MOST ? patches_of(NARROW_TALL, nr, nt) : g;
+    }
     if (!alone) return PatchGeom{};
     if (nt == 1) {
         const PatchGeom g = patches_of(PATCH_COLUMN, nr, 1);

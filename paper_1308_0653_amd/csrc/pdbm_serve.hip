@@ -157,17 +157,22 @@ class Pack {
 
   private:
     // The members by the kernel that steps them, and their part of the tables.
-    enum { WIDE, COLUMNS, PATCHED, KINDS };
+    enum { WIDE, COLUMNS, PATCHED, PATCHED_TALL, KINDS };
     struct Part {
         int m0 = 0, nm = 0, t0 = 0, nt = 0;  // members, tiles
     };
-    static int kind_of(const Solve &m) { return m.patched() ? PATCHED : m.columnar() ? COLUMNS : WIDE; }
-    // steps per launch of the columns and of the patches (the same of every patched member)
+    static int kind_of(const Solve &m)
+    {
+        if (m.patched()) return m.hd.patch.threads == NARROW.threads ? PATCHED : PATCHED_TALL;
+        return m.columnar() ? COLUMNS : WIDE;
+    }
+    static const PatchShape &shape_of(int kind) { return kind == PATCHED ? NARROW : NARROW_TALL; }
+    // steps per launch of the columns and of the patches (the same of every member of a kind)
     int most_of(int kind) const
     {
         if (kind == COLUMNS) return COL_K;
         for (const Solve *m : members)
-            if (m->patched()) return m->patch_steps();
+            if (kind_of(*m) == kind) return m->patch_steps();
         return 1;
     }
     Part part[KINDS];
@@ -255,7 +260,7 @@ class Pack {
                     e = launch_step(ddescs, dtiles, w.nt, dbases, i, dflips, 0, fp32, mixed, false, st);
             }
         }
-        for (int k : {COLUMNS, PATCHED}) {
+        for (int k = COLUMNS; k < KINDS; ++k) {
             const Part &c = part[k];
             if (c.nm == 0) continue;
             const int most = most_of(k);
@@ -265,8 +270,8 @@ class Pack {
                 if (k == COLUMNS)
                     e = launch_column(ddescs, dtiles + c.t0, c.nt, dbases, done, dflips, pf, nk, fp32, false, st);
                 else
-                    e = launch_patch(ddescs, dtiles + c.t0, c.nt, PACK_PATCH_THREADS, PACK_PATCH_LANES, dbases, done, dflips, pf, nk,
-                                     fp32, false, st);
+                    e = launch_patch(ddescs, dtiles + c.t0, c.nt, shape_of(k).threads, shape_of(k).lanes, dbases, done,
+                                     dflips, pf, nk, fp32, false, st);
                 pf ^= (nk + 1) & 1;
                 done += nk;
             }

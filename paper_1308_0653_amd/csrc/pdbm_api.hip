@@ -58,9 +58,9 @@ Layout pdbm::layout_of(const pdbm_params &p, int rows, bool alone)
     L.cs = align256((size_t)p.ntheta * sizeof(double2));
     L.desc = align256(sizeof(SolveDesc));
     L.state = align256(sizeof(SolveState));
-    // drift partial sums of this form's wavefronts or patches (without
-    // records none are written)
-    const int parts = p.diag_every > 0 ? L.nwaves : solve_waves(p.nr, p.ntheta, FUSE_ROWS);
+    // drift partial sums: of this form's wavefronts or patches if there are
+    // records, and no less than a pack of the solve takes
+    const int parts = std::max(p.diag_every > 0 ? L.nwaves : 0, solve_waves(p.nr, p.ntheta, FUSE_ROWS));
     L.wpart = align256((size_t)PART_RING * parts * 5 * sizeof(double));
     L.hist = align256((size_t)(HIST_CAP + 1) * sizeof(pdbm_diag));
     L.cpart = align256((size_t)L.cblocks * 5 * sizeof(double));

@@ -34,6 +34,8 @@ def test_noalloc_takes_narrow_grids_of_many_rows(diag_every, precision):
     for nr, nt, sector in [(100, 7, 8), (5121, 7, 8), (40000, 6, 8), (40000, 7, 8), (60000, 5, 8), (80000, 4, 8),
                            (80000, 4, 5), (100000, 2, 8), (100000, 7, 8), (100000, 2, 3)]:
         assert not refused(nr, nt, sector), (nr, nt, sector)
+    for nt in (2, 5, 7):
+        assert refused(110000, nt, 8), nt
 
 
 @pytest.mark.gpu
@@ -70,3 +72,15 @@ def test_tall_patches_step_like_the_others_bitwise(precision):
         a.close()
         r.close()
     b.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("diag_every", [0, 2])
+@pytest.mark.parametrize("nr,nt,sector", [(1000, 1, 8), (64, 2, 2), (64, 8, 8), (200, 20, 8), (400, 7, 8), (64, 64, 8)])
+def test_a_cap_of_the_solves_own_bytes_admits_it(nr, nt, sector, diag_every):
+    """A packed solve takes no more memory than alone (pdbm_state_bytes)."""
+    p, ic = _made(nr, nt, P.PDBM_FP64, diag_every, sector)
+    srv = P.Server(hbm_cap_bytes=P.pdbm_state_bytes(p), max_slots=1, chunk_steps=4)
+    rid = srv.submit(p, ic, 4)
+    assert srv.wait(30.0) and srv.poll(rid)[0] == P.PDBM_DONE
+    srv.close()

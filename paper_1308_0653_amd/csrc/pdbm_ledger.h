@@ -40,9 +40,16 @@ struct Ledger {
     // so a request is retired at most once whatever path reaches it twice.
     bool retire(int32_t &state, size_t bytes, bool ok, double cell_updates)
     {
+        if (!finish(state, ok, cell_updates)) return false;
+        in_use -= bytes;
+        return true;
+    }
+    // The same of a request whose memory is given back later, by taking its
+    // bytes off in_use.
+    bool finish(int32_t &state, bool ok, double cell_updates)
+    {
         if (state != PDBM_RUNNING) return false;
         state = ok ? PDBM_DONE : PDBM_FAILED;
-        in_use -= bytes;
         stats.running--;
         if (ok) {
             stats.done++;

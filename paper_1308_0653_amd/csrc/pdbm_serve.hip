@@ -467,6 +467,9 @@ struct Request {
     pdbm_diag diag{};
     bool read = true;  // nothing failed so far in reading its result
     double t_submit = -1, t_admit = -1, t_done = -1;
+
+    bool ok() const { return !diag.n_nonfinite && !diag.n_nonphys; }
+    double cell_updates() const { return (double)p.nr * p.ntheta * (double)nsteps; }
 };
 
 }  // namespace
@@ -489,9 +492,13 @@ struct pdbm_server {
 
     // scheduler-thread state
     std::vector<Request *> running;
-    std::vector<Request *> leaving;  // at their step count, out of the packs, results not read yet
+    std::vector<Request *> leaving;  // at their step count, out of the packs, kept fields not read yet
     hipStream_t copies = nullptr;    // results of the leaving ones, beside the steps of the others
     hipEvent_t ready = nullptr;      // ... made on st
+    struct Spent {                   // memory of a finished request, to be given back
+        std::unique_ptr<Solve> solve;
+        size_t bytes;
+    };
     Pack pack[2];  // by precision: PDBM_FP64, PDBM_FP32
     std::thread thr;
 
@@ -500,7 +507,8 @@ struct pdbm_server {
     int admit_and_step(std::vector<Request *> &admitted);
     void retire(Request *r, int err);
     void make_results();
-    void read_results();
+    void read_results(bool beside);
+    void read_reports(const std::vector<Request *> &ended);
 };
 
 // The results of the leaving requests: their kernels on st, ahead of the
@@ -517,20 +525,45 @@ void pdbm_server::make_results()
         for (Request *r : leaving) r->read = false;
 }
 
-void pdbm_server::read_results()
+// `beside`: steps of the others are in flight.  Freeing memory waits for
+// them, so each request ends as soon as its result is there, and their memory
+// is given back after the last copy.
+void pdbm_server::read_results(bool beside)
 {
+    std::vector<Spent> spent;
     for (Request *r : leaving) {
-        std::shared_ptr<HostArray> f;
-        if (r->flags & PDBM_KEEP_FIELDS) {
-            f = std::make_shared<HostArray>((size_t)6 * r->p.nr * r->p.ntheta);
-            if (!f->data) r->read = false;
-        }
-        if (r->read) r->read = fetch_result(*r->solve, f ? f->data : nullptr, &r->diag, copies) == PDBM_OK;
+        std::shared_ptr<HostArray> f = std::make_shared<HostArray>((size_t)6 * r->p.nr * r->p.ntheta);
+        if (!f->data) r->read = false;
+        if (r->read) r->read = fetch_result(*r->solve, f->data, &r->diag, copies) == PDBM_OK;
         if (r->read) r->fields = std::move(f);
+        if (!beside || !r->read) {
+            retire(r, r->read ? PDBM_OK : PDBM_EHIP);
+            continue;
+        }
+        spent.push_back({std::move(r->solve), r->bytes});
+        std::lock_guard<std::mutex> g(mu);
+        r->t_done = now();
+        led.finish(r->state, r->ok(), r->cell_updates());
+        done.notify_all();  // (from here on the request may be released)
     }
-    // (freeing a solve's memory waits for the device: after the last copy)
-    for (Request *r : leaving) retire(r, r->read ? PDBM_OK : PDBM_EHIP);
     leaving.clear();
+    if (spent.empty()) return;
+    (void)hipStreamSynchronize(st);
+    for (Spent &m : spent) m.solve->release();
+    std::lock_guard<std::mutex> g(mu);
+    for (const Spent &m : spent) led.in_use -= m.bytes;
+}
+
+// The ends of requests that keep no fields: their drift reports alone, read
+// between the chunks.
+void pdbm_server::read_reports(const std::vector<Request *> &ended)
+{
+    for (Request *r : ended)
+        if (start_result(*r->solve, false, st) != PDBM_OK) r->read = false;
+    for (Request *r : ended) {
+        if (r->read) r->read = fetch_result(*r->solve, nullptr, &r->diag, st) == PDBM_OK;
+        retire(r, r->read ? PDBM_OK : PDBM_EHIP);
+    }
 }
 
 void pdbm_server::retire(Request *r, int err)
@@ -540,7 +573,6 @@ void pdbm_server::retire(Request *r, int err)
         std::lock_guard<std::mutex> g(mu);
         if (r->state != PDBM_RUNNING) return;
     }
-    const bool ok = err == 0 && !r->diag.n_nonfinite && !r->diag.n_nonphys;
     if (r->solve) {
         (void)hipStreamSynchronize(st);
         r->solve->release();
@@ -548,7 +580,7 @@ void pdbm_server::retire(Request *r, int err)
     }
     std::lock_guard<std::mutex> g(mu);
     r->t_done = now();
-    led.retire(r->state, r->bytes, ok, (double)r->p.nr * r->p.ntheta * (double)r->nsteps);
+    led.retire(r->state, r->bytes, err == 0 && r->ok(), r->cell_updates());
     done.notify_all();
 }
 
@@ -568,6 +600,15 @@ void pdbm_server::loop()
                     admitted.push_back(r);
                 }
                 if (stop) break;
+                if (!queue.empty() && !leaving.empty()) {
+                    // a request waits for the slot or memory of one that is
+                    // leaving: the results are read at once
+                    lk.unlock();
+                    make_results();
+                    read_results(false);
+                    lk.lock();
+                    continue;
+                }
                 if (!admitted.empty() || !running.empty() || !leaving.empty()) break;
                 cv.wait(lk);
             }
@@ -595,7 +636,7 @@ void pdbm_server::loop()
                 leaving.clear();
             }
             make_results();  // those at their step count have finished
-            read_results();
+            read_results(false);
             for (auto &k : pack) k.members.clear();
             if (rc) {
                 std::lock_guard<std::mutex> g(mu);
@@ -635,25 +676,26 @@ int pdbm_server::admit_and_step(std::vector<Request *> &admitted)
         int rc = pack[k].run(chunk, chunk, st);
         if (rc) return rc;
     }
-    read_results();
+    read_results(!running.empty());
     HIPCHK(hipStreamSynchronize(st));
     if (!running.empty()) {
         std::lock_guard<std::mutex> g(mu);
         led.stats.steps_launched += chunk;
     }
-    std::vector<Request *> still;
+    std::vector<Request *> still, ended;
     for (size_t i = 0; i < running.size(); ++i) {
         Request *r = running[i];
         if (r->solve->step >= r->nsteps) {
             auto &m = pack[r->p.precision].members;
             m.erase(std::find(m.begin(), m.end(), r->solve.get()));
             pack[r->p.precision].dirty = true;
-            leaving.push_back(r);
+            (r->flags & PDBM_KEEP_FIELDS ? leaving : ended).push_back(r);
         } else {
             still.push_back(r);
         }
     }
     running.swap(still);
+    read_reports(ended);
     return PDBM_OK;
 }
 

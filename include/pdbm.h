@@ -237,7 +237,10 @@ int pdbm_set_tau_async(pdbm_solver *s, const void *tau_device);
  * small grid, 2 to 4 steps; solves with a single theta column take up to 24
  * steps per launch, of more than about 40 thousand rows up to 8.  The states
  * after every call are those of Sec. II.C's scheme, bit for bit the same
- * however the steps are cut into calls and launches. */
+ * however the steps are cut into calls and launches.  A call of a multiple of
+ * 4 steps (of 16 for a single theta column) leaves the state in the buffer it
+ * found it in, so that, captured in a HIP graph, it can be replayed (the step
+ * counter and drift records are then those of the captured call). */
 int pdbm_step(pdbm_solver *s, int64_t nsteps);
 
 /* Number of steps taken so far (host-side counter). */

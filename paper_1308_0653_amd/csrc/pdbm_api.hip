@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "pdbm_host.h"
+#include "pdbm_schedule.h"
 
 using namespace pdbm;
 
@@ -502,10 +503,13 @@ int pdbm_step(pdbm_solver *h, int64_t nsteps)
     const bool pairs = s.fusable();
     const bool column = s.columnar();
     const int most = s.patched() ? s.patch_steps() : column ? COL_K : 2;  // steps of one launch, at most
+    // launches of a solve on patches (patch_launches)
+    int64_t launches = s.patched() && nsteps > 0 ? patch_launches(nsteps, most, s.p.ntheta == 1 ? COL_K : 2) : 0;
     for (int64_t i = 0; i < nsteps;) {
         if (s.patched()) {
-            // as a column's launches
-            const int nk = (int)std::min<int64_t>(most, nsteps - i);
+            // as a column's launches, of about the same number of steps each
+            const int nk = (int)((nsteps - i + launches - 1) / launches);
+            --launches;
             HIPCHK(launch_patch(s.dd, nullptr, s.waves(), s.hd.patch.threads, s.hd.patch.lanes, nullptr, s.step, nullptr, s.flip, nk,
                                 s.fp32, s.tauf(), h->st));
             s.step += nk;

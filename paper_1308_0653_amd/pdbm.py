@@ -71,9 +71,9 @@ class PdbmError(RuntimeError):
 
 _lib = None
 
-# PyBytes_FromStringAndSize(NULL, n): a bytes object of n bytes still to be filled
-_new_bytes = C.pythonapi.PyBytes_FromStringAndSize
-_new_bytes.restype, _new_bytes.argtypes = C.py_object, [C.c_char_p, C.c_ssize_t]
+# PyBytes_FromStringAndSize(NULL, n): a bytes object of n bytes still to be filled (a prototype of our own: the
+# attributes of C.pythonapi are shared by the whole process)
+_new_bytes = C.PYFUNCTYPE(C.py_object, C.c_char_p, C.c_ssize_t)(("PyBytes_FromStringAndSize", C.pythonapi))
 
 
 def lib():

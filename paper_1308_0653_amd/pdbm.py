@@ -361,7 +361,8 @@ class Solver:
     get_state = pdbm_get_state
 
     def pdbm_set_state(self, blob: bytes):
-        blob = bytes(blob)  # the same object if it is one
+        if not isinstance(blob, bytes):
+            raise TypeError(f"a checkpoint is a bytes object, not {type(blob).__name__}")
         _check(self.L.pdbm_set_state(self.h, C.c_char_p(blob), len(blob)))
 
     set_state = pdbm_set_state

@@ -12,10 +12,11 @@ namespace {
 // and after the last its own cells, which it stores.  Workgroups never wait
 // for one another.
 //
-// Four lanes take a cell, lane h the ring of speed h + 1 (lane 0 also the
-// rest particle): each keeps its ring's eight distributions in registers,
-// the four add up their partial moments (DPP), and each updates its ring, so
-// the chain of a cell's step is about a quarter of what one lane would run.
+// Two or four lanes (LPC) take a cell, lane h the rings of speeds 4 h / LPC + 1
+// to 4 (h + 1) / LPC (lane 0 also the rest particle): each keeps its rings'
+// distributions in registers, they add up their partial moments (DPP), and each
+// updates its rings, so the chain of a cell's step is about a half or a quarter
+// of what one lane would run.
 // The upwind neighbours come from LDS, where every cell publishes its
 // distributions at the start of a step in one of two buffers (one barrier
 // per step): element (direction d, thread t) at d * threads + t, so that
@@ -141,6 +142,7 @@ __global__ __launch_bounds__(NT, 1) void k_patch(const SolveDesc *descs, const u
         __syncthreads();
         if (rec && t == 0) {
             double *out = dp->wpart + (((size_t)((step / dp->diag_every) % PART_RING)) * dp->nwaves + tile) * 5;
+#pragma unroll 1  // (loaded all at once, the values of 12 wavefronts spill to scratch memory)
             for (int i = 0; i < 5; ++i) {
                 double s = part[0][i];
                 for (int w = 1; w < NT / 64; ++w) s += part[w][i];
@@ -198,17 +200,27 @@ __global__ __launch_bounds__(NT, 1) void k_patch(const SolveDesc *descs, const u
 
 }  // namespace
 
-// A kernel per precision, tau field, lanes per cell and workgroup size.
-template <typename real, bool TAUF, int LPC>
-static void launch_k_patch(int ntiles, int threads, hipStream_t st, const SolveDesc *descs, const uint2 *tiles,
-                           const int64_t *bases, int64_t step_off, const int *flips, int flip, int nk)
+// A kernel per precision and tau field for the lanes per cell and the
+// workgroup sizes that the shapes of pdbm_offsets.h use.
+template <typename real, bool TAUF>
+static auto patch_kernel(int threads, int lanes) -> decltype(&k_patch<real, TAUF, 2, 512>)
 {
-    // (in float64, two lanes to a cell in workgroups of 768 would need 200 KB of LDS)
-    constexpr int MOST = LPC == 4 || sizeof(real) == 4 ? 768 : 512;
-    auto *fn = threads == 256   ? &k_patch<real, TAUF, LPC, 256>
-               : threads == 512 ? &k_patch<real, TAUF, LPC, 512>
-                                : &k_patch<real, TAUF, LPC, MOST>;
-    hipLaunchKernelGGL(fn, dim3(ntiles), dim3(threads), 0, st, descs, tiles, bases, step_off, flips, flip, nk);
+    constexpr bool fp32 = sizeof(real) == 4;
+    switch (8 * threads + lanes) {
+    case 8 * 256 + 2: return &k_patch<real, TAUF, 2, 256>;
+    case 8 * 256 + 4: return &k_patch<real, TAUF, 4, 256>;
+    case 8 * 512 + 2: return &k_patch<real, TAUF, 2, 512>;
+    case 8 * 512 + 4:
+        if constexpr (!fp32) return &k_patch<real, TAUF, 4, 512>;
+        break;
+    case 8 * 768 + 2:
+        if constexpr (fp32) return &k_patch<real, TAUF, 2, 768>;  // (200 KB of LDS in float64)
+        break;
+    case 8 * 768 + 4:
+        if constexpr (fp32) return &k_patch<real, TAUF, 4, 768>;
+        break;
+    }
+    return nullptr;
 }
 
 hipError_t launch_patch(const SolveDesc *descs, const uint2 *tiles, int ntiles, int threads, int lanes,
@@ -216,14 +228,10 @@ hipError_t launch_patch(const SolveDesc *descs, const uint2 *tiles, int ntiles, 
                         hipStream_t st)
 {
     if (ntiles == 0 || nk <= 0) return hipSuccess;
-    using L = void (*)(int, int, hipStream_t, const SolveDesc *, const uint2 *, const int64_t *, int64_t, const int *, int,
-                       int);
-    // [lanes / 4][fp32][tauf]
-    static const L table[2][2][2] = {{{launch_k_patch<double, false, 2>, launch_k_patch<double, true, 2>},
-                                      {launch_k_patch<float, false, 2>, launch_k_patch<float, true, 2>}},
-                                     {{launch_k_patch<double, false, 4>, launch_k_patch<double, true, 4>},
-                                      {launch_k_patch<float, false, 4>, launch_k_patch<float, true, 4>}}};
-    table[lanes / 4][fp32][tauf](ntiles, threads, st, descs, tiles, bases, step_off, flips, flip, nk);
+    auto *fn = fp32 ? (tauf ? patch_kernel<float, true>(threads, lanes) : patch_kernel<float, false>(threads, lanes))
+                    : (tauf ? patch_kernel<double, true>(threads, lanes) : patch_kernel<double, false>(threads, lanes));
+    if (!fn) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(fn, dim3(ntiles), dim3(threads), 0, st, descs, tiles, bases, step_off, flips, flip, nk);
     return hipGetLastError();
 }
 

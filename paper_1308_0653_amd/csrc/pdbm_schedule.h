@@ -34,11 +34,11 @@ inline int column_chunk_toggle(int64_t left, int64_t n, int k)
     return t;
 }
 
-// Launches that n > 0 steps on patches are cut into, of up to `most` steps
-// each: as few as there can be, or one more, so that their number is even
-// where that of marching launches, of up to `march` steps, is.  A call that
-// leaves the state in the buffer it found it in does so in either form, and
-// can be captured in a graph and replayed.
+// Launches that n > 0 steps on patches are cut into where they are captured
+// in a graph, of up to `most` steps each: as few as there can be, or one more,
+// so that their number is even where that of marching launches, of up to
+// `march` steps, is.  A call that leaves the state in the buffer it found it
+// in does so in either form, and can be replayed.
 inline int64_t patch_launches(int64_t n, int most, int march)
 {
     const int64_t m = most > 1 ? (n - 1) / march + 1 : n;  // one step per launch: as many in either form

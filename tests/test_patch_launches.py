@@ -1,4 +1,4 @@
-"""How steps on patches are cut into launches (patch_launches of
+"""How captured steps on patches are cut into launches (patch_launches of
 pdbm_schedule.h): every launch takes 1 to `most` steps, they add up, and their
 number is even where that of marching launches is."""
 import os

@@ -306,7 +306,6 @@ int Solve::init(const pdbm_params &pp, const pdbm_ic *ic, void *workspace, size_
     hd.nwaves = L.nwaves;
     hd.nstrip = (p.ntheta + STRIP - 1) / STRIP;
     hd.diag_every = p.diag_every;
-    hd.plane = L.pitch;
     hd.rstride = (int64_t)NQ * L.pitch;
     hd.nsteps = nsteps;
     hd.dr = (p.r_max - p.r_min) / p.nr;

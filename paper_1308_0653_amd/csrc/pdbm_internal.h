@@ -60,7 +60,6 @@ struct SolveDesc {
     int32_t nr, nt, pitch, sector;
     int32_t m, n, disc, reacts;          // disc: r_min == 0; reacts: w1+w2 > 0
     int32_t rows, nwaves, nstrip, diag_every;  // rows marched by one wavefront; its wavefronts
-    int64_t plane;    // elements of the rest particle's plane (= pitch; a pair takes 2 * plane)
     int64_t rstride;  // elements between consecutive r rows of f (= NQ * pitch)
     int64_t nsteps;   // the solve stops advancing once it has taken this many steps
     double r_min, dr, dth;

@@ -402,6 +402,22 @@ __host__ __device__ inline PatchCell patch_cell(const PatchGeom &g, int nr, int 
     c.own = in && c.row >= r0 && c.row < r1 && ext >= c0 && ext < c1;
     return c;
 }
+// Byte offsets of what lane h of a cell's `lanes` loads and stores: the first of
+// its 16 / lanes pairs (each next one a pair on), the rest particle, lambda and
+// the cell's entry of the per-cell tau field.
+struct PatchOffsets {
+    uint32_t pair, rest, lam, om;
+};
+__host__ __device__ inline PatchOffsets patch_offsets(const PatchCell &c, const RowBytes &b, int esz, int lanes, int h)
+{
+    PatchOffsets o;
+    const uint32_t es = (uint32_t)esz, row = (uint32_t)c.row * b.row;
+    o.rest = row + (uint32_t)c.pc * es;
+    o.lam = (uint32_t)c.row * b.lrow + (uint32_t)c.pc * 8u;
+    o.pair = row + 2u * (uint32_t)c.pc * es + pair_in_row(b, 16 / lanes * h);
+    o.om = (uint32_t)c.row * b.rest + (uint32_t)c.pc * es;
+    return o;
+}
 // Places (cells of the patch) of a cell's neighbours: itself beyond the
 // radial ends of the grid (the ghosts of Sec. II.D) and at the edge of the
 // halo (never used by a cell still needed), the other end around a whole

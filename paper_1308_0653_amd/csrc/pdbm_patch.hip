@@ -55,17 +55,14 @@ __global__ __launch_bounds__(NT, 1) void k_patch(const SolveDesc *descs, const u
     const PatchCell c = patch_cell(g, nr, nt, dp->inv2, tile, t / LPC);
 
     // the state at step0: this lane's ring, the rest particle, lambda
-    const uint32_t vrow = (uint32_t)c.row * b.row;
-    const uint32_t vrest = vrow + (uint32_t)c.pc * (uint32_t)sizeof(real);
-    const uint32_t vlam = (uint32_t)c.row * b.lrow + (uint32_t)c.pc * 8u;
-    const uint32_t vpair = vrow + 2u * (uint32_t)c.pc * (uint32_t)sizeof(real) + pair_in_row(b, 4 * NS * h);
+    const PatchOffsets o = patch_offsets(c, b, (int)sizeof(real), LPC, h);
     real x[NS][8], x0;
     double lc;
 #pragma unroll
-    for (int i = 0; i < 4 * NS; ++i) bload2(x[i >> 2][i & 3], x[i >> 2][(i & 3) + 4], fin, vpair, (uint32_t)i * b.pair);
-    bload(x0, fin, vrest, 0u);
-    bload(lc, lin, vlam, 0u);
-    const real om = omega_at<real, TAUF>(dp, (uint32_t)c.row * b.rest + (uint32_t)c.pc * (uint32_t)sizeof(real), 0u);
+    for (int i = 0; i < 4 * NS; ++i) bload2(x[i >> 2][i & 3], x[i >> 2][(i & 3) + 4], fin, o.pair, (uint32_t)i * b.pair);
+    bload(x0, fin, o.rest, 0u);
+    bload(lc, lin, o.lam, 0u);
+    const real om = omega_at<real, TAUF>(dp, o.om, 0u);
     // this ring's row of the moment inversion, read again in every step
     __shared__ double Arow[16];
     if (t < 16) Arow[t] = dp->A[t];
@@ -193,10 +190,10 @@ __global__ __launch_bounds__(NT, 1) void k_patch(const SolveDesc *descs, const u
     if (c.own) {
 #pragma unroll
         for (int i = 0; i < 4 * NS; ++i)
-            bstore2(x[i >> 2][i & 3], x[i >> 2][(i & 3) + 4], fout, vpair, (uint32_t)i * b.pair);
+            bstore2(x[i >> 2][i & 3], x[i >> 2][(i & 3) + 4], fout, o.pair, (uint32_t)i * b.pair);
         if (h == 0) {
-            bstore(x0, fout, vrest, 0u);
-            bstore(lc, lout, vlam, 0u);
+            bstore(x0, fout, o.rest, 0u);
+            bstore(lc, lout, o.lam, 0u);
         }
     }
 }

@@ -50,7 +50,9 @@ Layout pdbm::layout_of(const pdbm_params &p, int rows, bool alone)
     L.esz = p.precision == PDBM_FP32 ? sizeof(float) : sizeof(double);
     L.pitch = pitch_of(p.ntheta);
     L.rows = rows;
-    L.nwaves = rows == PATCHES ? patches(p, alone).ntiles : solve_waves(p.nr, p.ntheta, rows);
+    const int one = rows_one(p, rows, alone);
+    L.nwaves = std::max(rows == PATCHES ? patches(p, alone).ntiles : solve_waves(p.nr, p.ntheta, rows),
+                        one == PATCHES ? 0 : solve_waves(p.nr, p.ntheta, one));
     L.cblocks = cell_blocks(p.nr, p.ntheta);
     const size_t cells_p = (size_t)p.nr * L.pitch;
     L.f = align256((size_t)NQ * cells_p * L.esz);
@@ -101,13 +103,30 @@ PatchGeom pdbm::patches(const pdbm_params &p, bool alone)
 // overrides it (tuning).  Shorter blocks than FUSE_ROWS make no more than
 // MOST_WAVES wavefronts, whose drift partial sums a solve of
 // pdbm_create_noalloc has room for; beyond, they gain less than 3 %.
+static constexpr int64_t MOST_WAVES = 4096;
 int pdbm::rows_per_wave(const pdbm_params &p)
 {
-    constexpr int64_t MOST_WAVES = 4096;
     if (patches(p, true).threads > 0) return PATCHES;
     if (rows_env() > 0) return rows_env();
     return best_rows([&](int r) { return (int64_t)solve_waves(p.nr, p.ntheta, r); }, p.precision == PDBM_FP32,
                      MOST_WAVES);
+}
+
+// A launch of one step alone on the GPU has blocks of its own: 300 x 300 in
+// blocks of 2, 3 and 5 rows took 16.3, 21.1 and 28.4 us in float64, 4000 x 25
+// in blocks of 2 and of the pairs' 4 rows 17.1 and 18.4 us in float32.  Of
+// grids on patches it marches those that take more than two rounds of them
+// and make one of wavefronts of 2 rows: 300 x 300 16.3 against 19.0 us
+// (float64) and 10.4 against 13.9 (float32); 260 x 260, two rounds, 14.9
+// against 13.4 and 10.1 against 10.1; 700 x 150, 3 rows, 22.1 against 19.5.
+int pdbm::rows_one(const pdbm_params &p, int rows, bool alone)
+{
+    if (!alone || rows_env() > 0 || p.ntheta == 1) return rows;
+    const bool fp32 = p.precision == PDBM_FP32;
+    if (rows == PATCHES && !single_steps_march(p.nr, p.ntheta, p.sector, fp32, patches(p, alone))) return PATCHES;
+    const int one =
+        best_rows([&](int r) { return (int64_t)solve_waves(p.nr, p.ntheta, r); }, fp32, MOST_WAVES, MORE_SINGLE);
+    return rows == PATCHES && one > FEWEST_ROWS ? PATCHES : one;
 }
 
 // Largest |C_r| + |C_theta| over the grid for the fastest speed: the
@@ -302,6 +321,7 @@ int Solve::init(const pdbm_params &pp, const pdbm_ic *ic, void *workspace, size_
     hd.disc = p.r_min == 0.0;
     hd.reacts = (p.w1 > 0.0 || p.w2 > 0.0) ? 1 : 0;
     hd.rows = rows;
+    hd.rows1 = rows_one(p, rows, alone);
     if (rows == PATCHES) hd.patch = patches(p, alone);
     hd.nwaves = L.nwaves;
     hd.nstrip = (p.ntheta + STRIP - 1) / STRIP;
@@ -509,33 +529,33 @@ int pdbm_step(pdbm_solver *h, int64_t nsteps)
     int64_t launches = 0;
     if (cap != hipStreamCaptureStatusNone) launches = patch_launches(nsteps, most, s.p.ntheta == 1 ? COL_K : 2);
     for (int64_t i = 0; i < nsteps;) {
-        if (s.patched()) {
-            // as a column's launches; captured, of about the same number of steps each
-            int nk = (int)std::min<int64_t>(most, nsteps - i);
-            if (launches > 0) nk = (int)((nsteps - i + launches - 1) / launches--);
-            HIPCHK(launch_patch(s.dd, nullptr, s.waves(), s.hd.patch.threads, s.hd.patch.lanes, nullptr, s.step, nullptr, s.flip, nk,
-                                s.fp32, s.tauf(), h->st));
+        int nk = (int)std::min<int64_t>(most, nsteps - i);
+        if (launches > 0) nk = (int)((nsteps - i + launches - 1) / launches--);  // about as many in each
+        if (s.patched() && (nk > 1 || s.hd.rows1 == PATCHES)) {
+            // as a column's launches
+            const PatchGeom &g = s.hd.patch;
+            HIPCHK(launch_patch(s.dd, nullptr, s.waves(), g.threads, g.lanes, nullptr, s.step, nullptr, s.flip, nk, s.fp32,
+                                s.tauf(), h->st));
             s.step += nk;
             s.flip ^= (nk + 1) & 1;
             i += nk;
         } else if (column) {
             // a single column: up to COL_K steps per launch; the state moves
             // to the other buffer, which toggles the parity unless nk is odd
-            const int nk = (int)std::min<int64_t>(COL_K, nsteps - i);
             HIPCHK(launch_column(s.dd, nullptr, s.waves(), nullptr, s.step, nullptr, s.flip, nk, s.fp32, s.tauf(),
                                  h->st));
             s.step += nk;
             s.flip ^= (nk + 1) & 1;
             i += nk;
-        } else if (pairs && nsteps - i >= 2) {
+        } else if (pairs && nk == 2) {
             HIPCHK(launch_step2(s.dd, nullptr, s.waves(), nullptr, s.step, nullptr, s.flip, false, s.fp32, s.tauf(),
                                 s.mixed(), h->st));
             s.step += 2;
             s.flip ^= 1;
             i += 2;
         } else {
-            HIPCHK(launch_step(s.dd, nullptr, s.waves(), nullptr, s.step, nullptr, s.flip, s.fp32, s.mixed(), s.tauf(),
-                               h->st));
+            HIPCHK(launch_step(s.dd, nullptr, s.waves_one(), nullptr, s.step, nullptr, s.flip, s.fp32, s.mixed(),
+                               s.tauf(), h->st));
             s.step += 1;
             i += 1;
         }

@@ -941,6 +941,17 @@ __device__ __forceinline__ void march(DescPtr dp, const StepBufs &bufs, int stri
     }
 }
 
+// Clears the partial sums of a record that a launch of n wavefronts or patches
+// leaves unused, where others of the solve's launches have more: part are the
+// sums of the launch's number lt.
+__device__ __forceinline__ void clear_rest(DescPtr dp, double *part, int lt, int n)
+{
+    for (int w = lt + n; w < dp->nwaves; w += n) {
+        part += 5 * (size_t)n;
+        for (int i = 0; i < 5; ++i) part[i] = 0.0;
+    }
+}
+
 // Whether step `s` of a solve makes a drift record.
 __device__ __forceinline__ bool records(DescPtr dp, int64_t s)
 {

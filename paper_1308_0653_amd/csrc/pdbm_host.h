@@ -54,23 +54,25 @@ inline double launch_rounds(int64_t waves, bool fp32)
 }
 // Rows per wavefront of the marching kernels for a launch of waves(r)
 // wavefronts in blocks of r rows: long blocks compute and read the fewest
-// rows twice, but a wavefront of r rows takes about 2 r + 5 rows' time (both
-// steps' rows, the two beside the block, its start), whole rounds of which
-// make the launch.  Between FEWEST_ROWS and FUSE_ROWS rows, more than `most`
+// rows twice, but a wavefront of r rows takes about the time of r + more
+// (a pair of steps 2 r + 5 rows, both steps' and the two beside the block and
+// its start, MORE_PAIR; a single step r + 2), whole rounds of which make the
+// launch.  Between FEWEST_ROWS and FUSE_ROWS rows, more than `most`
 // wavefronts only where FUSE_ROWS needs them.  With the fewest rows that make
 // one round, else 16, 1100 x 1024 took 220 us per two steps in float64 and
 // takes 161 (1.92 rounds of 9 rows instead of 1.08 of 16), 1500 x 1024 229
 // and 200; in float32 2400 x 1024 207 and 182, 1280 x 1800 217 and 187.
 constexpr int FEWEST_ROWS = 2;
+constexpr double MORE_PAIR = 2.5, MORE_SINGLE = 2.0;
 template <class Waves>
-int best_rows(Waves waves, bool fp32, int64_t most)
+int best_rows(Waves waves, bool fp32, int64_t most, double more = MORE_PAIR)
 {
     int best = FUSE_ROWS;
     double least = 0.0;
     for (int r = FUSE_ROWS; r >= FEWEST_ROWS; --r) {
         const int64_t n = waves(r);
         if (r < FUSE_ROWS && n > most) break;
-        const double t = (2 * r + 5) * launch_rounds(n, fp32);
+        const double t = (r + more) * launch_rounds(n, fp32);
         if (r == FUSE_ROWS || t < least) {
             best = r;
             least = t;
@@ -85,6 +87,8 @@ Layout layout_of(const pdbm_params &p, int rows, bool alone);
 // fixes them).
 int batch_rows(const pdbm_params &p);
 int batch_rows_env();
+// Rows per wavefront of the one-step launches of such a solve, or PATCHES.
+int rows_one(const pdbm_params &p, int rows, bool alone);
 // Patches of a solve that rows_per_wave (alone) or batch_rows gives them.
 PatchGeom patches(const pdbm_params &p, bool alone);
 class Solve;
@@ -133,13 +137,16 @@ class Solve {
     // Whether its launches step patches of the grid, up to geom.k steps each.
     bool patched() const { return hd.patch.threads > 0; }
     int patch_steps() const;  // ... of this many steps at most
-    int waves() const { return hd.nwaves; }
+    // Wavefronts or patches of its launches, and wavefronts of those that
+    // march a single step.
+    int waves() const { return patched() ? hd.patch.ntiles : solve_waves(p.nr, p.ntheta, hd.rows); }
+    int waves_one() const { return solve_waves(p.nr, p.ntheta, hd.rows1); }
     // Marches blocks of `rows` rows from now on (a member of a pack).  A
     // solve that makes drift records keeps the blocks it has memory for the
     // partial sums of.
     void set_rows(int rows)
     {
-        hd.rows = p.diag_every > 0 ? L.rows : rows;
+        hd.rows = hd.rows1 = p.diag_every > 0 ? L.rows : rows;
         hd.nwaves = waves_at(rows);
     }
     int waves_at(int rows) const { return solve_waves(p.nr, p.ntheta, p.diag_every > 0 ? L.rows : rows); }

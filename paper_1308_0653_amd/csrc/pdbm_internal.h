@@ -55,11 +55,13 @@ struct SolveDesc {
     double *lam[2];     // [nr][pitch]
     const double2 *cs;  // [ntheta] (cos, sin) of theta_j above its octant (pdbm_offsets.h)
     SolveState *state;
-    double *wpart;      // [PART_RING][nwaves][5] per-wavefront drift partial sums, slot (record % PART_RING)
+    double *wpart;      // [PART_RING][nwaves][5] drift partial sums per wavefront or patch, slot (record % PART_RING);
+                        // a launch of fewer clears the rest of the slot
     pdbm_diag *hist;    // [HIST_CAP] drift reports, record k for step k * diag_every
     int32_t nr, nt, pitch, sector;
     int32_t m, n, disc, reacts;          // disc: r_min == 0; reacts: w1+w2 > 0
-    int32_t rows, nwaves, nstrip, diag_every;  // rows marched by one wavefront; its wavefronts
+    int32_t rows, rows1, nwaves, nstrip, diag_every;  // rows marched by one wavefront, also in one-step launches;
+                                                      // wavefronts or patches of a launch, at most
     int64_t rstride;  // elements between consecutive r rows of f (= NQ * pitch)
     int64_t nsteps;   // the solve stops advancing once it has taken this many steps
     double r_min, dr, dth;

@@ -368,6 +368,16 @@ inline PatchGeom patch_geom(int nr, int nt, int sector, bool fp32, bool alone, b
     }
     return best;
 }
+// Whether single steps of a grid on patches `g`, alone on the GPU, are marched
+// all the same (rows_one): the 16 x 16 shape with k = 2 takes more than two
+// rounds, and the patches' kernel clears what a record of the two forms leaves
+// unused (those of four lanes to a cell, for smaller grids, need not).
+__host__ __device__ constexpr bool marched_beside(int lanes) { return lanes == 2; }
+inline bool single_steps_march(int nr, int nt, int sector, bool fp32, const PatchGeom &g)
+{
+    return nt > 1 && marchable(nt, sector) && marched_beside(g.lanes) &&
+           patches_of(fp32 ? PATCH_FP32[0] : PATCH_FP64[0], nr, nt).ntiles > 256 * 2;
+}
 struct PatchCell {
     int row, pc, ext;    // its row, physical column, column before wrapping
     int lr, lc, nrow, ncol;  // place within the patch, rows and columns of the patch

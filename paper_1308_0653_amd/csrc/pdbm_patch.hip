@@ -139,14 +139,18 @@ __global__ __launch_bounds__(NT, 1) void k_patch(const SolveDesc *descs, const u
         __syncthreads();
         if (rec && t == 0) {
             double *out = dp->wpart + (((size_t)((step / dp->diag_every) % PART_RING)) * dp->nwaves + tile) * 5;
-            // (of 12 wavefronts all at once they spill to scratch memory; one
-            // at a time of 4, 400 steps of a 20000-row column took 3 % longer)
-            constexpr int AT_ONCE = NT > 512 ? 1 : 5;
+            // (of 12 wavefronts and two lanes to a cell all at once they spill
+            // to scratch memory; one at a time of 4 wavefronts, 400 steps of a
+            // 20000-row column took 3 % longer)
+            constexpr int AT_ONCE = NT > 512 && LPC == 2 ? 1 : 5;
 #pragma unroll AT_ONCE
             for (int i = 0; i < 5; ++i) {
                 double s = part[0][i];
                 for (int w = 1; w < NT / 64; ++w) s += part[w][i];
                 out[i] = s;
+            }
+            if constexpr (marched_beside(LPC)) {
+                if (!tiles) clear_rest(dp, out, tile, g.ntiles);
             }
         }
         if (update) {

@@ -342,7 +342,7 @@ __global__ __launch_bounds__(BLOCK, StepOcc<real>::waves) void k_step(const Solv
         // one theta column: lanes along r
         radial_block<real, TAUF>(dp, bufs, lt, prev[threadIdx.x >> 6], red, diag);
     } else {
-        const int rows = dp->rows, nstrip = dp->nstrip;
+        const int rows = dp->rows1, nstrip = dp->nstrip;
         const int rb = lt / nstrip, strip = lt - rb * nstrip;
         const int i0 = rb * rows;
         const int i1 = min(i0 + rows, dp->nr);
@@ -354,9 +354,11 @@ __global__ __launch_bounds__(BLOCK, StepOcc<real>::waves) void k_step(const Solv
         double v[5];
 #pragma unroll
         for (int i = 0; i < 5; ++i) v[i] = wave_sum(red[i]);
-        if ((threadIdx.x & 63) == 0)
+        if ((threadIdx.x & 63) == 0) {
 #pragma unroll
             for (int i = 0; i < 5; ++i) part[i] = v[i];
+            if (!tiles) clear_rest(dp, part, lt, ntiles);
+        }
     }
 }
 

@@ -654,6 +654,7 @@ __global__ __launch_bounds__(BLOCK, Step2Occ<real>::waves) void k_step2(const So
             double *part = dp->wpart + ((size_t)slot * dp->nwaves + lt) * 5;
 #pragma unroll
             for (int i = 0; i < 5; ++i) part[i] = v[s][i];
+            if (!tiles) clear_rest(dp, part, lt, ntiles);
         }
     }
 }

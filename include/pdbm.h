@@ -42,7 +42,8 @@
  *                          columns than octants); above 16 disables two-step
  *                          launches.
  *   PDBM_BATCH_ROWS=n      n rows per wavefront of packed grids of more
- *                          than one column (else 2 to 16, by what fills the
+ *                          than one column (else 16 of those with drift
+ *                          records, 2 to 16 of the others, by what fills the
  *                          device); above 16 disables two-step launches.
  */
 #ifndef PDBM_H
@@ -200,7 +201,7 @@ int pdbm_create(const pdbm_params *p, const pdbm_ic *ic, void *workspace, size_t
  * start at zero is cleared here, on the solver's stream.
  * Errors: as pdbm_create; PDBM_ENOMEM if the state buffer is too small or
  * the solve needs more than PDBM_SCRATCH_BYTES of auxiliary memory (about
- * 2048 x 2048 cells). */
+ * 2048 x 2048 cells, or 100 thousand rows of up to 64 columns). */
 enum { PDBM_SCRATCH_BYTES = 16 << 20 };
 int pdbm_create_noalloc(const pdbm_params *p, const pdbm_ic *ic, void *state, size_t *state_bytes, void *stream,
                         pdbm_solver **out);
@@ -234,7 +235,7 @@ int pdbm_set_tau_async(pdbm_solver *s, const void *tau_device);
  * waiting.  Every diag_every-th step also records the drift report of the
  * state it starts from.  A launch takes two steps of a solve with ntheta > 1
  * (one pass over f for both; an odd count ends with a single step) or, of a
- * small grid, 2 to 4 steps; solves with a single theta column take up to 24
+ * small grid, up to 2 to 4 steps; solves with a single theta column take up to 24
  * steps per launch, of more than about 40 thousand rows up to 8.  The states
  * after every call are those of Sec. II.C's scheme, bit for bit the same
  * however the steps are cut into calls and launches.  A call of a multiple of

@@ -23,8 +23,9 @@ constexpr int COL_W = STRIP - 2 * COL_K;  // rows a wavefront owns in a single-c
 // Layout of f within one r row (33 * pitch elements): the rest particle's
 // plane [pitch], then the 16 pairs of opposite directions of each speed, pair
 // c = 4 (k - 1) + (i mod 4) holding directions i and i + 4 (relative to the
-// column's octant, see pdbm_offsets.h) interleaved per column ([pitch][2]).  The pair of a cell is one 16-byte (float64) or
-// 8-byte (float32) access, and the two members are updated together.
+// column's octant, see pdbm_offsets.h) interleaved per column ([pitch][2]).
+// The pair of a cell is one 16-byte (float64) or 8-byte (float32) access, and
+// the two members are updated together.
 __host__ __device__ constexpr int pair_of(int q) { return 4 * ((q - 1) / 8) + ((q - 1) & 3); }
 __host__ __device__ constexpr int member_of(int q) { return ((q - 1) & 7) >> 2; }
 // Element offset of velocity q, column col, from the start of its r row.

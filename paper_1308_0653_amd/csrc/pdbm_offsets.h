@@ -284,7 +284,7 @@ __host__ __device__ inline ColumnOffsets column_offsets(int nr, const RowBytes &
 // grid and holds them with a halo of k rows and columns, `lanes` lanes to a
 // cell, cells row by row.  Rows are clipped to the grid; with cols >= nt
 // the patch holds the whole ring and has no column halo.
-// Shapes of patches a solve alone on the GPU chooses from (choose_patches):
+// Shapes of patches a solve alone on the GPU chooses from (patch_geom):
 // the cells of a workgroup (rows x cols, halo included), its threads, lanes
 // per cell and halo k, and what a launch takes in ns, t0 + rounds c with 256
 // workgroups to a round, one per CU, fitted to grids of 100 x 100 to 400 x

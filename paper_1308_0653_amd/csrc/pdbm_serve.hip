@@ -1,14 +1,14 @@
 // Packed launches over many independent solves: a fixed batch (pdbm_batch)
 // and continuous batching of a request stream (pdbm_server).
 //
-// Every member keeps its own state resident in HBM.  One launch of the step
-// kernel advances all members by one step: its wavefront tiles are the
-// concatenation of the members' tiles, mapped back to (member, tile) by a
-// device table.  Member i takes step bases[i] + (the launch's place in the
-// chunk); a small kernel at the end of a chunk adds up the chunk's drift
-// records and advances bases[] by the chunk, so a chunk of launches is
-// captured once in a hipGraph and replayed; membership changes only between
-// chunks.  Members never read each other's data, so a solve's fields are the
+// Every member keeps its own state resident in HBM.  One launch advances all
+// members of a kind (marched grids, single columns, grids on patches) by two
+// steps or as many as their kernel takes: its tiles are the concatenation of
+// the members' tiles, mapped back to (member, tile) by a device table.  Member
+// i starts a launch at step bases[i] + (the steps of the chunk before it);
+// small kernels at the end of a chunk add up its drift records and advance
+// bases[] by the chunk, so a chunk of launches is captured once in a hipGraph
+// and replayed; membership changes only between chunks.  Members never read each other's data, so a solve's fields are the
 // same bit for bit alone or in any mix.
 #include <hip/hip_runtime.h>
 #include <sys/mman.h>

@@ -8,6 +8,10 @@
 namespace pdbm {
 namespace {
 
+// Multiply-adds are written out here too: with every product of k_noneq
+// rounded by itself a call took 6.4 us instead of 5.4 for grids of up to 8000
+// cells, and 67 instead of 58 us for a 1024 x 1024 float32 state.
+
 // -------------------------------------------------------------- moments --
 template <typename real>
 __global__ __launch_bounds__(BLOCK) void k_moments(SolveDesc d, int cur, double *out, DiagCtl dc)
@@ -27,14 +31,15 @@ __global__ __launch_bounds__(BLOCK) void k_moments(SolveDesc d, int cur, double 
         real rho, jx, jy, e;
         raw_moments(f, rho, jx, jy, e);
         const double rd = (double)rho;
-        const double ux = (double)(jx / rho), uy = (double)(jy / rho);
-        const double T = (double)(e / rho - (real)0.5 * ((jx / rho) * (jx / rho) + (jy / rho) * (jy / rho)));
+        const real u = jx / rho, v = jy / rho;
+        const double ux = (double)u, uy = (double)v;
+        const double T = (double)fma((real)-0.5, fma(u, u, v * v), e / rho);
         const double2 cs = d.cs[jt];
         const double lam = d.lam[cur][idx];
         if (out) {
             out[c] = rd;
-            out[(size_t)ncell + c] = ux * cs.x + uy * cs.y;
-            out[2 * (size_t)ncell + c] = -ux * cs.y + uy * cs.x;
+            out[(size_t)ncell + c] = fma(ux, cs.x, uy * cs.y);
+            out[2 * (size_t)ncell + c] = fma(uy, cs.x, -(ux * cs.y));
             out[3 * (size_t)ncell + c] = T;
             out[4 * (size_t)ncell + c] = rd * T;
             out[5 * (size_t)ncell + c] = lam;
@@ -88,13 +93,13 @@ __global__ __launch_bounds__(BLOCK) void k_noneq(SolveDesc d, int cur, double *o
     double rho, jx, jy, e;
     raw_moments(f, rho, jx, jy, e);
     const double ux = jx / rho, uy = jy / rho;
-    const double T = e / rho - 0.5 * (ux * ux + uy * uy);
+    const double T = fma(-0.5, fma(ux, ux, uy * uy), e / rho);
     double g[NQ];
     equilibrium<double>(d.A, rho, ux, uy, T, g);
 #pragma unroll
     for (int q = 0; q < NQ; ++q) g[q] = f[q] - g[q];
     const double2 cs = d.cs[jt];
-    const double ur = ux * cs.x + uy * cs.y, ut = -ux * cs.y + uy * cs.x;
+    const double ur = fma(ux, cs.x, uy * cs.y), ut = fma(uy, cs.x, -(ux * cs.y));
     // cos and sin of the directions i pi/4
     constexpr double DX[8] = {1.0, SQH, 0.0, -SQH, -1.0, -SQH, 0.0, SQH};
     constexpr double DY[8] = {0.0, SQH, 1.0, SQH, 0.0, -SQH, -1.0, -SQH};
@@ -106,24 +111,24 @@ __global__ __launch_bounds__(BLOCK) void k_noneq(SolveDesc d, int cur, double *o
         double vr = 0.0, vt = 0.0;
         if (q > 0) {
             const int k = 1 + (q - 1) / 8, i = (q - 1) % 8;
-            vr = speed(k) * (DX[i] * cs.x + DY[i] * cs.y);  // v cos(i pi/4 - theta)
-            vt = speed(k) * (DY[i] * cs.x - DX[i] * cs.y);  // v sin(i pi/4 - theta)
+            vr = speed(k) * fma(DX[i], cs.x, DY[i] * cs.y);     // v cos(i pi/4 - theta)
+            vt = speed(k) * fma(DY[i], cs.x, -(DX[i] * cs.y));  // v sin(i pi/4 - theta)
         }
         const double cr = vr - ur, ct = vt - ut;
-        const double h = 0.5 * (cr * cr + ct * ct);
+        const double h = 0.5 * fma(cr, cr, ct * ct);
         const double grr = g[q] * cr, gtt = g[q] * ct;
-        m[0] += grr * cr;
-        m[1] += grr * ct;
-        m[2] += gtt * ct;
-        m[3] += grr * cr * cr;
-        m[4] += grr * cr * ct;
-        m[5] += grr * ct * ct;
-        m[6] += gtt * ct * ct;
-        m[7] += h * grr;
-        m[8] += h * gtt;
-        m[9] += h * grr * cr;
-        m[10] += h * grr * ct;
-        m[11] += h * gtt * ct;
+        m[0] = fma(grr, cr, m[0]);
+        m[1] = fma(grr, ct, m[1]);
+        m[2] = fma(gtt, ct, m[2]);
+        m[3] = fma(grr * cr, cr, m[3]);
+        m[4] = fma(grr * cr, ct, m[4]);
+        m[5] = fma(grr * ct, ct, m[5]);
+        m[6] = fma(gtt * ct, ct, m[6]);
+        m[7] = fma(h, grr, m[7]);
+        m[8] = fma(h, gtt, m[8]);
+        m[9] = fma(h * grr, cr, m[9]);
+        m[10] = fma(h * grr, ct, m[10]);
+        m[11] = fma(h * gtt, ct, m[11]);
     }
 #pragma unroll
     for (int k = 0; k < NONEQ; ++k) out[(size_t)k * ncell + c] = m[k];

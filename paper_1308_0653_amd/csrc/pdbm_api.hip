@@ -8,6 +8,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <memory>
 #include <new>
 #include <string>
 #include <vector>
@@ -648,13 +649,14 @@ int pdbm_diag_history(pdbm_solver *h, pdbm_diag *out, int32_t cap, int32_t *n)
 // with `wide` in float64) and lam [nr][ntheta], and such arrays into buffer
 // `buf`; either pointer may be NULL.  The rearrangement runs on the device
 // through the other pair of buffers: f there holds every plane in the solve's
-// precision and, of a float32 solve, a third of them in float64.  Synchronous.
-static int planes_per_copy(const Solve &s, bool wide) { return s.fp32 && wide ? NQ / 3 : NQ; }
+// precision and, of a float32 solve, a half of them in float64, or more where
+// rows are padded.  Synchronous.
+static int planes_per_copy(const Solve &s, size_t plane) { return (int)std::min<size_t>(NQ, s.L.f / plane); }
 
 static int state_to_host(const Solve &s, void *f, double *lam, bool wide, hipStream_t st)
 {
-    const int cur = s.cur(), most = planes_per_copy(s, wide);
     const size_t ncell = (size_t)s.p.nr * s.p.ntheta, plane = ncell * (wide ? sizeof(double) : s.L.esz);
+    const int cur = s.cur(), most = planes_per_copy(s, plane);
     void *stage = s.hd.f[cur ^ 1];
     double *lstage = s.hd.lam[cur ^ 1];
     if (lam) {
@@ -672,8 +674,8 @@ static int state_to_host(const Solve &s, void *f, double *lam, bool wide, hipStr
 
 static int state_to_device(const Solve &s, int buf, const void *f, const double *lam, bool wide, hipStream_t st)
 {
-    const int most = planes_per_copy(s, wide);
     const size_t ncell = (size_t)s.p.nr * s.p.ntheta, plane = ncell * (wide ? sizeof(double) : s.L.esz);
+    const int most = planes_per_copy(s, plane);
     void *stage = s.hd.f[buf ^ 1];
     double *lstage = s.hd.lam[buf ^ 1];
     if (lam) {
@@ -689,12 +691,26 @@ static int state_to_device(const Solve &s, int buf, const void *f, const double 
     return PDBM_OK;
 }
 
+// Values of a float32 f at most that are widened here: more launches and
+// copies cost more (8 x 64 cells 116 us in thirds, 48 this way; 32 x 64 139
+// and 63).
+static constexpr size_t WIDEN_HERE = 33 * 2048;
+
 extern "C" {
 
 int pdbm_read_f(pdbm_solver *h, double *f, double *lam)
 {
     if (!h) return fail(PDBM_EINVAL, "NULL solver");
-    return state_to_host(h->s, f, lam, true, h->st);
+    const Solve &s = h->s;
+    const size_t n = (size_t)NQ * s.p.nr * s.p.ntheta;
+    if (s.fp32 && f && n <= WIDEN_HERE) {
+        if (std::unique_ptr<float[]> tmp{new (std::nothrow) float[n]}) {
+            const int rc = state_to_host(s, tmp.get(), lam, false, h->st);
+            if (rc == PDBM_OK) std::copy(tmp.get(), tmp.get() + n, f);
+            return rc;
+        }
+    }
+    return state_to_host(s, f, lam, true, h->st);
 }
 
 int pdbm_write_f(pdbm_solver *h, const double *f, const double *lam, int64_t step)

@@ -1,6 +1,7 @@
 // CPU check of the launches that pdbm_step makes of single solves, on the
 // model GPU of model_gpu.h: how many steps each takes, in which kernel, of how
-// many wavefronts or patches.  Exit status 0 when every check holds.
+// many wavefronts or patches; and of the copies that reading the raw state
+// takes.  Exit status 0 when every check holds.
 #include "model_gpu.h"
 
 namespace {
@@ -43,10 +44,44 @@ void call(int nr, int nt, int precision, int steps, const std::string &want, boo
     }
 }
 
+// Copies of one read of f and lambda.
+void reads(int nr, int nt, int precision, int want)
+{
+    pdbm_params p{};
+    p.nr = nr;
+    p.ntheta = nt;
+    p.sector = 8;
+    p.precision = precision;
+    p.r_min = 0.3;
+    p.r_max = 1.0;
+    p.dt = 1e-9;
+    p.tau = 1e-3;
+    pdbm_solver *s = nullptr;
+    std::vector<double> f((size_t)33 * nr * nt), lam((size_t)nr * nt);
+    if (pdbm_create(&p, nullptr, nullptr, 0, nullptr, &s) == PDBM_OK) {
+        gpu.copies = 0;
+        gpu.logging = true;
+        (void)pdbm_read_f(s, f.data(), lam.data());
+        gpu.logging = false;
+        pdbm_destroy(s);
+    }
+    if (gpu.copies != want) {
+        std::fprintf(stderr, "FAILED read of %d x %d precision %d: %d copies, not %d\n", nr, nt, precision, gpu.copies, want);
+        fails++;
+    }
+}
+
 }  // namespace
 
 int main()
 {
+    // lambda, and f at once: in its own precision, or as much of it in float64 as the idle buffer holds
+    reads(64, 64, PDBM_FP64, 2);
+    reads(8, 64, PDBM_FP32, 2);
+    reads(32, 64, PDBM_FP32, 2);
+    reads(33, 64, PDBM_FP32, 4);
+    reads(400, 20, PDBM_FP32, 2);
+    reads(100, 100, PDBM_FP32, 3);
     // on patches, single steps too up to two rounds of them (260 x 260: 484 of 12 x 12 cells) ...
     call(64, 64, PDBM_FP64, 1, "p1x256");
     call(260, 260, PDBM_FP64, 3, "p2x484 p1x484");

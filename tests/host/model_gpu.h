@@ -31,6 +31,7 @@ struct Gpu {
     void *capturing = nullptr;
     long allocated = 0;
     bool logging = false;
+    int copies = 0;
     struct Launch {
         char kernel;  // m, d: one or two steps marched; c: columns; p: patches
         int tiles, steps;
@@ -99,6 +100,7 @@ hipError_t hipFree(void *p)
 hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipStream_t)
 {
     std::memcpy(d, s, n);
+    if (gpu.logging) ++gpu.copies;
     return hipSuccess;
 }
 hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) { return *s = (hipStream_t)handle(), hipSuccess; }

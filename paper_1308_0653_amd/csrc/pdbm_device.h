@@ -762,17 +762,20 @@ __device__ __forceinline__ void row_or_ghost(const Strip<real, MIXED> &S, int ro
 
 // One row of one strip: moments, F_k(T), f^eq, BGK + chemical term, Cochran
 // lambda, donor-cell fluxes of f and lambda.  fc: row i.  Marching outward
-// (down = false): prev (LDS, this lane's column) holds row i-1 and fn row
-// i+1; marching inward the roles swap.  prev is replaced by row i as it is
-// consumed.  mr[dd] / mt[dd]: which side is upwind for direction dd (its
-// opposite dd+4 takes the other side); evaluated from the angle here, for
-// either marching direction, which costs selects the two-step kernel avoids.
-template <typename real, bool MIXED, bool TAUF>
+// (DOWN = false): prev (LDS, this lane's column) holds row i-1 and fn row
+// i+1; marching inward the roles swap.  The upwind radial side follows from
+// the direction (below for 0, 1, 2, 7), so only the 16 directions that come
+// from the row behind pass through prev, replaced by row i as they are
+// consumed (with both rows selected between per lane, a step of 330 x 333 took
+// 17.1 us in float64, 16.6 this way; a packed one of 300 x 200, 87 and 81).  mt[dd]: which side is upwind in theta for
+// direction dd (its opposite dd+4 takes the other one), evaluated from the
+// angle.
+template <typename real, bool MIXED, bool TAUF, bool DOWN>
 __device__ __forceinline__ void update_row(const Strip<real, MIXED> &S, int ir, real (*prev)[64], const real fc[NQ],
                                            const real fn[NQ], const real hf[2], double hlam, double lbehind,
                                            double lc, double lahead,
-                                           const bool mr[4], const bool mt[4], const real acr[4], const real ctv[4],
-                                           bool lr_behind, double2 cs, real om, double red[5], bool diag)
+                                           const bool mt[4], const real acr[4], const real ctv[4], double2 cs,
+                                           real om, double red[5], bool diag)
 {
     const DescPtr dp = S.dp;
     // the cell's exp(-dt/tau): with TAUF `om`, loaded by march a row ahead
@@ -825,10 +828,14 @@ __device__ __forceinline__ void update_row(const Strip<real, MIXED> &S, int ir, 
                 const int dir = dd + 4 * sgn, q = base + dir;
                 const real x = fc[q];
                 // upwind neighbours: C >= 0 takes the lower one (Sec. II.C)
-                const real behind = prev[q][lane];
-                prev[q][lane] = x;
-                const bool rb = sgn == 0 ? mr[dd] : !mr[dd];
-                const real nbr = rb ? behind : fn[q];
+                const bool low = dir <= 2 || dir == 7;
+                real nbr;
+                if (low != DOWN) {
+                    nbr = prev[4 * (k - 1) + dd][lane];
+                    prev[4 * (k - 1) + dd][lane] = x;
+                } else {
+                    nbr = fn[q];
+                }
                 // both shifts and both halo values are taken by every lane
                 // (a DPP read of a lane switched off by a branch would return
                 // 0), then selected; lanes 0 and 63 take the halo columns
@@ -862,7 +869,7 @@ __device__ __forceinline__ void update_row(const Strip<real, MIXED> &S, int ir, 
     const double hll = lane_value(hlam, 0), hlr = lane_value(hlam, 1);
     const double lleft = lane == 0 ? hll : sll;
     const double lright = lane == 63 ? hlr : slr;
-    const double lr = (urp >= 0.0) == lr_behind ? lbehind : lahead;
+    const double lr = (urp >= 0.0) != DOWN ? lbehind : lahead;
     const double lt = utp >= 0.0 ? lleft : lright;
     bstore(C.lambda(dp, lc, urp, utp, dp->dt_dr, ktd, lr, lt), S.lout, S.vols, (uint32_t)ir * S.lrow_bytes);
 
@@ -872,10 +879,10 @@ __device__ __forceinline__ void update_row(const Strip<real, MIXED> &S, int ir, 
 }
 
 // Work of one wavefront: strip `strip`, rows [i0, i1), marched outward or,
-// with `down`, inward.  prev: this wavefront's [NQ][64] LDS slots.
-template <typename real, bool MIXED, bool TAUF>
-__device__ __forceinline__ void march(DescPtr dp, const StepBufs &bufs, int strip, int i0, int i1, bool down,
-                                      real (*prev)[64], double red[5], bool diag)
+// with DOWN, inward.  prev: 16 of this wavefront's LDS slots of 64.
+template <typename real, bool MIXED, bool TAUF, bool DOWN>
+__device__ __forceinline__ void march(DescPtr dp, const StepBufs &bufs, int strip, int i0, int i1, real (*prev)[64],
+                                      double red[5], bool diag)
 {
     const Strip<real, MIXED> S(dp, bufs, strip);
     const int lane = S.lane;
@@ -883,15 +890,14 @@ __device__ __forceinline__ void march(DescPtr dp, const StepBufs &bufs, int stri
     const Polar<real> V(cs);
     const real kr = (real)dp->dt_dr;
     real acr[4];
-    bool mr[4], mt[4];
+    bool mt[4];
 #pragma unroll
     for (int dd = 0; dd < 4; ++dd) {
         acr[dd] = fabs(V.r[dd]) * kr;
-        mr[dd] = (V.r[dd] >= (real)0) != down;  // true: the upwind radial neighbour is the row behind
-        mt[dd] = V.t[dd] >= (real)0;            // true: the upwind azimuthal neighbour is lane-1
+        mt[dd] = V.t[dd] >= (real)0;  // true: the upwind azimuthal neighbour is lane-1
     }
-    const int step = down ? -1 : 1;
-    const int first = down ? i1 - 1 : i0;
+    constexpr int step = DOWN ? -1 : 1;
+    const int first = DOWN ? i1 - 1 : i0;
     const int count = i1 - i0;
     // halos of a row are gathered right after its main loads, when the
     // adjacent strips fetch the same lines (they then hit in L2)
@@ -907,7 +913,10 @@ __device__ __forceinline__ void march(DescPtr dp, const StepBufs &bufs, int stri
     if (count > 1) S.load_halo(first + step, hn, hln);
     row_or_ghost(S, first - step, fnn, lp, fc, lc);  // the row behind the first
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) prev[q][lane] = fnn[q];
+    for (int c = 0; c < 16; ++c) {
+        const int dd = c & 3, low = low_dir(dd);
+        prev[c][lane] = fnn[1 + 8 * (c >> 2) + (DOWN ? low ^ 4 : low)];
+    }
     if constexpr (TAUF) settle(oc);
     int ir = first;
     for (int n = 0; n < count; ++n, ir += step) {
@@ -918,8 +927,7 @@ __device__ __forceinline__ void march(DescPtr dp, const StepBufs &bufs, int stri
         if constexpr (TAUF) {
             if (n + 1 < count) on = omega_at<real, true>(dp, S.vo, (uint32_t)(ir + step) * S.rest_bytes);
         }
-        update_row<real, MIXED, TAUF>(S, ir, prev, fc, fn, hc, hlc, lp, lc, ln, mr, mt, acr, V.t, !down, cs, oc, red,
-                                      diag);
+        update_row<real, MIXED, TAUF, DOWN>(S, ir, prev, fc, fn, hc, hlc, lp, lc, ln, mt, acr, V.t, cs, oc, red, diag);
         oc = on;
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {

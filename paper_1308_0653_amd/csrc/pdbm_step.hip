@@ -346,7 +346,10 @@ __global__ __launch_bounds__(BLOCK, StepOcc<real>::waves) void k_step(const Solv
         const int rb = lt / nstrip, strip = lt - rb * nstrip;
         const int i0 = rb * rows;
         const int i1 = min(i0 + rows, dp->nr);
-        march<real, MIXED, TAUF>(dp, bufs, strip, i0, i1, (rb & 1) != 0, prev[threadIdx.x >> 6], red, diag);
+        if ((rb & 1) != 0)
+            march<real, MIXED, TAUF, true>(dp, bufs, strip, i0, i1, prev[threadIdx.x >> 6], red, diag);
+        else
+            march<real, MIXED, TAUF, false>(dp, bufs, strip, i0, i1, prev[threadIdx.x >> 6], red, diag);
     }
     if (diag) {
         const int64_t slot = (step / dp->diag_every) % PART_RING;

@@ -616,7 +616,10 @@ __global__ __launch_bounds__(BLOCK, Step2Occ<real>::waves) void k_step2(const So
         // one step, with the row behind in the LDS row of g
         const bool diag = records(dp, step);
         double red[5] = {0, 0, 0, 0, 0};
-        march<real, MIXED, TAUF>(dp, bufs, strip, i0, i1, (rb & 1) != 0, ga[w], red, diag);
+        if ((rb & 1) != 0)
+            march<real, MIXED, TAUF, true>(dp, bufs, strip, i0, i1, ga[w], red, diag);
+        else
+            march<real, MIXED, TAUF, false>(dp, bufs, strip, i0, i1, ga[w], red, diag);
         if (diag) {
             const int64_t slot = (step / dp->diag_every) % PART_RING;
             double *part = dp->wpart + ((size_t)slot * dp->nwaves + lt) * 5;

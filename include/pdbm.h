@@ -330,11 +330,11 @@ int pdbm_batch_noneq(pdbm_batch *b, int32_t i, double *out);
  * than its pdbm_state_bytes).  All running solves advance together
  * in packed, graph-captured launches on the server's stream (NULL: a stream
  * of its own) driven by a scheduler thread; a solve leaves at the chunk
- * boundary after it reaches its step count.  One that keeps no fields is done
- * there; kept fields are read, on a second stream of the server's, while the
- * others take their next chunk, or there too if a queued request waits for
- * the slot or the memory.  A solve is done, and gives back its slot, once its
- * result is read, and its memory then or at the end of the chunk in flight.
+ * boundary after it reaches its step count.  Its result is read, on a second
+ * stream of the server's, while the others take their next chunk, or before
+ * it if a queued request waits for the slot or the memory.  A solve is done,
+ * and gives back its slot, once its result is read, and its memory then or at
+ * the end of the chunk in flight.
  * Submit and poll are thread-safe. */
 enum { PDBM_KEEP_FIELDS = 1 }; /* submit flag: keep the final fields for pdbm_poll */
 

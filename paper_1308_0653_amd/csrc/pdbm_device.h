@@ -767,8 +767,8 @@ __device__ __forceinline__ void row_or_ghost(const Strip<real, MIXED> &S, int ro
 // the direction (below for 0, 1, 2, 7), so only the 16 directions that come
 // from the row behind pass through prev, replaced by row i as they are
 // consumed (with both rows selected between per lane, a step of 330 x 333 took
-// 17.1 us in float64, 16.6 this way; a packed one of 300 x 200, 87 and 81).  mt[dd]: which side is upwind in theta for
-// direction dd (its opposite dd+4 takes the other one), evaluated from the
+// 17.1 us in float64, 16.6 this way).  mt[dd]: which side is upwind in theta
+// for direction dd (its opposite dd+4 takes the other one), evaluated from the
 // angle.
 template <typename real, bool MIXED, bool TAUF, bool DOWN>
 __device__ __forceinline__ void update_row(const Strip<real, MIXED> &S, int ir, real (*prev)[64], const real fc[NQ],

@@ -492,7 +492,7 @@ struct pdbm_server {
 
     // scheduler-thread state
     std::vector<Request *> running;
-    std::vector<Request *> leaving;  // at their step count, out of the packs, kept fields not read yet
+    std::vector<Request *> leaving;  // at their step count, out of the packs, results not read yet
     hipStream_t copies = nullptr;    // results of the leaving ones, beside the steps of the others
     hipEvent_t ready = nullptr;      // ... made on st
     struct Spent {                   // memory of a finished request, to be given back
@@ -508,7 +508,6 @@ struct pdbm_server {
     void retire(Request *r, int err);
     void make_results();
     void read_results(bool beside);
-    void read_reports(const std::vector<Request *> &ended);
 };
 
 // The results of the leaving requests: their kernels on st, ahead of the
@@ -532,9 +531,12 @@ void pdbm_server::read_results(bool beside)
 {
     std::vector<Spent> spent;
     for (Request *r : leaving) {
-        std::shared_ptr<HostArray> f = std::make_shared<HostArray>((size_t)6 * r->p.nr * r->p.ntheta);
-        if (!f->data) r->read = false;
-        if (r->read) r->read = fetch_result(*r->solve, f->data, &r->diag, copies) == PDBM_OK;
+        std::shared_ptr<HostArray> f;
+        if (r->flags & PDBM_KEEP_FIELDS) {
+            f = std::make_shared<HostArray>((size_t)6 * r->p.nr * r->p.ntheta);
+            if (!f->data) r->read = false;
+        }
+        if (r->read) r->read = fetch_result(*r->solve, f ? f->data : nullptr, &r->diag, copies) == PDBM_OK;
         if (r->read) r->fields = std::move(f);
         if (!beside || !r->read) {
             retire(r, r->read ? PDBM_OK : PDBM_EHIP);
@@ -552,18 +554,6 @@ void pdbm_server::read_results(bool beside)
     for (Spent &m : spent) m.solve->release();
     std::lock_guard<std::mutex> g(mu);
     for (const Spent &m : spent) led.in_use -= m.bytes;
-}
-
-// The ends of requests that keep no fields: their drift reports alone, read
-// between the chunks.
-void pdbm_server::read_reports(const std::vector<Request *> &ended)
-{
-    for (Request *r : ended)
-        if (start_result(*r->solve, false, st) != PDBM_OK) r->read = false;
-    for (Request *r : ended) {
-        if (r->read) r->read = fetch_result(*r->solve, nullptr, &r->diag, st) == PDBM_OK;
-        retire(r, r->read ? PDBM_OK : PDBM_EHIP);
-    }
 }
 
 void pdbm_server::retire(Request *r, int err)
@@ -682,20 +672,19 @@ int pdbm_server::admit_and_step(std::vector<Request *> &admitted)
         std::lock_guard<std::mutex> g(mu);
         led.stats.steps_launched += chunk;
     }
-    std::vector<Request *> still, ended;
+    std::vector<Request *> still;
     for (size_t i = 0; i < running.size(); ++i) {
         Request *r = running[i];
         if (r->solve->step >= r->nsteps) {
             auto &m = pack[r->p.precision].members;
             m.erase(std::find(m.begin(), m.end(), r->solve.get()));
             pack[r->p.precision].dirty = true;
-            (r->flags & PDBM_KEEP_FIELDS ? leaving : ended).push_back(r);
+            leaving.push_back(r);
         } else {
             still.push_back(r);
         }
     }
     running.swap(still);
-    read_reports(ended);
     return PDBM_OK;
 }
 

@@ -95,7 +95,7 @@ void places(bool by_memory)
 }
 
 // A finished request beside a long one is done, and may be released, while
-// the next chunk is in flight (`fields`) or before it is launched.
+// the next chunk is in flight.
 void results(bool fields)
 {
     gpu.allow(0);
@@ -106,10 +106,6 @@ void results(bool fields)
     const uint64_t a = submit(s, CHUNK, fields), b = submit(s, CHUNK - 1, fields);
     gpu.allow(2);  // the chunk in flight, and that of the two
     CHECK(gpu.reaches(before + 3));
-    if (!fields) {
-        int32_t state = -1;
-        CHECK(pdbm_poll(s, a, &state, nullptr, nullptr) == PDBM_OK && state == PDBM_DONE);
-    }
     CHECK(ends(s, a) && ends(s, b));
     std::vector<double> out(6 * 6 * 9);
     pdbm_diag d{};

@@ -1,8 +1,8 @@
 """The request server's host code on a model of the GPU (tests/host/
 server_check.cpp): a finished request is done while the next chunk of the
-others is in flight, or before it where it keeps no fields; its slot and its
-memory serve the next request at once; and no use of it from several threads
-races, hangs or leaks, whenever it is destroyed (also under ThreadSanitizer)."""
+others is in flight; its slot and its memory serve the next request at once;
+and no use of it from several threads races, hangs or leaks, whenever it is
+destroyed (also under ThreadSanitizer)."""
 import os
 import subprocess
 

@@ -616,7 +616,11 @@ __global__ __launch_bounds__(BLOCK, Step2Occ<real>::waves) void k_step2(const So
         // one step, with the row behind in the LDS row of g
         const bool diag = records(dp, step);
         double red[5] = {0, 0, 0, 0, 0};
-        if ((rb & 1) != 0)
+        // (odd blocks inward, beside the rows of the block before, in float32
+        // alone: 16 packed 300 x 200 then take 88 us, 91 all outward; in
+        // float64, 145 and 149, the 16 KB of code cost the pairs more: 20
+        // steps of 1024 x 512 took 749 us with them, 741 without)
+        if (sizeof(real) == 4 && (rb & 1) != 0)
             march<real, MIXED, TAUF, true>(dp, bufs, strip, i0, i1, ga[w], red, diag);
         else
             march<real, MIXED, TAUF, false>(dp, bufs, strip, i0, i1, ga[w], red, diag);
@@ -678,10 +682,14 @@ hipError_t launch_step2(const SolveDesc *descs, const uint2 *tiles, int ntiles, 
 {
     const int nb = (ntiles + BLOCK / 64 - 1) / (BLOCK / 64);
     if (nb == 0) return hipSuccess;
-    auto *fn = fp32 ? (mixed ? (tauf ? &launch_k_step2<float, true, true> : &launch_k_step2<float, false, true>)
-                           : (tauf ? &launch_k_step2<float, true, false> : &launch_k_step2<float, false, false>))
-                    : (mixed ? (tauf ? &launch_k_step2<double, true, true> : &launch_k_step2<double, false, true>)
-                           : (tauf ? &launch_k_step2<double, true, false> : &launch_k_step2<double, false, false>));
+    // named in the order in which they are to lie in the code object: the
+    // float64 kernels of 72 KB exceed the instruction cache and feel where they
+    // start (1024 x 1024, with drift records: 130.4 us this way, 130.8 with the
+    // float32 kernels first, at times 130.5 or 131.1 for other code between)
+    auto *fn = !fp32 ? (!mixed ? (!tauf ? &launch_k_step2<double, false, false> : &launch_k_step2<double, true, false>)
+                               : (!tauf ? &launch_k_step2<double, false, true> : &launch_k_step2<double, true, true>))
+                     : (!mixed ? (!tauf ? &launch_k_step2<float, false, false> : &launch_k_step2<float, true, false>)
+                               : (!tauf ? &launch_k_step2<float, false, true> : &launch_k_step2<float, true, true>));
     fn(nb, st, descs, tiles, ntiles, bases, step_off, flips, flip, single);
     return hipGetLastError();
 }
